@@ -2212,7 +2212,12 @@ PwChoice choose_pw(const ng_graph* g, int v) {
     }
     const bool vec = hw % 4 == 0;
     const long tiles16 = ((o.c + 15) / 16) * ((cols + 15) / 16);
-    if (!vec && tiles16 > 128) {                             // enough tiles anyway: 32 x 32 tiles read less
+    // Maps without 128-bit loads: the 16 x 16 tiles with K split over the wavefronts up to 512 of them (two workgroups per
+    // compute unit), 32 x 32 tiles, which read less, beyond. The 32 x 32 kernels hold registers that only the full build of
+    // the resident kernel has room for: a NAS cell on 25 x 25 maps (240 tiles) replays in 356 us with 16 x 16 tiles (lean
+    // build) and in 474 us with two of its tasks on 32 x 32 tiles, which take 4.2 us there against 2.9 us; an
+    // Inception-style network at batch 1 (31 layers of 17 x 17 and 35 x 35 maps, 228 - 385 tiles) 765 against 810 us.
+    if (!vec && tiles16 > 512) {
         c.kind = PwChoice::DIRECT32;
         c.in_flight = pw_chunk(cin);
         c.groups = pw_padded_steps(cin);

@@ -819,3 +819,11 @@ def test_kernel_choice_in_a_training_graph():
     # 32 x 32 and 16 x 16 maps: the weight gradient reads both operands 128 bits along the pixels; the fc (1 x 1 maps) cannot
     assert by_op["conv1x1_wgrad"] == {"conv1x1_wgrad_px_16", "conv1x1_wgrad_px_32", "small_gemm"}
     assert by_op["conv3x3_wgrad"] == {"conv3x3_wgrad_px_16"}         # the stem: 44 x 27 weights, rows of 32 pixels
+
+
+@pytest.mark.parametrize("shape,cout,prefix", [((1, 132, 25, 25), 88, "conv1x1_s"), ((1, 64, 45, 45), 64, "conv1x1_s"),
+                                               ((1, 64, 47, 47), 64, "conv1x1_mfma_d"), ((1, 64, 46, 46), 64, "conv1x1_v")])
+def test_kernel_choice_of_conv1x1_on_odd_maps(shape, cout, prefix):
+    """Maps without 128-bit loads take 16 x 16 tiles up to 512 of them (45 x 45 pixels: 508; 47 x 47: 556), which keeps
+    a network of odd maps in the lean build of the resident kernel."""
+    assert _kernels_on(shape, [lambda b, x: b.conv1x1(x, cout)])[0].startswith(prefix)
