@@ -74,6 +74,17 @@ __device__ __forceinline__ void stg4(float* base, float* p, float4 v, bool far) 
     __builtin_memcpy(&u, &v, sizeof u);
     __builtin_amdgcn_raw_buffer_store_b128(u, tensor_rsrc(base), byte_offset(base, p), 0, kPolicyDeviceScope);
 }
+// 128 bits at an address that is only a multiple of four bytes (rows or planes that are no multiple of four floats)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 ldg4_any(const float* base, const float* p, bool far) {
+    if (far) return ldg4(base, p, true);
+    const f32x4_any v = *reinterpret_cast<const f32x4_any*>(p);
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void stg4_any(float* base, float* p, float4 v, bool far) {
+    if (far) stg4(base, p, v, true);
+    else *reinterpret_cast<f32x4_any*>(p) = f32x4_any{v.x, v.y, v.z, v.w};
+}
 // per-lane tensor (concat picks its source per lane): single relaxed device-scope accesses
 __device__ __forceinline__ float ldg_any(const float* p, bool far) {
     return far ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
@@ -1502,9 +1513,11 @@ __device__ __forceinline__ void pool3x3_col_tile(const PoolArgs& a, int tile, fl
 
 // ------------------------------------------------------------------------------------
 // dwconv for large tensors of small planes (batches of CIFAR-sized maps): a workgroup takes as many whole
-// (image, channel) planes as fit 1024 input pixels, stages them in LDS with a border of zeros (one 128-bit load per
+// (image, channel) planes as fit 256 quads of input pixels, stages them in LDS with a border of zeros (one 128-bit load per
 // thread; the taps then need no bounds and no index arithmetic beyond a row pitch) and every thread computes four
-// outputs side by side from K rows of 3 S + K values, stored with one 128-bit store.
+// outputs side by side from K rows of 3 S + K values, stored with one 128-bit store. A quad is four pixels of a row; in a
+// row that is no multiple of four the last quad starts four pixels before the end, and the values it shares with the quad
+// before it are loaded, computed and stored twice.
 // ------------------------------------------------------------------------------------
 template <int K, int S, bool FIN, class Wait>
 __device__ __forceinline__ void dwconv_lds_impl(const DwArgs& a, int tile, float* smem, int tid, bool live, Wait& wait) {
@@ -1514,15 +1527,16 @@ __device__ __forceinline__ void dwconv_lds_impl(const DwArgs& a, int tile, float
     const int PW = a.W + 2 * p, PHW = (a.H + 2 * p) * PW;
     const int G = a.planes_per_tile;
     const int p0 = tile * G, np = live ? min(G, a.total / HWo - p0) : 0;
-    const int xq = 4 * tid, gi = xq / HW, xrem = xq - gi * HW, iy = xrem / a.W, ix = xrem - iy * a.W;
-    const int oq = 4 * tid, go = oq / HWo, orem = oq - go * HWo, oy = orem / a.Wo, ox = orem - oy * a.Wo;
+    const int QW = (a.W + 3) >> 2, QWo = (a.Wo + 3) >> 2;
+    const int gi = tid / (a.H * QW), xrem = tid - gi * (a.H * QW), iy = xrem / QW, ix = min(4 * (xrem - iy * QW), a.W - 4);
+    const int go = tid / (a.Ho * QWo), orem = tid - go * (a.Ho * QWo), oy = orem / QWo, ox = min(4 * (orem - oy * QWo), a.Wo - 4);
     const bool xin = gi < np, oin = go < np;
     float w[K * K];
     const float* wt = a.w + ((p0 + min(go, max(np - 1, 0))) % a.C) * (K * K);
 #pragma unroll
     for (int q = 0; q < K * K; ++q) w[q] = wt[q];              // filter taps: not produced by any task
     wait();
-    const float4 x4 = xin ? ldg4(a.x, a.x + (size_t)p0 * HW + xq, FIN) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 x4 = xin ? ldg4_any(a.x, a.x + (size_t)(p0 + gi) * HW + iy * a.W + ix, FIN) : make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();                                            // a previous tile of this workgroup has been read to the end
     for (int i = tid; i < G * PHW; i += kBlock) smem[i] = 0.f;
     __syncthreads();
@@ -1544,7 +1558,7 @@ __device__ __forceinline__ void dwconv_lds_impl(const DwArgs& a, int tile, float
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[j] = fmaf(w[da * K + db], v[j * S + db], acc[j]);   // taps in ascending order, as dwconv_tile
     }
-    stg4(a.y, a.y + (size_t)p0 * HWo + oq, make_float4(acc[0], acc[1], acc[2], acc[3]), fout);
+    stg4_any(a.y, a.y + (size_t)(p0 + go) * HWo + oy * a.Wo + ox, make_float4(acc[0], acc[1], acc[2], acc[3]), fout);
 }
 template <bool FIN, class Wait>
 __device__ __forceinline__ void dwconv_lds_tile(const DwArgs& a, int tile, float* smem, int tid, bool live, Wait& wait) {
@@ -2032,7 +2046,7 @@ long ceil_div(long a, long b) { return (a + b - 1) / b; }
 // activations once per 16 rows, which pays while the rows are few (the 64 x 64 LDS-staged GEMM tile otherwise).
 bool pw_px_applies(const GemmArgs& a) {
     const long hw = (long)a.Ho * a.Wo;
-    return hw % 4 == 0 && a.K % 4 == 0 && a.M <= 256 && a.bias == nullptr && (long)a.K * a.N * 4 < (1L << 31) &&
+    return hw >= 4 && a.K % 4 == 0 && a.M <= 256 && a.bias == nullptr && (long)a.K * a.N * 4 < (1L << 31) &&
            (long)a.M * a.N * 4 < (1L << 31);
 }
 // The classifier's GEMMs (1 x 1 maps, a few thousand outputs, K up to a few hundred): no tiles. K over the lanes of a
@@ -2042,7 +2056,15 @@ void set_small_gemm(Task& t, SmallGemmArgs a, void (*set)(Task&, const SmallGemm
     a.by_wave = a.sak == 1 && a.sbk == 1 && a.K >= 64;
     set(t, a, a.by_wave ? ceil_div((long)a.M * a.N, kBlock / 64) : ceil_div((long)a.M * a.N, kBlock));
 }
-long pw_px_tiles(const GemmArgs& a) { return ceil_div(ceil_div(a.N / 4, 16) * ceil_div(a.M, 16), 4); }
+long pw_px_tiles(const GemmArgs& a) {
+    const long hw = (long)a.Ho * a.Wo;
+    return ceil_div(ceil_div(a.N / hw * ceil_div(hw, 4), 16) * ceil_div(a.M, 16), 4);
+}
+// Backward kernels whose ragged edges (planes or rows that are no multiple of 16 or 4 pixels) cost extra work per edge: below
+// this many pixels (weight gradients) or elements (depthwise input gradient) a task is a few workgroups that wait for
+// memory once either way, and the general kernels stay. Above it, a training step of a NAS cell: 36 channels, 10 images of
+// 27 x 27 pixels 1090 -> 750 us; 24 channels, 60 images of 30 x 30 pixels 2945 -> 1225 us.
+constexpr long kRaggedMinPixels = 1024, kRaggedMinElements = 1 << 16;
 
 // Direct conv1x1: k steps per chunk by problem depth, and the padded step count of the packed copy.
 int pw_chunk(long cin) { return cin <= 64 ? 4 : (cin <= 128 ? 8 : 16); }
@@ -2342,8 +2364,11 @@ WgradPlan wgrad_plan(const ng_graph* g, int v) {
         p.small = true, p.splits = 1, p.k_per_split = (int)k;
         return p;
     }
-    p.px = (dy.h * dy.w) % 16 == 0 && dy.elems() * 4 < (1L << 31) && x.elems() * 4 < (1L << 31) &&
-           (nd.op == NG_OP_CONV1X1_WGRAD || (nd.p.stride == 1 && nd.p.pad == 1 && dy.w % 16 == 0 && dy.h == x.h && dy.w == x.w));
+    const long hw = dy.h * dy.w;
+    const bool c3 = nd.op == NG_OP_CONV3X3_WGRAD, whole = c3 ? dy.w % 16 == 0 : hw % 16 == 0;
+    p.px = hw >= 4 && (whole || k >= kRaggedMinPixels) && dy.elems() * 4 < (1L << 31) && x.elems() * 4 < (1L << 31) &&
+           (!c3 || (nd.p.stride == 1 && nd.p.pad == 1 && dy.w >= 4 && dy.h == x.h && dy.w == x.w));
+    k = dy.n * ceil_div(hw, 16) * 16;                           // an image is a whole number of slices of 16 pixels
     const long fm = ceil_div(m, 16), fn = ceil_div(n, 16);
     p.px = p.px && fm * fn <= 256;
     if (p.px) {
@@ -2362,7 +2387,7 @@ WgradPlan wgrad_plan(const ng_graph* g, int v) {
         }
         return p;
     }
-    gemm_split(m, n, k, &p.splits, &p.k_per_split);
+    gemm_split(m, n, dy.n * hw, &p.splits, &p.k_per_split);
     if (p.splits > 1) {
         p.ws_floats = (size_t)p.tiles * p.splits * tile_floats;
         p.cnt_words = ((size_t)p.tiles + 63) & ~(size_t)63;
@@ -2545,11 +2570,10 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
             DwArgs a{buf(nd.preds[0]), wf(0), buf(v), (int)o.c, (int)i0.h, (int)i0.w, (int)o.h, (int)o.w, total};
             const long n = ceil_div(total, kBlock);
             // large tensors of small planes (batches): whole planes through LDS, four outputs per thread
-            const long plane = (long)i0.h * i0.w, per_wg = plane <= 1024 ? 1024 / plane : 0;
+            const long quads = i0.h * ceil_div(i0.w, 4), per_wg = quads <= kBlock ? kBlock / quads : 0;
             const int bd = nd.p.k / 2;
-            if (total >= kDwLdsMinOutputs && (nd.p.k == 3 || nd.p.k == 5) && (nd.p.stride == 1 || nd.p.stride == 2) && i0.w % 4 == 0 &&
-                o.w % 4 == 0 && per_wg > 0 && (long)o.h * o.w <= plane &&
-                per_wg * (i0.h + 2 * bd) * (i0.w + 2 * bd) <= kSmemFloats) {
+            if (total >= kDwLdsMinOutputs && (nd.p.k == 3 || nd.p.k == 5) && (nd.p.stride == 1 || nd.p.stride == 2) && i0.w >= 4 &&
+                o.w >= 4 && per_wg > 0 && o.h * ceil_div(o.w, 4) <= quads && per_wg * (i0.h + 2 * bd) * (i0.w + 2 * bd) <= kSmemFloats) {
                 a.K = nd.p.k, a.S = nd.p.stride, a.planes_per_tile = (int)per_wg;
                 set_kernel<KID_DW_LDS>(t, a, ceil_div((long)o.n * o.c, per_wg));
                 break;
@@ -2822,9 +2846,11 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
                 a.w = wf(0);
                 const long plane = (long)a.H * a.W, planes = a.total / plane;
                 const int bd = a.K / 2;
-                const long per_wg = plane <= 1024 ? 1024 / plane : 0;
-                if ((a.K == 3 || a.K == 5) && (a.S == 1 || a.S == 2) && a.W % 4 == 0 && a.Wo % 4 == 0 && per_wg > 0 &&
-                    (long)a.Ho * a.Wo <= plane && per_wg * (a.Ho + 2 * bd) * (a.Wo + 2 * bd) <= kSmemFloats) {
+                const long quads = a.H * ceil_div(a.W, 4), per_wg = quads <= kBlock ? kBlock / quads : 0;
+                const bool whole = a.W % 4 == 0 && a.Wo % 4 == 0;  // ragged rows: LDS is read up to three floats beyond the last row
+                if ((a.K == 3 || a.K == 5) && (a.S == 1 || a.S == 2) && a.W >= 4 && a.Wo >= 4 && per_wg > 0 &&
+                    a.Ho * ceil_div(a.Wo, 4) <= quads && (whole || a.total >= kRaggedMinElements) &&
+                    per_wg * (a.Ho + 2 * bd) * (a.Wo + 2 * bd) + (whole ? 0 : 4) <= kSmemFloats) {
                     a.chunks = (int)per_wg;                        // whole planes of dx per workgroup, their dy staged in LDS
                     set_kernel<KID_DW_DGRAD_LDS>(t, a, ceil_div(planes, per_wg));
                     break;

@@ -277,6 +277,78 @@ def test_training_conv1x1_pixel_kernels(shape, cout):
     check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT, B.NG_MODE_GRAPH_MULTI), end_to_end=False)
 
 
+def _ragged_names(fwd, seeds, lr, op):
+    tw = workloads.training_graph(fwd, lr, seeds)
+    r = GraphRunner(tw)
+    r.schedule()
+    r.plan()
+    try:
+        return {B.ng_planned_task_kernel(r.g, v) for v, nd in enumerate(tw.nodes) if nd.op == op}
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("shape,cout", [((5, 20, 15, 15), 24),     # planes of 225 pixels: a short last slice of one pixel
+                                        ((4, 12, 18, 15), 40),     # 270: 14 pixels in the last slice, 32 x 32 blocks of weights
+                                        ((3, 36, 19, 19), 7),      # 361, rows used up to 7 of 16
+                                        ((300, 8, 2, 2), 12),      # 4 pixels a plane: one quad
+                                        ((160, 16, 1, 7), 20)])    # 7: a quad and three pixels
+def test_training_conv1x1_pixel_kernels_on_ragged_planes(shape, cout):
+    """Planes that are no multiple of 4 or 16 pixels, 1024 pixels and more in all: forward (with its batch-norm), input
+    gradient and weight gradient read pixels 128 bits at a time all the same."""
+    from workloads.model import Builder
+    b = Builder("conv1x1_ragged")
+    x = b.input(*shape)
+    c1 = b.bn_act(b.conv1x1(x, cout), relu=True)
+    c2 = b.bn_act(b.conv1x1(c1, shape[1]), relu=False)
+    f = b.fc(b.global_avgpool(b.add_n([c2, x])), 3)
+    rng = np.random.default_rng(8)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    seeds = {f: rng.standard_normal(fwd.nodes[f].shape).astype(np.float32)}
+    names = _ragged_names(fwd, seeds, 0.01, "conv1x1_wgrad") - {"small_gemm"}
+    assert names and all(n.startswith("conv1x1_wgrad_px") for n in names), names
+    assert _ragged_names(fwd, seeds, 0.01, "conv1x1_dgrad") == {"conv1x1_px_dgrad", "small_gemm"} or cout % 4 != 0
+    check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
+
+
+@pytest.mark.parametrize("shape,cout,kernel", [((3, 3, 19, 21), 9, "conv3x3_wgrad_px_16"), ((60, 3, 5, 5), 44, "conv3x3_wgrad_px_16"),
+                                               ((2, 20, 24, 25), 40, "conv3x3_wgrad_px_32"), ((80, 5, 4, 4), 7, "conv3x3_wgrad_px_16"),
+                                               ((3, 4, 30, 30), 33, "conv3x3_wgrad_px_16")])
+def test_training_conv3x3_weight_gradient_on_ragged_rows(shape, cout, kernel):
+    """Rows that are no multiple of 16 pixels: quads that run over a row's end, taps outside on all four sides, short slices."""
+    from workloads.model import Builder
+    b = Builder("conv3x3_ragged")
+    x = b.input(*shape)
+    c = b.bn_act(b.conv3x3(x, cout, 1, 1), relu=True)
+    f = b.fc(b.global_avgpool(c), 5)
+    rng = np.random.default_rng(6)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    seeds = {f: rng.standard_normal(fwd.nodes[f].shape).astype(np.float32)}
+    assert _ragged_names(fwd, seeds, 0.01, "conv3x3_wgrad") == {kernel}
+    check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
+
+
+@pytest.mark.parametrize("shape", [(24, 24, 12, 11), (9, 16, 27, 27), (31, 44, 7, 9), (3, 130, 30, 30), (40, 20, 10, 15)])
+def test_training_depthwise_on_ragged_rows(shape):
+    """Rows that are no multiple of four: forward (where the tensor is large enough), input and weight gradient on planes
+    staged in LDS, both filter sizes and strides, one plane to several per workgroup."""
+    from workloads.model import Builder
+    b = Builder("depthwise_ragged")
+    x = b.input(*shape)
+    pw = b.conv1x1(x, shape[1])
+    outs = [b.global_avgpool(b.dwconv(pw, k, s)) for k in (3, 5) for s in (1, 2)]
+    f = b.fc(b.add_n(outs), 4)
+    rng = np.random.default_rng(7)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    seeds = {f: rng.standard_normal(fwd.nodes[f].shape).astype(np.float32)}
+    assert _ragged_names(fwd, seeds, 0.01, "dwconv_dgrad") == {"dwconv_dgrad_lds"}
+    assert ("dwconv_lds" in _ragged_names(fwd, seeds, 0.01, "dwconv")) == (shape[0] * shape[1] * shape[2] * shape[3] >= 1 << 18)
+    check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
+
+
 def test_training_step_nas_cell_batch32_cifar():
     """The paper's training setting: batch 32, 32 x 32 inputs. One normal and one reduction cell of the
     NASNet-style recipe between a 3x3 stem and a 10-way classifier; 259 tasks in one DAG."""
