@@ -196,7 +196,8 @@ int ng_set_memory_reuse(ng_graph* g, int on);
  * input is a convolution result is applied by that convolution's kernel, a concat whose inputs
  * were all produced in place is not launched, and weight updates (NG_OP_SGD_UPDATE) whose output no
  * node reads are carried out together by the launch of the last of them on their stream (modes 1 and
- * 2: of the last of them in the submission order; same arithmetic per element), and the input gradient
+ * 2: of the last of them in the submission order; same arithmetic per element; that launch then also adds up
+ * the weight gradients whose kernels leave partial results and that nothing but updates reads), and the input gradient
  * and the parameter gradients of a batch-norm (NG_OP_BN_ACT_DGRAD, NG_OP_BN_ACT_WGRAD with the same dy
  * and x) are computed in one walk over dy and x by the launch of whichever of the two comes first, if
  * both are on one stream (always, in modes 1 and 2); likewise the input gradient and the weight gradient

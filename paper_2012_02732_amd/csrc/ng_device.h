@@ -268,7 +268,7 @@ struct GemmArgs {
     float* c;                  // forward: Y; dgrad: dX; wgrad: dW
     const float* bias;         // forward of an fc: [Cout], else nullptr
     float* ws;                 // wgrad: partial tiles [tiles][splits][64 * 64]
-    unsigned* cnt;             // wgrad: arrivals per tile [tiles], zero between replays
+    unsigned* cnt;             // wgrad: arrivals per tile [tiles], zero between replays; nullptr: the partial tiles are left for a later launch (SgdTile)
     int M, N, K;
     int Cin, Cout, H, W, Ho, Wo, stride, pad;
     int tiles_n;               // tiles along N
@@ -290,7 +290,7 @@ struct BnRawArgs {             // batch-norm with its four parameter vectors as 
     float eps;
     int relu, C, HW, N, total;
     float* ws;                 // wgrad, chunks > 1: per-chunk sums [C][chunks][2]
-    unsigned* cnt;             // wgrad, chunks > 1: arrivals per channel, zero between replays
+    unsigned* cnt;             // wgrad, chunks > 1: arrivals per channel, zero between replays; nullptr: the sums are left for a later launch (SgdTile)
     int chunks;                // wgrad: workgroups a channel's images are split over; dwconv_dgrad_lds: planes per workgroup
     float* dx;                 // bn_act_backward: the input gradient, written by the kernel of the parameter gradients
 };
@@ -307,7 +307,7 @@ struct DwGradArgs {            // depthwise backward; C, H, W, Ho, Wo, K, S of t
     float* y;                  // dgrad: dx [N][C][H][W]; wgrad: dW [C][K][K]
     int N, C, H, W, Ho, Wo, K, S, total;
     float* ws;                 // wgrad, chunks > 1: per-chunk partial sums [C][chunks][K K]
-    unsigned* cnt;             // wgrad, chunks > 1: arrivals per channel, zero between replays
+    unsigned* cnt;             // wgrad, chunks > 1: arrivals per channel, zero between replays; nullptr: the sums are left for a later launch (SgdTile)
     int chunks;                // wgrad: workgroups a channel's images are split over; dwconv_dgrad_lds: planes per workgroup
 };
 struct PoolGradArgs {          // pool backward; geometry of the FORWARD operator
@@ -332,16 +332,28 @@ struct SgdArgs {
     int offset, total;
 };
 
-// One workgroup's share of a batched update: up to kSgdTileElems consecutive elements of one update node, with the
-// addresses already advanced to the share's first element. A table of these in device memory is the whole
-// description of the launch.
-constexpr int kSgdTileElems = 1024;
+// One workgroup's share of a batched update: up to kSgdTileElems consecutive elements of one update node (kSgdSumElems if
+// the gradient is still in parts), with the addresses already advanced to the share's first element. A table of these in
+// device memory is the whole description of the launch.
+// A gradient in parts: the kernel that computed it left one partial result per split of its K range (or chunk of images) in
+// its workspace; the share adds them up in split order, stores the gradient and updates the weights. Element e of the
+// gradient tensor = sum over s of parts[base(e) + s * stride]:
+//   PARTS_PLANES  e = (row e / width, column e % width): base = row * splits * width + column, stride = width
+//                 (depthwise weights: a row = a channel's K K taps)
+//   PARTS_PAIRS   e = (t, c) = (e / width, e % width): base = c * splits * 2 + t, stride = 2 (batch-norm: gamma and beta of a channel)
+//   PARTS_BLOCKS  blocks of edge x edge elements of a matrix of `width` columns, `blocks` of them side by side: each block's
+//                 parts one after the other, stride = edge * edge (GEMM tiles)
+constexpr int kSgdTileElems = 1024, kSgdSumElems = 256;
+enum { PARTS_NONE = 0, PARTS_PLANES, PARTS_PAIRS, PARTS_BLOCKS };
 struct SgdTile {
     float* w;
-    const float* g;
+    float* g;                  // read, or (gradient in parts) written
     float* flag;               // the node's (1-element) output if this is the node's first share, else nullptr
+    const float* parts;        // workspace of the kernel that computed the gradient
     float lr;
     int count;
+    int kind, splits, first;   // first: the share's first element as an element of the gradient tensor
+    int width, edge, blocks;
 };
 struct SgdBatchArgs {
     const SgdTile* tiles;      // [ntiles]

@@ -178,8 +178,11 @@ void decide_launch_fusion(const ng_graph* g, const std::vector<Task>& tasks, boo
 void make_bn_backward_task(const Task& dgrad, const Task& wgrad, Task& t);
 bool can_pair(int kid_first, int kid_second);
 void make_pair_task(const Task& first, const Task& second, Task& t);
-void make_sgd_batch_task(const std::vector<Task>& tasks, const std::vector<int>& members, std::vector<SgdTile>& table,
-                         const SgdTile* table_dev, Task& t);
+SgdTile gradient_parts(const Task& wgrad);
+void leave_sum_to_later_launch(Task& wgrad);
+void gradients_left_in_parts(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, std::vector<char>& in_parts);
+void make_sgd_batch_task(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& members, const std::vector<char>& in_parts,
+                         std::vector<SgdTile>& table, const SgdTile* table_dev, Task& t);
 void build_launch_graph(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, LaunchGraph& out);
 // ng_resident_plan.cpp: xcds = 0 lets the cost model choose among 1, 2, 4, 8.
 int plan_resident(const ng_graph* g, int n_wg, int xcds, const PlanKnobs& knobs, ResidentPlan& plan);

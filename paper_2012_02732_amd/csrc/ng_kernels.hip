@@ -2085,17 +2085,59 @@ __global__ __launch_bounds__(kGroup) void xcd_probe_kernel(int* xcd_of_workgroup
 }  // namespace
 const void* xcd_probe_kernel_handle() { return reinterpret_cast<const void*>(&xcd_probe_kernel); }
 
-// The launch that carries out the update nodes `members` (their stand-alone tasks in `tasks`) at once. The shares of
-// the members are appended to `table`, the host copy of the device table that will sit at `table_dev`: the task's
-// argument points at its first share there.
-void make_sgd_batch_task(const std::vector<Task>& tasks, const std::vector<int>& members, std::vector<SgdTile>& table,
-                         const SgdTile* table_dev, Task& t) {
+// Where the partial results of a weight-gradient task are (kind PARTS_NONE: it has none, it writes the gradient itself), and
+// the same task with its sum left to a later launch.
+SgdTile gradient_parts(const Task& t) {
+    SgdTile p{};
+    switch (t.kid) {
+        case KID_GEMM_PW_WGRAD: case KID_GEMM_C3_WGRAD: case KID_PW_WGRAD_PX: case KID_PW_WGRAD_PX2: case KID_C3_WGRAD_PX: case KID_C3_WGRAD_PX2: {
+            GemmArgs a;
+            std::memcpy(&a, t.args, sizeof a);
+            if (a.splits <= 1) break;
+            p.kind = PARTS_BLOCKS, p.parts = a.ws, p.splits = a.splits, p.width = a.N, p.blocks = a.tiles_n;
+            p.edge = (t.kid == KID_GEMM_PW_WGRAD || t.kid == KID_GEMM_C3_WGRAD) ? kGemmTile : (t.kid == KID_PW_WGRAD_PX || t.kid == KID_C3_WGRAD_PX) ? 16 : 32;
+            break;
+        }
+        case KID_DW_WGRAD: {
+            DwGradArgs a;
+            std::memcpy(&a, t.args, sizeof a);
+            if (a.chunks > 1) p.kind = PARTS_PLANES, p.parts = a.ws, p.splits = a.chunks, p.width = a.K * a.K;
+            break;
+        }
+        case KID_BN_WGRAD: {
+            BnRawArgs a;
+            std::memcpy(&a, t.args, sizeof a);
+            if (a.chunks > 1) p.kind = PARTS_PAIRS, p.parts = a.ws, p.splits = a.chunks, p.width = a.C;
+            break;
+        }
+        default: break;
+    }
+    return p;
+}
+void leave_sum_to_later_launch(Task& t) {
+    if (t.kid == KID_DW_WGRAD) reinterpret_cast<DwGradArgs*>(t.args)->cnt = nullptr;
+    else if (t.kid == KID_BN_WGRAD) reinterpret_cast<BnRawArgs*>(t.args)->cnt = nullptr;
+    else reinterpret_cast<GemmArgs*>(t.args)->cnt = nullptr;
+}
+
+// The launch that carries out the update nodes `members` (their stand-alone tasks in `tasks`) at once; in_parts[v] != 0:
+// gradient node v is left in parts. The shares of the members are appended to `table`, the host copy of the device
+// table that will sit at `table_dev`: the task's argument points at its first share there.
+void make_sgd_batch_task(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& members, const std::vector<char>& in_parts,
+                         std::vector<SgdTile>& table, const SgdTile* table_dev, Task& t) {
     const size_t first = table.size();
     for (int v : members) {
         SgdArgs a;
         std::memcpy(&a, tasks[v].args, sizeof a);
-        for (int at = 0; at < a.total || at == 0; at += kSgdTileElems)
-            table.push_back(SgdTile{a.w + at, a.g + a.offset + at, at == 0 ? a.flag : nullptr, a.lr, std::min(a.total - at, kSgdTileElems)});
+        const int gradient = g->nodes[v].preds[0];
+        const bool parts = in_parts[gradient] != 0;
+        const int per = parts ? kSgdSumElems : kSgdTileElems;
+        for (int at = 0; at < a.total || at == 0; at += per) {
+            SgdTile s = parts ? gradient_parts(tasks[gradient]) : SgdTile{};
+            s.w = a.w + at, s.g = const_cast<float*>(a.g) + a.offset + at, s.flag = at == 0 ? a.flag : nullptr, s.lr = a.lr;
+            s.count = std::min(a.total - at, per), s.first = a.offset + at;
+            table.push_back(s);
+        }
     }
     t = Task();
     t.block[0] = kBlock;

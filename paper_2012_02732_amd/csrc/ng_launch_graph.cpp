@@ -108,6 +108,39 @@ void decide_launch_fusion(const ng_graph* g, const std::vector<Task>& tasks, boo
     }
 }
 
+// Which weight gradients the single-stream modes leave in parts for the one launch that carries out all updates
+// (`fused_into` as decided with one_stream): those that nothing but updates of that launch reads, each element by exactly
+// one of them. That launch is behind every other one that touches the gradient, so the gradient is whole before anybody
+// reads it; the node's own launch only leaves its partial results.
+void gradients_left_in_parts(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, std::vector<char>& in_parts) {
+    const int n = (int)g->nodes.size();
+    in_parts.assign(n, 0);
+    int last = -1;                                              // the update whose launch carries out the others
+    for (int v = 0; v < n; ++v)
+        if (tasks[v].kid == KID_SGD && fused_into[v] >= 0) last = fused_into[v];
+    if (last < 0) return;
+    std::vector<int64_t> read(n, 0);                            // elements of a gradient that updates of that launch take
+    std::vector<char> others(n, 0);
+    for (int v = 0; v < n; ++v) {
+        const bool gathered = tasks[v].kid == KID_SGD && (v == last || fused_into[v] == last);
+        for (size_t j = 0; j < g->nodes[v].preds.size(); ++j) {
+            if (gathered && j == 0) read[g->nodes[v].preds[0]] += g->nodes[v].p.cout;
+            else if (!gathered) others[g->nodes[v].preds[j]] = 1;
+        }
+    }
+    for (int v = 0; v < n; ++v) {
+        if (others[v] || read[v] != g->nodes[v].out.elems() || !tasks[v].fn || gradient_parts(tasks[v]).kind == PARTS_NONE) continue;
+        // exactly one update per element: sorted ranges that follow each other
+        std::vector<std::pair<int64_t, int64_t>> ranges;
+        for (int u = 0; u < n; ++u)
+            if (tasks[u].kid == KID_SGD && g->nodes[u].preds[0] == v) ranges.emplace_back(g->nodes[u].p.slice_lo[0], g->nodes[u].p.cout);
+        std::sort(ranges.begin(), ranges.end());
+        int64_t at = 0;
+        for (const auto& r : ranges) at = r.first == at ? at + r.second : -1;
+        in_parts[v] = at == g->nodes[v].out.elems();
+    }
+}
+
 // The multi-stream graph: one kernel node per launched task, in submission order; a node
 // depends on the previous task of its stream (FIFO order within a stream) and on the
 // producer of every planned event wait (Lambda). A task without a launch of its own keeps

@@ -639,34 +639,37 @@ int ng_bind(ng_graph* g, void* arena, size_t arena_bytes, void* const* hip_strea
     decide_launch_fusion(g, g->tasks, g->launch_fusion, true, single_fused_into);
     size_t sgd_shares = 0;
     for (int v = 0; v < (int)g->nodes.size(); ++v)
-        if (g->tasks[v].kid == KID_SGD && g->tasks[v].fn) sgd_shares += 2 * (size_t)(1 + g->nodes[v].p.cout / kSgdTileElems);   // once per table, rounded up
+        if (g->tasks[v].kid == KID_SGD && g->tasks[v].fn) sgd_shares += 2 * (size_t)(1 + g->nodes[v].p.cout / kSgdSumElems);   // once per table, rounded up
     if (sgd_shares > 0) NG_HIP(hipMalloc(reinterpret_cast<void**>(&rt.sgd_tiles), sgd_shares * sizeof(SgdTile)));
     std::vector<SgdTile> sgd_table;
-    auto fuse_launches = [&](const std::vector<int>& fused_into, std::vector<Task>& out) {
-        out = g->tasks;
+    auto fuse_launches = [&](const std::vector<int>& fused_into, const std::vector<char>& in_parts, std::vector<Task>& out) {
+        std::vector<Task> tasks = g->tasks;
+        for (size_t v = 0; v < tasks.size(); ++v)
+            if (in_parts[v]) leave_sum_to_later_launch(tasks[v]);
+        out = tasks;
         std::vector<std::vector<int>> batch(g->nodes.size());       // per last update: the updates its launch carries out, in submission order
         for (int v : g->sched.order) {
             const int u = fused_into[v];
             if (u < 0) continue;
-            if (g->tasks[v].kid == KID_SGD && u != v) {
+            if (tasks[v].kid == KID_SGD && u != v) {
                 batch[u].push_back(v);
-            } else if (g->tasks[v].kid == KID_BN_DGRAD && g->tasks[u].kid == KID_BN_WGRAD) {
-                make_bn_backward_task(g->tasks[v], g->tasks[u], out[u]);
-            } else if (g->tasks[v].kid == KID_BN_WGRAD && g->tasks[u].kid == KID_BN_DGRAD) {
-                make_bn_backward_task(g->tasks[u], g->tasks[v], out[u]);
-            } else if (can_pair(g->tasks[u].kid, g->tasks[v].kid)) {
-                make_pair_task(g->tasks[u], g->tasks[v], out[u]);
-            } else if (can_pair(g->tasks[v].kid, g->tasks[u].kid)) {
-                make_pair_task(g->tasks[v], g->tasks[u], out[u]);
-            } else if (g->tasks[v].kid == KID_BN_RAW && g->tasks[u].kid == KID_PW_PX_FWD) {
-                const BnRawArgs* bn = reinterpret_cast<const BnRawArgs*>(g->tasks[v].args);
+            } else if (tasks[v].kid == KID_BN_DGRAD && tasks[u].kid == KID_BN_WGRAD) {
+                make_bn_backward_task(tasks[v], tasks[u], out[u]);
+            } else if (tasks[v].kid == KID_BN_WGRAD && tasks[u].kid == KID_BN_DGRAD) {
+                make_bn_backward_task(tasks[u], tasks[v], out[u]);
+            } else if (can_pair(tasks[u].kid, tasks[v].kid)) {
+                make_pair_task(tasks[u], tasks[v], out[u]);
+            } else if (can_pair(tasks[v].kid, tasks[u].kid)) {
+                make_pair_task(tasks[v], tasks[u], out[u]);
+            } else if (tasks[v].kid == KID_BN_RAW && tasks[u].kid == KID_PW_PX_FWD) {
+                const BnRawArgs* bn = reinterpret_cast<const BnRawArgs*>(tasks[v].args);
                 GemmArgs* conv = reinterpret_cast<GemmArgs*>(out[u].args);
                 conv->bn_gamma = bn->gamma, conv->bn_beta = bn->beta, conv->bn_mean = bn->mean, conv->bn_var = bn->var;
                 conv->bn_y = bn->y, conv->bn_eps = bn->eps, conv->bn_relu = bn->relu;
             } else if (u != v) {
-                const BnArgs* bn = reinterpret_cast<const BnArgs*>(g->tasks[v].args);
+                const BnArgs* bn = reinterpret_cast<const BnArgs*>(tasks[v].args);
                 const Epilogue ep{bn->scale, bn->shift, bn->y, bn->relu};
-                if (takes_c3_args(g->tasks[u].kid)) reinterpret_cast<C3Args*>(out[u].args)->ep = ep;
+                if (takes_c3_args(tasks[u].kid)) reinterpret_cast<C3Args*>(out[u].args)->ep = ep;
                 else reinterpret_cast<PwArgs*>(out[u].args)->ep = ep;
             }
             out[v].fn = nullptr;
@@ -674,11 +677,14 @@ int ng_bind(ng_graph* g, void* arena, size_t arena_bytes, void* const* hip_strea
         for (int u = 0; u < (int)g->nodes.size(); ++u) {
             if (batch[u].empty()) continue;
             batch[u].push_back(u);
-            make_sgd_batch_task(g->tasks, batch[u], sgd_table, rt.sgd_tiles, out[u]);
+            make_sgd_batch_task(g, tasks, batch[u], in_parts, sgd_table, rt.sgd_tiles, out[u]);
         }
     };
-    fuse_launches(g->launch_fused_into, g->launch_tasks);
-    fuse_launches(single_fused_into, g->single_tasks);
+    // In the single-stream modes that launch also adds up the weight gradients that their kernels leave in parts.
+    std::vector<char> in_parts(g->nodes.size(), 0);
+    fuse_launches(g->launch_fused_into, in_parts, g->launch_tasks);
+    gradients_left_in_parts(g, g->tasks, single_fused_into, in_parts);
+    fuse_launches(single_fused_into, in_parts, g->single_tasks);
     if (sgd_table.size() > sgd_shares) return g->fail(NG_EINVAL, "ng_bind: %zu shares of weight updates, room for %zu", sgd_table.size(), sgd_shares);
     if (!sgd_table.empty()) NG_HIP(hipMemcpy(rt.sgd_tiles, sgd_table.data(), sgd_table.size() * sizeof(SgdTile), hipMemcpyHostToDevice));
 

@@ -349,6 +349,36 @@ def test_training_depthwise_on_ragged_rows(shape):
     check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
 
 
+def test_training_gradient_with_another_reader_is_whole_at_its_place():
+    """Single-stream modes leave weight gradients in parts for the launch of the updates only if nothing else reads them:
+    here a relu reads the weight gradients of a 1 x 1 convolution, a depthwise one and a batch-norm inside the graph, and a
+    second 1 x 1 convolution's gradient has no other reader. All of them, and the weights, as in the device-resident replay."""
+    from workloads.model import Builder, Node
+    b = Builder("gradient_readers")
+    x = b.input(9, 12, 16, 16)
+    c1 = b.bn_act(b.dwconv(b.conv1x1(x, 20), 3, 1), relu=True)
+    f = b.fc(b.global_avgpool(b.conv1x1(c1, 24)), 3)
+    rng = np.random.default_rng(9)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    seeds = {f: rng.standard_normal(fwd.nodes[f].shape).astype(np.float32)}
+    tw = workloads.training_graph(fwd, 0.01, seeds)
+    watched = [tw.wgrad_of[(v, 0)][0] for v in (1, 2, 3)]
+    readers = []
+    for node in watched:
+        tw.nodes.append(Node("relu", [node], {}, [], tw.nodes[node].shape))
+        readers.append(len(tw.nodes) - 1)
+    tw.outputs.extend(readers)
+    single, w_single = run_training_step(tw, B.NG_MODE_GRAPH_SINGLE)
+    resident, w_resident = run_training_step(tw, B.NG_MODE_DEVICE_RESIDENT)
+    for v in range(1, len(tw.nodes)):
+        assert np.array_equal(single[v], resident[v]), (v, tw.nodes[v].op)
+    for k in w_single:
+        assert np.array_equal(w_single[k], w_resident[k]), k
+    for node, reader in zip(watched, readers):
+        assert np.abs(single[node]).max() > 0 and np.array_equal(single[reader], np.maximum(single[node], 0)), node
+
+
 def test_training_step_nas_cell_batch32_cifar():
     """The paper's training setting: batch 32, 32 x 32 inputs. One normal and one reduction cell of the
     NASNet-style recipe between a 3x3 stem and a 10-way classifier; 259 tasks in one DAG."""
