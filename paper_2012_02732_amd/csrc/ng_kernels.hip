@@ -1668,7 +1668,6 @@ NG_KERNEL(KID_BN_BACKWARD, BnRawArgs, "bn_act_backward", bn_wgrad_tile < true)
 NG_KERNEL(KID_RELU_DGRAD, EltGradArgs, "relu_dgrad", elt_grad_tile < 0)
 NG_KERNEL(KID_GAP_DGRAD, EltGradArgs, "global_avgpool_dgrad", elt_grad_tile < 1)
 NG_KERNEL(KID_SLICE_PAD, EltGradArgs, "slice_pad", elt_grad_tile < 2)
-#undef NG_KERNEL
 // kernels without further template arguments
 #define NG_KERNEL0(KID, ARGS, NAME, FN)                                                        \
     template <> struct KernelOf<KID> {                                                         \
@@ -1704,6 +1703,26 @@ __device__ __forceinline__ void pair_tile(const PairArgs<typename KernelOf<KA>::
 }
 using PairDwArgs = PairArgs<DwGradArgs, DwGradArgs>;
 using PairPwArgs = PairArgs<GemmArgs, GemmArgs>;
+// The input gradient (a) and the weight gradient (b) of a 1 x 1 convolution in one launch. Every block of 16 x 16 or 32 x 32
+// weights reads a row block of dY and of X, every 16 rows of dX read all of dY: with 44 channels each tensor is read three
+// times. The pixels are cut into the splits of the weight gradient, and everything that reads the pixels of one split - na
+// workgroups of the input gradient, nb blocks of the weight gradient - runs on one XCD, one after the other, so that
+// memory is read once and the rest comes from that XCD's L2 (workgroups are dealt out to the 8 XCDs by index):
+// workgroup 8 j + x takes part j % (na + nb) of split 8 (j / (na + nb)) + x.
+template <int KB, bool FIN, class Wait>
+__device__ __forceinline__ void pw_backward_tile(const PairPwArgs& p, int tile, float* smem, int tid, bool live, Wait& wait) {
+    const int per = p.na + p.nb, j = tile >> 3;
+    const int split = 8 * (j / per) + (tile & 7), part = j % per - p.nb;
+    if (split >= p.b.splits) return;                            // the whole workgroup (launched alone, never by the resident kernel)
+    if (part >= 0) {
+        const int HW = p.a.Ho * p.a.Wo, quads = p.a.N / HW * ((HW + 3) >> 2);
+        const int MT = (p.a.M + 15) >> 4, PG = (quads + 15) >> 4, each = (PG + p.b.splits - 1) / p.b.splits;
+        const int task = part * 4 + (tid >> 6), pg = task / MT;
+        pw_px_wave<GEMM_PW_DGRAD, FIN>(p.a, split * each + pg, task - pg * MT, live && pg < each && split * each + pg < PG, tid, wait);
+    } else {
+        KernelOf<KB>::template tile<FIN>(p.b, (part + p.nb) * p.b.splits + split, smem, tid, live, wait);
+    }
+}
 #define NG_PAIR(KID, ARGS, NAME, KA, KB)                                                       \
     template <> struct KernelOf<KID> {                                                         \
         using Args = ARGS;                                                                     \
@@ -1715,9 +1734,10 @@ using PairPwArgs = PairArgs<GemmArgs, GemmArgs>;
     };
 NG_PAIR(KID_PAIR_DW, PairDwArgs, "dwconv_dgrad+wgrad", KID_DW_DGRAD, KID_DW_WGRAD)
 NG_PAIR(KID_PAIR_DW_LDS, PairDwArgs, "dwconv_dgrad_lds+wgrad", KID_DW_DGRAD_LDS, KID_DW_WGRAD)
-NG_PAIR(KID_PAIR_PW16, PairPwArgs, "conv1x1_px_dgrad+wgrad_16", KID_PW_PX_DGRAD, KID_PW_WGRAD_PX)
-NG_PAIR(KID_PAIR_PW32, PairPwArgs, "conv1x1_px_dgrad+wgrad_32", KID_PW_PX_DGRAD, KID_PW_WGRAD_PX2)
 #undef NG_PAIR
+NG_KERNEL(KID_PAIR_PW16, PairPwArgs, "conv1x1_px_dgrad+wgrad_16", pw_backward_tile < KID_PW_WGRAD_PX)
+NG_KERNEL(KID_PAIR_PW32, PairPwArgs, "conv1x1_px_dgrad+wgrad_32", pw_backward_tile < KID_PW_WGRAD_PX2)
+#undef NG_KERNEL
 NG_KERNEL0(KID_SGD_BATCH, SgdBatchArgs, "sgd_update_batch", sgd_batch_tile)
 #undef NG_KERNEL0
 
@@ -2163,12 +2183,24 @@ static void set_pair(const Task& first, const Task& second, Task& t) {
     t.block[0] = kBlock;
     set_kernel<KID>(t, p, first.ntiles + second.ntiles);
 }
+template <int KID>
+static void set_pw_backward(const Task& dgrad, const Task& wgrad, Task& t) {
+    PairPwArgs p{};
+    std::memcpy(&p.a, dgrad.args, sizeof p.a);
+    std::memcpy(&p.b, wgrad.args, sizeof p.b);
+    const long hw = (long)p.a.Ho * p.a.Wo, groups = ceil_div(p.a.N / hw * ceil_div(hw, 4), 16);
+    p.na = (int)ceil_div(ceil_div(groups, p.b.splits) * ceil_div(p.a.M, 16), 4);
+    p.nb = (int)(wgrad.ntiles / p.b.splits);
+    t = Task();
+    t.block[0] = kBlock;
+    set_kernel<KID>(t, p, ceil_div(p.b.splits, 8) * 8 * (p.na + p.nb));
+}
 void make_pair_task(const Task& first, const Task& second, Task& t) {
     switch (pair_kid(first.kid, second.kid)) {
         case KID_PAIR_DW: set_pair<KID_PAIR_DW>(first, second, t); break;
         case KID_PAIR_DW_LDS: set_pair<KID_PAIR_DW_LDS>(first, second, t); break;
-        case KID_PAIR_PW16: set_pair<KID_PAIR_PW16>(first, second, t); break;
-        case KID_PAIR_PW32: set_pair<KID_PAIR_PW32>(first, second, t); break;
+        case KID_PAIR_PW16: set_pw_backward<KID_PAIR_PW16>(first, second, t); break;
+        case KID_PAIR_PW32: set_pw_backward<KID_PAIR_PW32>(first, second, t); break;
         default: t = first; break;
     }
 }
@@ -2414,14 +2446,22 @@ WgradPlan wgrad_plan(const ng_graph* g, int v) {
     const long fm = ceil_div(m, 16), fn = ceil_div(n, 16);
     p.px = p.px && fm * fn <= 256;
     if (p.px) {
-        // blocks of B x B fragments of 16 x 16 weights, each split over K so that the task has about two workgroups per
-        // compute unit; a wavefront wants four slices of 16 pixels at least, and the last workgroup of a block adds up
-        // `splits` partial blocks
+        // Blocks of B x B fragments of 16 x 16 weights, each split over K: 512 pixels a split (eight slices of 16 for each of
+        // the four wavefronts: one batch of loads) up to 128 splits, which somebody has to add up; where that leaves compute
+        // units idle, 256 pixels for about two workgroups each. Training step of a NAS cell with 44 channels on 32 x 32
+        // maps: batch 32 (64 splits) 1072 us, with 128 splits 1097; batch 96 (128 splits) 2187 us, with 64 splits 2220 -
+        // 2230, with 32 splits 2266.
         p.block = fm * fn <= 16 ? 1 : 2;
         p.tiles = ceil_div(fm, p.block) * ceil_div(fn, p.block);
-        const long most = p.block == 1 ? 64 : 32;
-        const long want = std::max<long>(1, std::min<long>({ceil_div(k, 256), std::max<long>(1, 512 / p.tiles), most}));
-        p.k_per_split = (int)(ceil_div(ceil_div(k, want), 64) * 64);
+        const long most = 128;
+        const long want = std::max<long>({1, std::min(k / 512, most), std::min<long>({ceil_div(k, 256), 512 / p.tiles, 64})});
+        // of the splits near that (each a multiple of 64 pixels) the one whose XCDs, which take every eighth split, are
+        // busiest for the shortest time
+        long best = -1;
+        for (long per = ceil_div(ceil_div(k, std::min(want * 5 / 4, most)), 64); per <= ceil_div(ceil_div(k, std::max<long>(1, want * 3 / 4)), 64); ++per) {
+            const long cost = ceil_div(ceil_div(k, per * 64), 8) * per;
+            if (best < 0 || cost < best) best = cost, p.k_per_split = (int)(per * 64);
+        }
         p.splits = (int)ceil_div(k, p.k_per_split);
         if (p.splits > 1) {
             p.ws_floats = (size_t)p.tiles * p.splits * 256 * p.block * p.block;

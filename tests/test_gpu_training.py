@@ -292,7 +292,9 @@ def _ragged_names(fwd, seeds, lr, op):
                                         ((4, 12, 18, 15), 40),     # 270: 14 pixels in the last slice, 32 x 32 blocks of weights
                                         ((3, 36, 19, 19), 7),      # 361, rows used up to 7 of 16
                                         ((300, 8, 2, 2), 12),      # 4 pixels a plane: one quad
-                                        ((160, 16, 1, 7), 20)])    # 7: a quad and three pixels
+                                        ((160, 16, 1, 7), 20),     # 7: a quad and three pixels
+                                        ((67, 8, 32, 32), 12),     # 68608 pixels: more splits of K than one batch of partial sums
+                                        ((38, 68, 32, 31), 72)])   # ... in blocks of 32 x 32 weights, on short slices
 def test_training_conv1x1_pixel_kernels_on_ragged_planes(shape, cout):
     """Planes that are no multiple of 4 or 16 pixels, 1024 pixels and more in all: forward (with its batch-norm), input
     gradient and weight gradient read pixels 128 bits at a time all the same."""
