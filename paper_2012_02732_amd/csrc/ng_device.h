@@ -221,7 +221,7 @@ struct PwArgs {
     int Cin, Cout, HW, cols;   // cols = N * HW
     int tiles_n;               // tiles along the column (pixel) axis
     const float* wp;           // direct kernels: weights repacked into MFMA operand order
-                               // (kernels with the activations pixel-major in LDS: [Cin / 16][CoutP][16], see pack_pw_patch_weights_kernel)
+                               // (patch-stationary kernels: split into three bf16 parts, see pack_split_weights_kernel)
     int ksteps;                // 32 x 32 kernels: k-steps of 4 in the packed copy (padded, a multiple of 4 * chunk);
                                // 16-row kernels: groups of 4 k-steps in the packed copy (a multiple of 4 * groups in flight)
     int mtiles;                // direct kernels: ceil(Cout / 16); pixel-major kernels: tiles along Cout
@@ -242,7 +242,7 @@ struct C3Args {
     int co_groups;             // channel groups (workgroups along Cout)
     // implicit-GEMM kernels: Y[Cout][cols] = W[Cout][9 Cin] * patches[9 Cin][cols]
     const float* wp;           // weights repacked into MFMA operand order, 4 k-steps per lane
-                               // (patch-stationary kernels: [tap * Cin / 16 + block][CoutP][16], see pack_c3_patch_weights_kernel)
+                               // (patch-stationary kernels: split into three bf16 parts, see pack_split_weights_kernel)
     int groups;                // groups of 4 k-steps in the packed copy (a multiple of 4 * groups in flight);
                                // LDS-staged and patch-stationary kernels: input channels of the packed copy
     int stride;

@@ -97,13 +97,15 @@ __device__ __forceinline__ float4 ldg4_any_far(const float* p) {
     return make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// LDS floats every workgroup owns: the largest users are the conv3x3 input patches (4 x 33 x 34; 256 pixels x 20).
+// LDS floats every workgroup owns: the largest user is the conv3x3 input patch of the vector-ALU kernel (4 x 33 x 34).
 constexpr int kSmemFloats = 5120;
-// ... and what the conv3x3 kernels with a patch of up to 640 pixels get instead (stand-alone kernels: only they; the
-// resident kernel: every workgroup of the build that contains them)
-constexpr int kSmemFloatsWide = 12800;
+// ... and what the patch-stationary kernels get instead: 24 floats (16 channels in three bf16 parts) for 256 pixels, or for up
+// to 640. Stand-alone kernels: only they; the resident kernel: every workgroup of the build that contains them.
+constexpr int kSmemFloatsPatch = 24 * 256, kSmemFloatsWide = 24 * 640;
 constexpr bool has_wide_patch(int kid) { return kid == KID_C3_Q32 || kid == KID_C3_Q64 || kid == KID_C3_Q128; }
-constexpr int smem_floats(int kid) { return has_wide_patch(kid) ? kSmemFloatsWide : kSmemFloats; }
+constexpr int smem_floats(int kid) {
+    return has_wide_patch(kid) ? kSmemFloatsWide : kid == KID_PW_P32 ? 2 * kSmemFloatsPatch : is_c3_patch(kid) || is_pw_patch(kid) ? kSmemFloatsPatch : kSmemFloats;
+}
 
 // ------------------------------------------------------------------------------------
 // bn_act / relu: y = x * s[c] + t[c] (s, t folded from gamma, beta, mean, var), optional ReLU
@@ -682,140 +684,200 @@ __device__ __forceinline__ void conv3x3_lds_tile(const C3Args& a, int tile, floa
 }
 
 // ------------------------------------------------------------------------------------
-// conv3x3 for many output pixels (large maps, batches), patch-stationary: Y[Cout x pixels] = W[Cout x 9 Cin] * patches.
-// A tile is TM = 32 FM output channels by a run of TN = 32 FN consecutive output pixels of one image (row-major, so a run
-// may wrap over several rows). K is walked in blocks of 16 input channels, and within a block tap by tap:
-//   * B operand. The input pixels the run needs - its rows plus the halo, (W + 2 pad) wide with the padding stored as
-//     zeros - are kept in LDS for one block of 16 channels, pixel-major, 20 floats per pixel, the 16 channels of a
-//     pixel in the order p = 4 (k % 4) + k / 4: v_mfma_f32_16x16x4_f32 step s takes k = 4 s + g from lane group g, so
-//     one 128-bit LDS read gives a lane its operands of all four steps. A tap is an address shift
-//     ((dr (W + 2 pad) + dc) pixels), so the nine taps of a block run off ONE patch without a barrier between them: 9 x
-//     4 FM FN matrix instructions per wavefront per pair of barriers, and each input element is fetched once per
-//     tile and block instead of once per tap.
-//   * A operand. The weights were repacked at bind time into [tap * blocks + block][CoutP][16] with the same order of
-//     the 16 k: the 16 rows x 64 bytes a wavefront needs for one fragment are 1 KiB in a row, and every lane loads its
-//     four operands with one 128-bit load straight from memory (L2) into registers, three slices ahead. No LDS, no
-//     barrier and no vector ALU work for A.
-//   * Filling the patch: a thread owns up to 4 PM / 256 (pixel, group of 4 channels) items; their global offsets are
-//     worked out once per tile (out-of-image and padding positions get an offset beyond the buffer's size, for which
-//     a buffer load returns 0), so a fill is four 32-bit loads with a scalar channel offset and one 128-bit LDS write
-//     per item. The loads of block b + 1 are issued in the middle of block b's taps.
-// Four wavefronts as 2 x 2, each 16 FM x 16 FN. Needs Cin % 16 == 0 and a patch of at most PM pixels.
+// fp32 products on the bf16 matrix cores. A value is split into three bf16 parts, x = h + m + l (each the rest rounded to
+// nearest even; 3 x 8 significant bits: the rest after l is below 2^-26 of x), and of the nine products of two split values
+// the six of 2^-18 and larger are formed: h h in an accumulator of its own, h m, m h, m m, h l and l h in a second one,
+// added once at the end. v_mfma_f32_32x32x16_bf16 does 16 times the work of v_mfma_f32_16x16x4_f32 per cycle, six of them
+// replace sixteen cycles by six. The large accumulator is rounded once per 16 k instead of once per 4 k, so that the results
+// are closer to 64 bits than those of the fp32 instructions: 2-norm of the error over that of the result, K = 288 - 4032:
+// 0.7 - 3.0e-7 against 2.2 - 7.6e-7. (All six in one accumulator: 2.3 - 8.3e-7, which is why there are two.)
+// Infinities have no such split (inf - inf), and values of 3.39e38 and more round to one: a wavefront that finds a result
+// that is not finite works its outputs out again with fp32 multiply-adds.
 // ------------------------------------------------------------------------------------
-template <int FM, int FN, int PM, bool FIN, class Wait>
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr int kSplitFragBytes = 3 * 64 * 16;            // 32 rows x 16 k of packed weights: three parts x 64 lanes x 8 bf16
+
+// two values at a time: the parts of x0 in the low halves of h, m, l, those of x1 in the high halves
+__device__ __forceinline__ void split_bf16x3(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+    h = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
+    const float r0 = x0 - __builtin_bit_cast(float, h << 16), r1 = x1 - __builtin_bit_cast(float, h & 0xffff0000u);
+    m = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
+    const float q0 = r0 - __builtin_bit_cast(float, m << 16), q1 = r1 - __builtin_bit_cast(float, m & 0xffff0000u);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{q0, q1}), bf16x2));
+}
+__device__ __forceinline__ void split8(const float (&v)[8], u32x4 (&part)[3]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        unsigned h, m, l;
+        split_bf16x3(v[2 * q], v[2 * q + 1], h, m, l);
+        part[0][q] = h, part[1][q] = m, part[2][q] = l;
+    }
+}
+// 32 x 32 outputs, 16 k: high += ah bh, low += the five smaller products
+__device__ __forceinline__ void mfma_split(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x16& high, f32x16& low) {
+    constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {0, 0, 1, 2, 0, 1};
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+        f32x16& d = p == 0 ? high : low;
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[pa[p]]), __builtin_bit_cast(bf16x8, b[pb[p]]), d, 0, 0, 0);
+    }
+}
+__device__ __forceinline__ bool all_finite(const f32x16& v) {
+    float z = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) z = fmaf(v[q], 0.f, z);       // NaN if any is not finite
+    return z == 0.f;
+}
+
+// ------------------------------------------------------------------------------------
+// conv3x3 for many output pixels (large maps, batches), patch-stationary: Y[Cout x pixels] = W[Cout x 9 Cin] * patches.
+// A tile is TM output channels by a run of TN consecutive output pixels of one image (row-major, so a run may wrap over
+// several rows). K is walked in blocks of 16 input channels, and within a block tap by tap, in split bf16 (above):
+//   * B operand. The input pixels the run needs - its rows plus the halo, (W + 2 pad) wide with the padding stored as
+//     zeros - are kept in LDS for one block of 16 channels, already split: three planes, 32 bytes per pixel and plane. Lane
+//     (r, g) takes channels 8 g .. 8 g + 7 of pixel r with one 128-bit read per part; which half of a pixel's 32 bytes holds
+//     which eight channels alternates every four pixels, so that eight consecutive lanes hit all banks. A tap is an
+//     address shift ((dr (W + 2 pad) + dc) pixels): the nine taps of a block run off ONE patch without a barrier between
+//     them, and each input element is fetched and split once per tile and block instead of once per tap.
+//   * A operand. The weights were split and repacked at bind time into [block * 9 + tap][CoutP / 32][part][lane][8], so a
+//     fragment is three 128-bit loads of 1 KiB in a row, straight from memory (L2) into registers, three slices ahead.
+//   * Filling the patch: a thread owns up to 2 PM / 256 (pixel, 8 channels) items; their global offsets are worked out once
+//     per tile (out-of-image and padding positions get an offset beyond the buffer's size, for which a buffer load returns
+//     0), so a fill is eight 32-bit loads with a scalar channel offset and three 128-bit LDS writes per item. The loads of
+//     block b + 1 are issued in the middle of block b's taps.
+// A wavefront owns 32 FM x 32 FN outputs. ROWS = 64: 2 x 2 wavefronts; 32: 1 x 4; 96: 2 x 2 of which the upper two own 64
+// rows and the lower two 32 (which are which alternates from tile to tile, so that the SIMDs of a compute unit, each of
+// which gets the same wavefront of every workgroup, share the work).
+// What bounds it: the vector L1 (weights: 3 KiB per fragment and wavefront), at 35 - 40 % of the matrix rate; with
+// v_mfma_f32_16x16x4_f32 the matrix rate did (0.65 - 0.75 of it). Layers at batch 32, us before and after: 17 x 17 192 -> 192
+// 58 -> 39, 8 x 8 448 -> 384 69 -> 47, 147 x 147 32 -> 64 282 -> 224, 73 x 73 80 -> 192 391 -> 295.
+// Needs Cin % 16 == 0 and a patch of at most PM pixels.
+// ------------------------------------------------------------------------------------
+template <int ROWS, int FN, int PM, bool FIN, class Wait>
 __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, float* smem, int tid, bool live, Wait& wait) {
     const bool fout = wait.far_out();
-    constexpr int WM = 16 * FM, WN = 16 * FN, TM = 2 * WM, TN = 2 * WN, LD = 20;
-    constexpr int ITEMS = 4 * PM / kBlock;
+    constexpr int NW = ROWS == 32 ? 4 : 2, FM = ROWS == 96 ? 2 : 1, TM = ROWS, TN = 32 * FN * NW, ST = 3;
+    constexpr int ITEMS = 2 * PM / kBlock, PLANE = 2 * PM;          // PLANE: one part of the patch, in units of 16 bytes
     constexpr unsigned kOutside = 0x80000000u;          // beyond any tensor (num_records < 2^31): the load returns 0
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
-    static_assert(PM * LD <= (PM > 256 ? kSmemFloatsWide : kSmemFloats) && PM % 64 == 0, "LDS budget");
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int r = lane & 15, g = lane >> 4;
+    static_assert(PM * 24 <= (PM > 256 ? kSmemFloatsWide : kSmemFloatsPatch) && PM % 128 == 0 && (ROWS == 32 || ROWS == 64 || ROWS == 96), "LDS budget");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, g = lane >> 5;
     const int by = tile % a.co_groups, bt = tile / a.co_groups;
+    const int wn = wave % NW, wm = ROWS == 96 ? (wave / NW + bt) & 1 : wave / NW;
     const int img = bt / a.tiles_xy, seg = bt - img * a.tiles_xy;
-    const int m0 = by * TM;
+    const int m0 = by * TM, mw = m0 + wm * 32 * FM;     // this wavefront's first row
     const int HWo = a.Ho * a.Wo, HW = a.H * a.W;
     const int p0 = seg * TN, npx = min(TN, HWo - p0);
     const int oy_a = p0 / a.Wo, oy_b = (p0 + npx - 1) / a.Wo;
     const int iy_a = oy_a * a.stride - a.pad, Wp = a.W + 2 * a.pad, P = ((oy_b - oy_a) * a.stride + 3) * Wp;
-    const int blocks = a.groups / 16, n_slices = 9 * blocks, CoutP = a.co_groups * TM;
+    const int blocks = a.groups / 16, Mf = a.co_groups * (TM / 32);
     const __amdgpu_buffer_rsrc_t xr =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.x), 0, (a.tiles_n / a.tiles_xy) * a.Cin * HW * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wp), 0, n_slices * CoutP * 64, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wp), 0, 9 * blocks * Mf * kSplitFragBytes, 0x00020000);
 
-    // this thread's fill items: (pixel of the patch, channels j, j + 4, j + 8, j + 12 of the block)
+    // this thread's fill items: (pixel of the patch, channels 8 j .. 8 j + 7 of the block)
     unsigned goff[ITEMS];
     int loff[ITEMS];
 #pragma unroll
     for (int t = 0; t < ITEMS; ++t) {
         const int idx = tid + kBlock * t;
-        const int j = idx / P, pixel = idx - j * P;
+        const int j = idx >= P ? 1 : 0, pixel = idx - (idx >= P ? P : 0);
         const int pr = pixel / Wp, pc = pixel - pr * Wp;
         const int iy = iy_a + pr, ix = pc - a.pad;
-        const bool item = live && idx < 4 * P;
+        const bool item = live && idx < 2 * P;
         const bool inside = item && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-        goff[t] = inside ? (unsigned)(((img * a.Cin + j) * HW + iy * a.W + ix) * 4) : kOutside;
-        loff[t] = item ? pixel * (LD / 4) + j : -1;     // in units of 4 floats
+        goff[t] = inside ? (unsigned)(((img * a.Cin + 8 * j) * HW + iy * a.W + ix) * 4) : kOutside;
+        loff[t] = item ? 2 * pixel + (j ^ ((pixel >> 2) & 1)) : -1;     // in units of 16 bytes
     }
-    // where this lane's B fragments start in the patch (tap 0), and its A rows in a slice of the packed weights
-    int lbase[FN];
+    // the patch pixel under tap 0 of this lane's output pixels
+    int base[FN];
 #pragma unroll
     for (int jn = 0; jn < FN; ++jn) {
-        const int px = p0 + min(wn * WN + jn * 16 + r, npx - 1);
+        const int px = p0 + min((wn * FN + jn) * 32 + r, npx - 1);
         const int oy = px / a.Wo, ox = px - oy * a.Wo;
-        lbase[jn] = ((oy - oy_a) * a.stride * Wp + ox * a.stride) * LD + 4 * g;
+        base[jn] = (oy - oy_a) * a.stride * Wp + ox * a.stride;
     }
-    const unsigned va_off = (unsigned)(((wm * WM + r) * 16 + 4 * g) * 4);
 
-    f32x4 acc[FM][FN];
+    f32x16 high[FM][FN], low[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int jn = 0; jn < FN; ++jn) acc[i][jn] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int jn = 0; jn < FN; ++jn)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) high[i][jn][q] = 0.f, low[i][jn][q] = 0.f;
 
-    u32x4 pv[ITEMS];
+    float pv[ITEMS][8];
     // Loads are issued unconditionally and in a fixed order (idle items read "outside"): the compiler then counts
     // exactly how many younger loads may stay in flight at each wait.
     auto fill_load = [&](int block) {
 #pragma unroll
-        for (int t = 0; t < ITEMS; ++t) {
-            u32x4 v;
+        for (int t = 0; t < ITEMS; ++t)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_raw_buffer_load_b32(xr, goff[t], (unsigned)((block * 16 + 4 * q) * HW * 4), kIn);
-            pv[t] = v;
-        }
+            for (int q = 0; q < 8; ++q)
+                pv[t][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, goff[t], (unsigned)((block * 16 + q) * HW * 4), kIn));
     };
     auto fill_store = [&]() {
 #pragma unroll
-        for (int t = 0; t < ITEMS; ++t)
-            if (loff[t] >= 0) reinterpret_cast<u32x4*>(smem)[loff[t]] = pv[t];
+        for (int t = 0; t < ITEMS; ++t) {
+            u32x4 part[3];
+            split8(pv[t], part);
+            if (loff[t] >= 0) {
+                u32x4* s = reinterpret_cast<u32x4*>(smem) + loff[t];
+                s[0] = part[0], s[PLANE] = part[1], s[2 * PLANE] = part[2];
+            }
+        }
     };
-    u32x4 af[3][FM];
+    u32x4 af[ST][FM][3];
     auto a_load = [&](int slice, int stage) {
-        const int block = slice / 9, tap = slice - 9 * block;
-        const unsigned so = (unsigned)(((tap * blocks + block) * CoutP + m0) * 64);
+        const unsigned so = (unsigned)((slice * Mf + mw / 32) * kSplitFragBytes);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) af[stage][i] = __builtin_amdgcn_raw_buffer_load_b128(wr, va_off + i * 1024, so, 0);
+        for (int i = 0; i < FM; ++i) {
+            if (ROWS == 96 && i == 1 && wm == 1) break;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) af[stage][i][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, so + (unsigned)((i * 3 + p) * 1024), 0);
+        }
+    };
+    auto b_load = [&](u32x4 (&bf)[FN][3], int tap) {
+        const int shift = (tap / 3) * Wp + tap % 3;
+#pragma unroll
+        for (int jn = 0; jn < FN; ++jn) {
+            const int pixel = base[jn] + shift;
+            const u32x4* s = reinterpret_cast<const u32x4*>(smem) + 2 * pixel + (g ^ ((pixel >> 2) & 1));
+            bf[jn][0] = s[0], bf[jn][1] = s[PLANE], bf[jn][2] = s[2 * PLANE];
+        }
     };
 
     wait();
     if (live) {
         fill_load(0);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) a_load(d, d);
+        for (int d = 0; d < ST; ++d) a_load(d, d);
         fill_store();
     }
     __syncthreads();
+#pragma unroll 1                                        // unrolled twice it holds 64 registers more and runs 10 - 15 % slower
     for (int block = 0; block < blocks; ++block) {
         if (live) {
-            f32x4 bf[2][FN];
-#pragma unroll
-            for (int jn = 0; jn < FN; ++jn) bf[0][jn] = *reinterpret_cast<const f32x4*>(smem + lbase[jn]);
+            u32x4 bf[2][FN][3];
+            b_load(bf[0], 0);
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap) {
-                const int slice = block * 9 + tap, stage = tap % 3;
-                if (tap < 8) {                          // next tap's B fragments, before this tap's matrix instructions
-                    const int shift = (((tap + 1) / 3) * Wp + (tap + 1) % 3) * LD;
-#pragma unroll
-                    for (int jn = 0; jn < FN; ++jn) bf[(tap + 1) & 1][jn] = *reinterpret_cast<const f32x4*>(smem + lbase[jn] + shift);
-                }
+                if (tap < 8) b_load(bf[(tap + 1) & 1], tap + 1);   // next tap's B fragments, before this tap's matrix instructions
                 if (tap == 3) {
                     fill_load(min(block + 1, blocks - 1));
                     __builtin_amdgcn_sched_barrier(0);  // keep the loads here: the compiler would sink them to their use
                 }
-                f32x4 afr[FM];
 #pragma unroll
-                for (int i = 0; i < FM; ++i) afr[i] = __builtin_bit_cast(f32x4, af[stage][i]);
+                for (int i = 0; i < FM; ++i) {
+                    if (ROWS == 96 && i == 1 && wm == 1) break;
 #pragma unroll
-                for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-#pragma unroll
-                        for (int jn = 0; jn < FN; ++jn)
-                            acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[i][s4], bf[tap & 1][jn][s4], acc[i][jn], 0, 0, 0);
-                a_load(min(slice + 3, n_slices - 1), stage);
+                    for (int jn = 0; jn < FN; ++jn) mfma_split(af[tap % ST][i], bf[tap & 1][jn], high[i][jn], low[i][jn]);
+                }
+                a_load(block * 9 + tap + ST, tap % ST);        // beyond the last slice: zeros
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -824,169 +886,197 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
         __syncthreads();
     }
     if (!live) return;
+    bool finite = true;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int jn = 0; jn < FN; ++jn) {
-            const int cl = wn * WN + jn * 16 + r;
+            high[i][jn] += low[i][jn];
+            finite = finite && all_finite(high[i][jn]);
+        }
+    if (__any(!finite)) {                               // not the split's arithmetic: plain fp32, from memory
+        const int rows = ROWS == 96 && wm == 1 ? 32 : 32 * FM;
+        for (int jn = 0; jn < FN; ++jn) {
+            const int cl = (wn * FN + jn) * 32 + r;
             if (cl >= npx) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int m = m0 + wm * WM + i * 16 + 4 * g + q;
-                if (m < a.Cout) store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, acc[i][jn][q], fout);
+            const int oy = (p0 + cl) / a.Wo, ox = (p0 + cl) - oy * a.Wo;
+            for (int m = mw + 16 * g; m < mw + rows; m += (m & 15) == 15 ? 17 : 1) {    // lane group g: rows 16 g .. 16 g + 15 of every 32
+                if (m >= a.Cout) break;
+                float sum = 0.f;
+                for (int k = 0; k < 9 * a.Cin; ++k) {
+                    const int ci = k / 9, tap = k - 9 * ci;
+                    const int iy = oy * a.stride - a.pad + tap / 3, ix = ox * a.stride - a.pad + tap % 3;
+                    const bool inside = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+                    const size_t at = ((size_t)img * a.Cin + ci) * HW + (inside ? iy * a.W + ix : 0);
+                    const float x = ldg(a.x, a.x + at, FIN);
+                    sum = fmaf(a.w[(size_t)m * a.Cin * 9 + k], inside ? x : 0.f, sum);
+                }
+                store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, sum, fout);
             }
         }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        if (ROWS == 96 && i == 1 && wm == 1) break;
+#pragma unroll
+        for (int jn = 0; jn < FN; ++jn) {
+            const int cl = (wn * FN + jn) * 32 + r;
+            if (cl >= npx) continue;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int m = mw + i * 32 + 8 * (q / 4) + 4 * g + q % 4;
+                if (m < a.Cout) store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, high[i][jn][q], fout);
+            }
+        }
+    }
 }
 
-// W[Cout][Cin][3][3] -> [tap * (CinP / 16) + block][CoutP][16], the 16 channels of a block in the order
-// p = 4 (k % 4) + k / 4 (position p holds k = 4 (p % 4) + p / 4); zero where m >= Cout or the channel >= Cin
-__global__ __launch_bounds__(kBlock) void pack_c3_patch_weights_kernel(const float* w, float* wq, int Cout, int Cin, int CinP, int CoutP, long total) {
+// The weights of both patch-stationary kernels, W[Cout][Cin][TAPS]: -> [block * TAPS + tap][Mf][part][lane][8 bf16], block = 16
+// input channels, Mf = fragments of 32 rows; lane (r, g) holds row r, channels 8 g .. 8 g + 7; zero where m >= Cout.
+// One thread per (slice, fragment, lane).
+__global__ __launch_bounds__(kBlock) void pack_split_weights_kernel(const float* w, float* wq, int Cout, int Cin, int taps, int Mf, long total) {
     const long idx = (long)blockIdx.x * kBlock + threadIdx.x;
     if (idx >= total) return;
-    const int p = (int)(idx & 15);
-    const long row = idx >> 4;
-    const int m = (int)(row % CoutP), slice = (int)(row / CoutP);
-    const int kp = slice * 16 + 4 * (p & 3) + (p >> 2);
-    const int tap = kp / CinP, ci = kp - tap * CinP;
-    wq[idx] = (m < Cout && ci < Cin) ? w[((size_t)m * Cin + ci) * 9 + tap] : 0.f;
+    const int lane = (int)(idx & 63);
+    const long f = idx >> 6;
+    const int mf = (int)(f % Mf), slice = (int)(f / Mf), block = slice / taps, tap = slice - block * taps;
+    const int m = mf * 32 + (lane & 31), c = block * 16 + 8 * (lane >> 5);
+    float v[8];
+    for (int q = 0; q < 8; ++q) v[q] = m < Cout && c + q < Cin ? w[((size_t)m * Cin + c + q) * taps + tap] : 0.f;
+    u32x4 part[3];
+    split8(v, part);
+    for (int p = 0; p < 3; ++p) reinterpret_cast<u32x4*>(wq)[(f * 3 + p) * 64 + lane] = part[p];
 }
 
 // ------------------------------------------------------------------------------------
 // conv1x1 / fc for many output pixels on the plan of the patch-stationary conv3x3: Y[Cout x cols] = W[Cout x Cin] X[Cin x cols],
-// tile = 32 FM output channels x 64 consecutive columns (a run may cross from one image into the next). KB blocks of 16
-// input channels of the tile's columns sit in LDS, pixel-major (16 KB + 4 floats per column, the 16 channels of a block in
-// the order the matrix instruction consumes them, so a lane's operands of four steps are one 128-bit read); the weights
-// ([Cin / 16][CoutP][16], same channel order) go from memory straight into operands, one chunk ahead. Per pair of barriers
-// a wavefront issues 8 KB FM matrix instructions. A thread fills one column's four-channel group per block: its global
-// offset is worked out once per tile (columns beyond the end: an offset for which the buffer load returns 0).
-// Four wavefronts as 2 x 2, each 16 FM x 32. Needs Cin % 16 == 0.
+// tile = TM output channels x 64 consecutive columns (a run may cross from one image into the next), in split bf16. KB blocks of
+// 16 input channels of the tile's columns sit in LDS, split into three parts (32 bytes per column and part, as above), in two
+// buffers: while one is multiplied, the next is split into the other and the loads of the one after that are in flight - one
+// barrier per KB blocks. The weights ([Cin / 16][CoutP / 32][part][lane][8]) go from memory straight into operands, one
+// chunk ahead. ROWS = 64: 2 x 2 wavefronts of 32 x 32 outputs. ROWS = 32 (fewer than 200 tiles of 64 x 64): 1 x 2, and the
+// other two wavefronts take every second block of 16 channels; the halves of the sums meet in LDS at the end.
+// Splitting the activations (5.5 vector instructions per element for 64 rows) and the vector L1 bound it: 17 x 17 768 -> 192 at
+// batch 32 35 -> 28 us, 8 x 8 2048 -> 320 49 -> 39 us with the fp32 matrix instructions and with these.
+// Needs Cin % 16 == 0.
 // ------------------------------------------------------------------------------------
-template <int FM, int KB, bool FIN, class Wait>
+template <int ROWS, int KB, bool FIN, class Wait>
 __device__ __forceinline__ void conv1x1_patch_tile(const PwArgs& a, int tile, float* smem, int tid, bool live, Wait& wait) {
     const bool fout = wait.far_out();
-    constexpr int FN = 2, WM = 16 * FM, WN = 16 * FN, TM = 2 * WM, TN = 2 * WN, LD = 16 * KB + 4;
+    constexpr int TM = ROWS, TN = 64, KW = ROWS == 32 ? 2 : 1, OWN = KB / KW;
+    constexpr int PLANE = 2 * TN, BUFFER = KB * 3 * PLANE, ITEMS = KB / 2;                // LDS in units of 16 bytes
     constexpr unsigned kOutside = 0x80000000u;          // beyond any tensor (num_records < 2^31): the load returns 0
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
-    static_assert(TN * LD <= kSmemFloats && TN * 4 == kBlock, "LDS budget; one fill item per thread");
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1, r = lane & 15, g = lane >> 4;
+    static_assert(2 * BUFFER * 4 <= (KB == 2 ? kSmemFloatsPatch : 2 * kSmemFloatsPatch) && KB % 2 == 0 && TN * 4 == kBlock && (ROWS == 32 || ROWS == 64), "LDS budget");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = ROWS == 32 ? wave >> 1 : 0, wm = ROWS == 32 ? 0 : wave >> 1, wn = wave & 1, r = lane & 31, g = lane >> 5;
     const int by = tile % a.mtiles, bx = tile / a.mtiles;
-    const int m0 = by * TM, n0 = bx * TN;
-    const int blocks = a.ksteps / 16, chunks = (blocks + KB - 1) / KB, CoutP = a.mtiles * TM;
+    const int mw = by * TM + wm * 32, n0 = bx * TN;
+    const int blocks = a.ksteps / 16, chunks = (blocks + KB - 1) / KB, Mf = a.mtiles * (TM / 32);
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.x), 0, a.cols * a.Cin * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wp), 0, blocks * CoutP * 64, 0x00020000);
-    // this thread's fill item: column c of the tile, channels j, j + 4, j + 8, j + 12 of every block
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wp), 0, blocks * Mf * kSplitFragBytes, 0x00020000);
+    // this thread's fill items: column c of the tile, channels 8 j .. 8 j + 7 of blocks b0, b0 + 2, .. of a chunk
+    const int c = tid % TN, j = (tid / TN) & 1, b0 = tid / (2 * TN);
     unsigned goff;
     {
-        const int c = tid % TN, j = tid / TN;
         const int col = n0 + c;
         const int img = col / a.HW, pix = col - img * a.HW;
-        goff = (live && col < a.cols) ? (unsigned)(((img * a.Cin + j) * a.HW + pix) * 4) : kOutside;
+        goff = (live && col < a.cols) ? (unsigned)(((img * a.Cin + 8 * j) * a.HW + pix) * 4) : kOutside;
     }
-    const int loff = (tid % TN) * (LD / 4) + tid / TN;   // in units of 4 floats
-    int lbase[FN];
-#pragma unroll
-    for (int jn = 0; jn < FN; ++jn) lbase[jn] = (wn * WN + jn * 16 + r) * LD + 4 * g;
-    const unsigned va_off = (unsigned)(((wm * WM + r) * 16 + 4 * g) * 4);
+    const int loff = b0 * 3 * PLANE + 2 * c + (j ^ ((c >> 2) & 1));
+    const int cl = wn * 32 + r, lbase = 2 * cl + (g ^ ((cl >> 2) & 1));
 
-    f32x4 acc[FM][FN];
+    f32x16 high, low;
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < FN; ++jn) acc[i][jn] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < 16; ++q) high[q] = 0.f, low[q] = 0.f;
 
-    u32x4 pv[KB];
+    float pv[ITEMS][8];
     // loads are issued unconditionally and in a fixed order (blocks beyond Cin read "outside"): the compiler then counts
     // exactly how many younger loads may stay in flight at each wait
     auto fill_load = [&](int chunk) {
 #pragma unroll
-        for (int b = 0; b < KB; ++b) {
-            const int block = chunk * KB + b;
-            const unsigned off = block < blocks ? goff : kOutside;
-            u32x4 v;
+        for (int t = 0; t < ITEMS; ++t) {
+            const int block = chunk * KB + b0 + 2 * t;
+            const unsigned off = goff != kOutside && block < blocks ? goff + (unsigned)(block * 16 * a.HW * 4) : kOutside;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = __builtin_amdgcn_raw_buffer_load_b32(xr, off, (unsigned)((block * 16 + 4 * q) * a.HW * 4), kIn);
-            pv[b] = v;
+            for (int q = 0; q < 8; ++q) pv[t][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, off, (unsigned)(q * a.HW * 4), kIn));
         }
     };
-    auto fill_store = [&]() {
+    u32x4* const lds = reinterpret_cast<u32x4*>(smem);
+    auto fill_store = [&](int buffer) {
 #pragma unroll
-        for (int b = 0; b < KB; ++b) reinterpret_cast<u32x4*>(smem)[loff + 4 * b] = pv[b];
+        for (int t = 0; t < ITEMS; ++t) {
+            u32x4 part[3];
+            split8(pv[t], part);
+            u32x4* s = lds + buffer * BUFFER + loff + t * 6 * PLANE;
+            s[0] = part[0], s[PLANE] = part[1], s[2 * PLANE] = part[2];
+        }
     };
-    u32x4 af[KB][FM];
-    auto a_load = [&](int slice, int stage) {           // a slice beyond Cin re-reads the last one: its activations are zeros
-        const unsigned so = (unsigned)((min(slice, blocks - 1) * CoutP + m0) * 64);
+    u32x4 af[OWN][3];
+    auto a_load = [&](int chunk, int own) {             // a block beyond Cin reads zeros
+        const unsigned so = (unsigned)(((chunk * KB + own * KW + kg) * Mf + mw / 32) * kSplitFragBytes);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) af[stage][i] = __builtin_amdgcn_raw_buffer_load_b128(wr, va_off + i * 1024, so, 0);
+        for (int p = 0; p < 3; ++p) af[own][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, so + (unsigned)(p * 1024), 0);
     };
 
     wait();
     if (live) {
         fill_load(0);
 #pragma unroll
-        for (int b = 0; b < KB; ++b) a_load(b, b);
-        fill_store();
+        for (int own = 0; own < OWN; ++own) a_load(0, own);
+        fill_store(0);
+        fill_load(1);
     }
     __syncthreads();
+#pragma unroll 1
     for (int chunk = 0; chunk < chunks; ++chunk) {
         if (live) {
-            f32x4 bf[2][FN];
+            const u32x4* s0 = lds + (chunk & 1) * BUFFER + kg * 3 * PLANE + lbase;
 #pragma unroll
-            for (int jn = 0; jn < FN; ++jn) bf[0][jn] = *reinterpret_cast<const f32x4*>(smem + lbase[jn]);
+            for (int own = 0; own < OWN; ++own) {
+                u32x4 bf[3];
 #pragma unroll
-            for (int b = 0; b < KB; ++b) {
-                if (b + 1 < KB) {
-#pragma unroll
-                    for (int jn = 0; jn < FN; ++jn) bf[(b + 1) & 1][jn] = *reinterpret_cast<const f32x4*>(smem + lbase[jn] + 16 * (b + 1));
-                }
-                if (b == 0) {
-                    fill_load(min(chunk + 1, chunks - 1));
-                    __builtin_amdgcn_sched_barrier(0);  // keep the loads here: the compiler would sink them to their use
-                }
-                f32x4 afr[FM];
-#pragma unroll
-                for (int i = 0; i < FM; ++i) afr[i] = __builtin_bit_cast(f32x4, af[b][i]);
-#pragma unroll
-                for (int s4 = 0; s4 < 4; ++s4)
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-#pragma unroll
-                        for (int jn = 0; jn < FN; ++jn)
-                            acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[i][s4], bf[b & 1][jn][s4], acc[i][jn], 0, 0, 0);
-                a_load((chunk + 1) * KB + b, b);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int p = 0; p < 3; ++p) bf[p] = s0[(own * KW * 3 + p) * PLANE];
+                mfma_split(af[own], bf, high, low);
+                a_load(chunk + 1, own);
             }
+            if (chunk + 1 < chunks) fill_store((chunk + 1) & 1);
+            fill_load(chunk + 2);
         }
-        __syncthreads();                                // every wavefront is done with this chunk
-        if (live && chunk + 1 < chunks) fill_store();
-        __syncthreads();
+        __syncthreads();                                // the chunk is used up, the next one is there
     }
-    if (!live) return;
+    high += low;
+    if (KW > 1) {                                       // the second half of K joins the first
+        if (kg == 1) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < FN; ++jn) {
-            const int col = n0 + wn * WN + jn * 16 + r;
-            if (col >= a.cols) continue;
-            const int img = col / a.HW, pix = col - img * a.HW;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int m = m0 + wm * WM + i * 16 + 4 * g + q;
-                if (m < a.Cout)
-                    store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * a.HW + pix, m, acc[i][jn][q] + (a.bias ? a.bias[m] : 0.f), fout);
-            }
+            for (int q = 0; q < 16; ++q) smem[(wn * 16 + q) * 64 + lane] = high[q];
         }
-}
-
-// W[Cout][Cin] -> [Cin / 16][CoutP][16], the 16 channels of a block in the order p = 4 (k % 4) + k / 4; zero where m >= Cout
-__global__ __launch_bounds__(kBlock) void pack_pw_patch_weights_kernel(const float* w, float* wq, int Cout, int Cin, int CoutP, long total) {
-    const long idx = (long)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= total) return;
-    const int p = (int)(idx & 15);
-    const long row = idx >> 4;
-    const int m = (int)(row % CoutP), block = (int)(row / CoutP);
-    const int k = block * 16 + 4 * (p & 3) + (p >> 2);
-    wq[idx] = (m < Cout && k < Cin) ? w[(size_t)m * Cin + k] : 0.f;
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) high[q] += smem[(wn * 16 + q) * 64 + lane];
+        }
+        __syncthreads();                                // the next tile writes here
+    }
+    const int col = n0 + cl;
+    if (!live || kg != 0 || col >= a.cols) return;
+    const int img = col / a.HW, pix = col - img * a.HW;
+    if (__any(!all_finite(high))) {                     // not the split's arithmetic: plain fp32, from memory
+        for (int m = mw + 16 * g; m < mw + 16 * g + 16 && m < a.Cout; ++m) {
+            float sum = 0.f;
+            for (int k = 0; k < a.Cin; ++k)
+                sum = fmaf(a.w[(size_t)m * a.Cin + k], ldg(a.x, a.x + ((size_t)img * a.Cin + k) * a.HW + pix, FIN), sum);
+            store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * a.HW + pix, m, sum + (a.bias ? a.bias[m] : 0.f), fout);
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int m = mw + 8 * (q / 4) + 4 * g + q % 4;
+        if (m < a.Cout)
+            store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * a.HW + pix, m, high[q] + (a.bias ? a.bias[m] : 0.f), fout);
+    }
 }
 
 // W[Cout][Cin] -> W^T[CinP][CoutP], zero where k >= Cin or m >= Cout
@@ -1642,13 +1732,13 @@ NG_KERNEL(KID_C3_M3A, C3AddArgs, "conv3x3_mfma_3_add", conv3x3_k4_tile < 3, true
 NG_KERNEL(KID_C3_M4A, C3AddArgs, "conv3x3_mfma_4_add", conv3x3_k4_tile < 4, true)
 NG_KERNEL(KID_C3_L32, C3Args, "conv3x3_lds_32x128", conv3x3_lds_tile < 32, 128, 16)
 NG_KERNEL(KID_C3_L64, C3Args, "conv3x3_lds_64x64", conv3x3_lds_tile < 64, 64, 32)
-NG_KERNEL(KID_PW_P32, PwArgs, "conv1x1_patch_32x64", conv1x1_patch_tile < 1, 4)
-NG_KERNEL(KID_PW_P64, PwArgs, "conv1x1_patch_64x64", conv1x1_patch_tile < 2, 2)
-NG_KERNEL(KID_C3_P64, C3Args, "conv3x3_patch_64x64", conv3x3_patch_tile < 2, 2, 256)
-NG_KERNEL(KID_C3_P96, C3Args, "conv3x3_patch_96x64", conv3x3_patch_tile < 3, 2, 256)
-NG_KERNEL(KID_C3_Q32, C3Args, "conv3x3_patch_32x128_wide", conv3x3_patch_tile < 1, 4, 640)
-NG_KERNEL(KID_C3_Q64, C3Args, "conv3x3_patch_64x64_wide", conv3x3_patch_tile < 2, 2, 640)
-NG_KERNEL(KID_C3_Q128, C3Args, "conv3x3_patch_64x128_wide", conv3x3_patch_tile < 2, 4, 640)
+NG_KERNEL(KID_PW_P32, PwArgs, "conv1x1_patch_32x64", conv1x1_patch_tile < 32, 4)
+NG_KERNEL(KID_PW_P64, PwArgs, "conv1x1_patch_64x64", conv1x1_patch_tile < 64, 2)
+NG_KERNEL(KID_C3_P64, C3Args, "conv3x3_patch_64x64", conv3x3_patch_tile < 64, 1, 256)
+NG_KERNEL(KID_C3_P96, C3Args, "conv3x3_patch_96x64", conv3x3_patch_tile < 96, 1, 256)
+NG_KERNEL(KID_C3_Q32, C3Args, "conv3x3_patch_32x128_wide", conv3x3_patch_tile < 32, 1, 640)
+NG_KERNEL(KID_C3_Q64, C3Args, "conv3x3_patch_64x64_wide", conv3x3_patch_tile < 64, 1, 640)
+NG_KERNEL(KID_C3_Q128, C3Args, "conv3x3_patch_64x128_wide", conv3x3_patch_tile < 64, 2, 640)
 NG_KERNEL(KID_GEMM_PW_FWD, GemmArgs, "gemm_conv1x1_fwd", gemm_tile < GEMM_PW_FWD)
 NG_KERNEL(KID_GEMM_PW_DGRAD, GemmArgs, "gemm_conv1x1_dgrad", gemm_tile < GEMM_PW_DGRAD)
 NG_KERNEL(KID_GEMM_PW_WGRAD, GemmArgs, "gemm_conv1x1_wgrad", gemm_tile < GEMM_PW_WGRAD)
@@ -2291,12 +2381,12 @@ PwChoice choose_pw(const ng_graph* g, int v) {
     // many output pixels, whole blocks of 16 input channels: activations pixel-major in LDS, weights straight from memory;
     // 64-row tiles unless that leaves most compute units without one
     const long tiles64 = ((o.c + 63) / 64) * ((cols + 63) / 64);
-    if (cols >= kPwPatchMinCols && cin % 16 == 0 && cin >= 64 && tiles64 >= 64 && cols * cin * 4 < (1L << 31) && !knob("NG_NO_PATCH_KERNELS")) {
+    if (cols >= kPwPatchMinCols && cin % 16 == 0 && cin >= 64 && tiles64 >= 64 && cols * cin * 4 < (1L << 31) && cin * (o.c + 63) * 6 < (1L << 31) && !knob("NG_NO_PATCH_KERNELS")) {
         c.kind = PwChoice::PW_PATCH;
         c.kid = tiles64 < 200 ? KID_PW_P32 : KID_PW_P64;
         const long tm = c.kid == KID_PW_P32 ? 32 : 64;
         c.groups = (int)cin;
-        c.packed = (size_t)cin * (size_t)((o.c + tm - 1) / tm * tm);       // [Cin / 16][CoutP][16]
+        c.packed = (size_t)cin * (size_t)((o.c + tm - 1) / tm * tm) * 3 / 2;   // [Cin / 16][CoutP / 32][3 parts][64 lanes][8 bf16]
         return c;
     }
     // large problems (many 64 x 64 tiles) keep the LDS-tiled throughput kernel
@@ -2340,7 +2430,8 @@ long patch_pixels(long tn, long W, long Ho, long Wo, long stride, long pad) {
 // its tile, a compute unit works its workgroups off side by side, so the estimate is (tiles per compute unit, rounded up)
 // x rows; one lone workgroup per compute unit cannot keep the matrix cores busy on its own (x 1.15).
 int choose_patch_kernel(const Shape& in, const Shape& out, long stride, long pad) {
-    if (in.c % 16 != 0 || in.n * in.c * in.h * in.w * 4 >= (1L << 31)) return KID_NONE;
+    // activations and packed weights (three 16-bit parts) within the reach of a buffer descriptor
+    if (in.c % 16 != 0 || in.n * in.c * in.h * in.w * 4 >= (1L << 31) || 9 * in.c * (out.c + 95) * 6 >= (1L << 31)) return KID_NONE;
     int best = KID_NONE;
     double best_cost = 0;
     for (const PatchKernel& k : kPatchKernels) {
@@ -2368,7 +2459,7 @@ PwChoice choose_c3(const ng_graph* g, int v) {
             if (k.kid == kid) {
                 c.kind = PwChoice::C3_PATCH, c.kid = kid;
                 c.groups = (int)cin;                                                             // CinP = Cin (a multiple of 16)
-                c.packed = (size_t)(9 * cin) * (size_t)(ceil_div(nd.out.c, k.tm) * k.tm);        // [9 Cin / 16][CoutP][16]
+                c.packed = (size_t)(9 * cin) * (size_t)(ceil_div(nd.out.c, k.tm) * k.tm) * 3 / 2;    // [9 Cin / 16][CoutP / 32][3 parts][64 lanes][8 bf16]
                 return c;
             }
     }
@@ -2539,12 +2630,12 @@ int pack_constants(ng_graph* g, int v, float* packed, void* stream) {
     const int cin = (int)g->nodes[nd.preds[0]].out.c * (c3 ? 9 : 1), cout = (int)nd.out.c;
     if (!nd.weights[0]) return g->fail(NG_EINVAL, "node %d: weight 0 is a null device pointer", v);
     const dim3 grid((unsigned)((c.packed + kBlock - 1) / kBlock)), block(kBlock);
-    if (c.kind == PwChoice::PW_PATCH)
-        pack_pw_patch_weights_kernel<<<grid, block, 0, static_cast<hipStream_t>(stream)>>>(
-            static_cast<const float*>(nd.weights[0]), packed, cout, cin, (int)(c.packed / (size_t)c.groups), (long)c.packed);
-    else if (c.kind == PwChoice::C3_PATCH)
-        pack_c3_patch_weights_kernel<<<grid, block, 0, static_cast<hipStream_t>(stream)>>>(
-            static_cast<const float*>(nd.weights[0]), packed, cout, cin / 9, c.groups, (int)(c.packed / (9 * (size_t)c.groups)), (long)c.packed);
+    if (c.kind == PwChoice::PW_PATCH || c.kind == PwChoice::C3_PATCH) {
+        const long threads = (long)(c.packed / 12);             // one per 8 weights in three parts of 16 bits
+        pack_split_weights_kernel<<<dim3((unsigned)ceil_div(threads, kBlock)), block, 0, static_cast<hipStream_t>(stream)>>>(
+            static_cast<const float*>(nd.weights[0]), packed, cout, c.groups, c3 ? 9 : 1,
+            (int)(c.packed / ((size_t)cin / 16 * (kSplitFragBytes / 4))), threads);
+    }
     else if (c.kind == PwChoice::LDS64)
         pack_pw_lds_weights_kernel<<<grid, block, 0, static_cast<hipStream_t>(stream)>>>(
             static_cast<const float*>(nd.weights[0]), packed, cout, cin, (int)(c.packed / (size_t)c.groups), (long)c.packed);

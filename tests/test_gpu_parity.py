@@ -168,6 +168,72 @@ def test_conv3x3_patch_kernels(shape, cout, kernel):
     check_all_nodes(w, (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_DEVICE_RESIDENT))
 
 
+# The patch-stationary convolutions multiply in three bf16 parts per value. Against 64 bits, ragged in every direction: their
+# large accumulator is rounded once per 16 products, and partial sums grow to the result, so the 2-norm of the error is at most
+# about 2^-24 sqrt(K / 16) of the result's; one more 2^-24 for the stored value.
+@pytest.mark.parametrize("op,shape,cout,kernel", [
+    ("conv3x3", (3, 48, 35, 37), 70, "conv3x3_patch_64x64"), ("conv3x3", (32, 32, 35, 35), 90, "conv3x3_patch_96x64"),
+    ("conv3x3", (2, 32, 70, 71), 24, "conv3x3_patch_32x128_wide"), ("conv3x3", (4, 16, 150, 151), 64, "conv3x3_patch_64x128_wide"),
+    ("conv1x1", (3, 80, 31, 33), 130, "conv1x1_patch_32x64"), ("conv1x1", (5, 112, 41, 43), 130, "conv1x1_patch_64x64")])
+def test_split_products_against_64_bits(op, shape, cout, kernel):
+    def build(b):
+        x = b.input(*shape)
+        b.conv3x3(x, cout, 1, 1) if op == "conv3x3" else b.conv1x1(x, cout)
+    w = single_op(build)
+    k = shape[1] * (9 if op == "conv3x3" else 1)
+    x, wt = torch.from_numpy(w.input).double(), torch.from_numpy(w.nodes[1].weights[0]).double()
+    ref = torch.nn.functional.conv2d(x, wt.view(cout, shape[1], *((3, 3) if op == "conv3x3" else (1, 1))), padding=1 if op == "conv3x3" else 0).numpy()
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        assert B.ng_task_kernel(r.g, 1) == kernel
+        for mode in (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT):
+            r.arena.zero_()
+            got = r.run(w.input, mode=mode)[1].astype(np.float64)
+            assert np.linalg.norm(got - ref) <= 2.0 ** -24 * (1 + np.sqrt(k / 16)) * np.linalg.norm(ref), mode
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("op,shape,cout", [("conv3x3", (3, 48, 35, 37), 70), ("conv3x3", (32, 32, 35, 35), 90),
+                                           ("conv1x1", (3, 80, 31, 33), 130), ("conv1x1", (5, 112, 41, 43), 130)])
+def test_split_products_of_infinities_and_huge_values(op, shape, cout):
+    """Infinities have no split, and values next to the largest fp32 number round to an infinite bf16: results that see one
+    are what fp32 gives, all others are untouched. A batch-norm rides on the convolution (its tensor too)."""
+    def build(b):
+        x = b.input(*shape)
+        y = b.conv3x3(x, cout, 1, 1) if op == "conv3x3" else b.conv1x1(x, cout)
+        b.bn_act(y, relu=True)
+    w = single_op(build)
+    clean = forward(w, keep=range(len(w.nodes)))
+    w.input[0, 5, 7, 9] = np.inf
+    w.input[1, 17, 20, 3] = 3.4e38                       # times weights of a few tenths at most: finite
+    w.input[2, 0, 30, 30] = -np.inf
+    w.input[2, 9, 11, 2] = np.nan
+    with np.errstate(all="ignore"):
+        ref = forward(w, keep=range(len(w.nodes)))
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        for mode in (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT):
+            r.arena.zero_()
+            r.set_input(w.input)
+            r.replay(mode)
+            r.sync()
+            got = r.output(1)
+            finite = np.isfinite(ref[1])
+            assert np.array_equal(np.isnan(got), np.isnan(ref[1])) and np.array_equal(np.isfinite(got), finite)
+            assert np.array_equal(got[np.isinf(ref[1])], ref[1][np.isinf(ref[1])])
+            huge = finite & (np.abs(ref[1]) > 1e30)
+            assert huge.any() and rel_err(got[huge], ref[1][huge]) <= TOL
+            rest = finite & ~huge
+            assert rel_err(got[rest], ref[1][rest]) <= TOL
+            bn, plain = r.output(2), np.isfinite(ref[2]) & (np.abs(ref[2]) < 1e30)
+            assert rel_err(bn[plain], ref[2][plain]) <= TOL and not np.array_equal(ref[2], clean[2])
+    finally:
+        r.close()
+
+
 # pool3x3 on tensors of a million outputs and more: four outputs of a column per thread, both modes, strides and
 # paddings; heights that leave a partial block of 1, 2 and 3 output rows (and none)
 @pytest.mark.parametrize("shape", [(8, 64, 45, 47), (2, 48, 149, 147), (16, 32, 96, 101), (16, 32, 97, 96), (8, 64, 64, 88)])
