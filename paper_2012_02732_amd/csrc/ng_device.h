@@ -28,6 +28,7 @@ enum Kid : int {
     // read it at shifted addresses; weights go from memory straight into matrix-instruction operands. Output tiles (rows x pixels)
     // 64 x 64 and 96 x 64 with a patch of up to 256 pixels; 32 x 128, 64 x 64 and 64 x 128 with up to 640 (wide images, stride 2)
     KID_C3_P64, KID_C3_P96, KID_C3_Q32, KID_C3_Q64, KID_C3_Q128,
+    KID_C3_SK,                       // the same for few output pixels: 32 x 32, K split over the wavefronts, each with a patch of up to 160 pixels
     // conv1x1 for many output pixels on the same plan (activations pixel-major in LDS, 32 or 64 channels at a time, weights
     // straight from memory): 32 x 64 and 64 x 64 output tiles
     KID_PW_P32, KID_PW_P64,
@@ -68,7 +69,7 @@ constexpr bool is_pool(int kid) { return plain_variant(kid) == KID_POOL || plain
 constexpr bool is_pw16(int kid) { return plain_variant(kid) >= KID_PW_V1 && plain_variant(kid) <= KID_PW_S4; }
 constexpr bool is_c3m(int kid) { return plain_variant(kid) >= KID_C3_M1 && plain_variant(kid) <= KID_C3_M4; }
 constexpr bool has_add_epilogue(int kid) { return plain_variant(kid) != kid; }
-constexpr bool is_c3_patch(int kid) { return kid >= KID_C3_P64 && kid <= KID_C3_Q128; }
+constexpr bool is_c3_patch(int kid) { return kid >= KID_C3_P64 && kid <= KID_C3_SK; }
 constexpr bool is_pw_patch(int kid) { return kid == KID_PW_P32 || kid == KID_PW_P64; }
 // windowed kernels for large tensors (batches): not in the lean build, but in the full and the train build
 constexpr bool is_large_tensor_kernel(int kid) { return kid == KID_POOL_ROW_S1 || kid == KID_POOL_ROW_S2 || kid == KID_DW_LDS; }

@@ -102,7 +102,8 @@ constexpr int kSmemFloats = 5120;
 // ... and what the patch-stationary kernels get instead: 24 floats (16 channels in three bf16 parts) for 256 pixels, or for up
 // to 640. Stand-alone kernels: only they; the resident kernel: every workgroup of the build that contains them.
 constexpr int kSmemFloatsPatch = 24 * 256, kSmemFloatsWide = 24 * 640;
-constexpr bool has_wide_patch(int kid) { return kid == KID_C3_Q32 || kid == KID_C3_Q64 || kid == KID_C3_Q128; }
+constexpr int kSplitKPatch = 160;                       // pixels of each of the four patches of conv3x3_mfma_split_k
+constexpr bool has_wide_patch(int kid) { return kid == KID_C3_Q32 || kid == KID_C3_Q64 || kid == KID_C3_Q128 || kid == KID_C3_SK; }
 constexpr int smem_floats(int kid) {
     return has_wide_patch(kid) ? kSmemFloatsWide : kid == KID_PW_P32 ? 2 * kSmemFloatsPatch : is_c3_patch(kid) || is_pw_patch(kid) ? kSmemFloatsPatch : kSmemFloats;
 }
@@ -732,6 +733,21 @@ __device__ __forceinline__ bool all_finite(const f32x16& v) {
     return z == 0.f;
 }
 
+// one output of a conv3x3 from memory in fp32
+template <bool FIN>
+__device__ __forceinline__ float conv3x3_fp32(const C3Args& a, int img, int m, int oy, int ox) {
+    float sum = 0.f;
+    for (int k = 0; k < 9 * a.Cin; ++k) {
+        const int ci = k / 9, tap = k - 9 * ci;
+        const int iy = oy * a.stride - a.pad + tap / 3, ix = ox * a.stride - a.pad + tap % 3;
+        const bool inside = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+        const size_t at = ((size_t)img * a.Cin + ci) * a.H * a.W + (inside ? iy * a.W + ix : 0);
+        const float x = ldg(a.x, a.x + at, FIN);
+        sum = fmaf(a.w[(size_t)m * a.Cin * 9 + k], inside ? x : 0.f, sum);
+    }
+    return sum;
+}
+
 // ------------------------------------------------------------------------------------
 // conv3x3 for many output pixels (large maps, batches), patch-stationary: Y[Cout x pixels] = W[Cout x 9 Cin] * patches.
 // A tile is TM output channels by a run of TN consecutive output pixels of one image (row-major, so a run may wrap over
@@ -902,16 +918,7 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
             const int oy = (p0 + cl) / a.Wo, ox = (p0 + cl) - oy * a.Wo;
             for (int m = mw + 16 * g; m < mw + rows; m += (m & 15) == 15 ? 17 : 1) {    // lane group g: rows 16 g .. 16 g + 15 of every 32
                 if (m >= a.Cout) break;
-                float sum = 0.f;
-                for (int k = 0; k < 9 * a.Cin; ++k) {
-                    const int ci = k / 9, tap = k - 9 * ci;
-                    const int iy = oy * a.stride - a.pad + tap / 3, ix = ox * a.stride - a.pad + tap % 3;
-                    const bool inside = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-                    const size_t at = ((size_t)img * a.Cin + ci) * HW + (inside ? iy * a.W + ix : 0);
-                    const float x = ldg(a.x, a.x + at, FIN);
-                    sum = fmaf(a.w[(size_t)m * a.Cin * 9 + k], inside ? x : 0.f, sum);
-                }
-                store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, sum, fout);
+                store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, conv3x3_fp32<FIN>(a, img, m, oy, ox), fout);
             }
         }
         return;
@@ -929,6 +936,149 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
                 if (m < a.Cout) store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, high[i][jn][q], fout);
             }
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// The same for few output pixels (a batch of small maps, one image): a tile is 32 output channels by a run of 32 pixels, and K is
+// split over the four wavefronts - wavefront w takes blocks w, w + 4, .. of 16 channels. Each keeps the patch of its block in
+// its own quarter of the LDS (up to PM pixels), so there is no workgroup barrier until the four sums meet there at the end,
+// and fetches its next block while it multiplies. The 16 x 16 tiles that gather their operands from memory spend a round
+// trip per chunk of K and fetch every input nine times: alone, us, gathered and this: 14 x 14 192 -> 192, six images
+// 31 -> 10, 6 x 6 384 -> 768, six images 46 -> 21, 17 x 17 192 -> 192, one image 11.5 -> 9.2.
+// Needs Cin % 16 == 0 and patches of at most PM pixels.
+// ------------------------------------------------------------------------------------
+template <int PM, bool FIN, class Wait>
+__device__ __forceinline__ void conv3x3_split_k_tile(const C3Args& a, int tile, float* smem, int tid, bool live, Wait& wait) {
+    const bool fout = wait.far_out();
+    constexpr int ITEMS = (2 * PM + 63) / 64, PLANE = 2 * PM, ST = 3;    // PLANE: one part of a patch, in units of 16 bytes
+    constexpr unsigned kOutside = 0x80000000u;          // beyond any tensor (num_records < 2^31): the load returns 0
+    constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
+    static_assert(4 * PM * 24 <= kSmemFloatsWide && PM * 24 >= 16 * 64, "LDS budget: four patches; a quarter holds a wavefront's sums");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, g = lane >> 5;
+    const int by = tile % a.co_groups, bt = tile / a.co_groups;
+    const int img = bt / a.tiles_xy, seg = bt - img * a.tiles_xy;
+    const int HWo = a.Ho * a.Wo, HW = a.H * a.W;
+    const int p0 = seg * 32, npx = min(32, HWo - p0);
+    const int oy_a = p0 / a.Wo, oy_b = (p0 + npx - 1) / a.Wo;
+    const int iy_a = oy_a * a.stride - a.pad, Wp = a.W + 2 * a.pad, P = ((oy_b - oy_a) * a.stride + 3) * Wp;
+    const int blocks = a.groups / 16, Mf = a.co_groups;
+    const __amdgpu_buffer_rsrc_t xr =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.x), 0, (a.tiles_n / a.tiles_xy) * a.Cin * HW * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wp), 0, 9 * blocks * Mf * kSplitFragBytes, 0x00020000);
+    u32x4* const patch = reinterpret_cast<u32x4*>(smem) + wave * 3 * PLANE;
+
+    // this lane's fill items: (pixel of the patch, channels 8 j .. 8 j + 7 of the block)
+    unsigned goff[ITEMS];
+    int loff[ITEMS];
+#pragma unroll
+    for (int t = 0; t < ITEMS; ++t) {
+        const int idx = lane + 64 * t;
+        const int j = idx >= P ? 1 : 0, pixel = idx - (idx >= P ? P : 0);
+        const int pr = pixel / Wp, pc = pixel - pr * Wp;
+        const int iy = iy_a + pr, ix = pc - a.pad;
+        const bool item = live && idx < 2 * P;
+        const bool inside = item && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+        goff[t] = inside ? (unsigned)(((img * a.Cin + 8 * j) * HW + iy * a.W + ix) * 4) : kOutside;
+        loff[t] = item ? 2 * pixel + (j ^ ((pixel >> 2) & 1)) : -1;     // in units of 16 bytes
+    }
+    const int px = p0 + min(r, npx - 1), oy = px / a.Wo, ox = px - oy * a.Wo;
+    const int base = (oy - oy_a) * a.stride * Wp + ox * a.stride;      // the patch pixel under tap 0 of this lane's pixel
+
+    f32x16 high, low;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) high[q] = 0.f, low[q] = 0.f;
+    float pv[ITEMS][8];
+    auto fill_load = [&](int block) {                   // items that few patches need are skipped by all lanes together
+#pragma unroll
+        for (int t = 0; t < ITEMS; ++t) {
+            if (64 * t >= 2 * P) break;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                pv[t][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, goff[t], (unsigned)((block * 16 + q) * HW * 4), kIn));
+        }
+    };
+    auto fill_store = [&]() {
+#pragma unroll
+        for (int t = 0; t < ITEMS; ++t) {
+            if (64 * t >= 2 * P) break;
+            u32x4 part[3];
+            split8(pv[t], part);
+            if (loff[t] >= 0) patch[loff[t]] = part[0], patch[PLANE + loff[t]] = part[1], patch[2 * PLANE + loff[t]] = part[2];
+        }
+    };
+    u32x4 af[ST][3];
+    auto a_load = [&](int block, int tap, int stage) {
+        const unsigned so = (unsigned)(((block * 9 + tap) * Mf + by) * kSplitFragBytes);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) af[stage][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, so + (unsigned)(p * 1024), 0);
+    };
+    auto b_load = [&](u32x4 (&bf)[3], int tap) {
+        const int pixel = base + (tap / 3) * Wp + tap % 3;
+        const u32x4* s = patch + 2 * pixel + (g ^ ((pixel >> 2) & 1));
+        bf[0] = s[0], bf[1] = s[PLANE], bf[2] = s[2 * PLANE];
+    };
+    // Lanes of one wavefront exchange the patch through LDS: its LDS operations are carried out in order, the fence keeps the
+    // compiler from reordering them.
+    auto wave_fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    if (live && wave < blocks) {
+#pragma unroll
+        for (int d = 0; d < ST; ++d) a_load(wave, d, d);
+    }
+    wait();
+    if (live && wave < blocks) {
+        fill_load(wave);
+#pragma unroll 1
+        for (int block = wave; block < blocks; block += 4) {
+            wave_fence();                               // the previous block's patch has been read
+            fill_store();
+            wave_fence();
+            if (block + 4 < blocks) fill_load(block + 4);
+            __builtin_amdgcn_sched_barrier(0);          // keep the loads here: the compiler would sink them to their use
+            u32x4 bf[2][3];
+            b_load(bf[0], 0);
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) {
+                if (tap < 8) b_load(bf[(tap + 1) & 1], tap + 1);   // next tap's B fragments, before this tap's matrix instructions
+                mfma_split(af[tap % ST], bf[tap & 1], high, low);
+                a_load(tap + ST < 9 ? block : block + 4, (tap + ST) % 9, tap % ST);     // beyond the last block: zeros
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    // the four sums meet: each wavefront leaves its own where its patch was and adds up four rows of every eight
+    high += low;
+    wave_fence();
+    float* const sums = smem + wave * 3 * PLANE * 4;
+    if (live) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sums[q * 64 + lane] = high[q];
+    }
+    __syncthreads();
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (live) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) v[q] += smem[w * 3 * PLANE * 4 + (4 * wave + q) * 64 + lane];
+    }
+    __syncthreads();                                    // the next tile's patches go here
+    if (!live || r >= npx) return;
+    const int mw = by * 32 + 8 * wave + 4 * g;
+    const float z = fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, v[3] * 0.f)));
+    const bool fp32 = __any(z != 0.f);                  // not the split's arithmetic: plain fp32, from memory
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int m = mw + q;
+        if (m >= a.Cout) continue;
+        float sum = v[q];
+        if (fp32) sum = conv3x3_fp32<FIN>(a, img, m, oy, ox);
+        store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + r, m, sum, fout);
     }
 }
 
@@ -1739,6 +1889,7 @@ NG_KERNEL(KID_C3_P96, C3Args, "conv3x3_patch_96x64", conv3x3_patch_tile < 96, 1,
 NG_KERNEL(KID_C3_Q32, C3Args, "conv3x3_patch_32x128_wide", conv3x3_patch_tile < 32, 1, 640)
 NG_KERNEL(KID_C3_Q64, C3Args, "conv3x3_patch_64x64_wide", conv3x3_patch_tile < 64, 1, 640)
 NG_KERNEL(KID_C3_Q128, C3Args, "conv3x3_patch_64x128_wide", conv3x3_patch_tile < 64, 2, 640)
+NG_KERNEL(KID_C3_SK, C3Args, "conv3x3_mfma_split_k", conv3x3_split_k_tile < kSplitKPatch)
 NG_KERNEL(KID_GEMM_PW_FWD, GemmArgs, "gemm_conv1x1_fwd", gemm_tile < GEMM_PW_FWD)
 NG_KERNEL(KID_GEMM_PW_DGRAD, GemmArgs, "gemm_conv1x1_dgrad", gemm_tile < GEMM_PW_DGRAD)
 NG_KERNEL(KID_GEMM_PW_WGRAD, GemmArgs, "gemm_conv1x1_wgrad", gemm_tile < GEMM_PW_WGRAD)
@@ -1843,7 +1994,7 @@ NG_KERNEL0(KID_SGD_BATCH, SgdBatchArgs, "sgd_update_batch", sgd_batch_tile)
     X(KID_PW_V1A) X(KID_PW_V2A) X(KID_PW_V3A) X(KID_PW_V4A) X(KID_PW_S1A) X(KID_PW_S2A)                                 \
     X(KID_PW_S3A) X(KID_PW_S4A) X(KID_C3_M1A) X(KID_C3_M2A) X(KID_C3_M3A) X(KID_C3_M4A)                                 \
     X(KID_POOL_A) X(KID_POOL_P4A) X(KID_C3_L32) X(KID_C3_L64)                                                          \
-    X(KID_C3_P64) X(KID_C3_P96) X(KID_C3_Q32) X(KID_C3_Q64) X(KID_C3_Q128) X(KID_PW_P32) X(KID_PW_P64)                    \
+    X(KID_C3_P64) X(KID_C3_P96) X(KID_C3_Q32) X(KID_C3_Q64) X(KID_C3_Q128) X(KID_C3_SK) X(KID_PW_P32) X(KID_PW_P64)                    \
     X(KID_POOL_ROW_S1) X(KID_POOL_ROW_S2) X(KID_DW_LDS)                                                                               \
     X(KID_GEMM_PW_FWD) X(KID_GEMM_PW_DGRAD) X(KID_GEMM_PW_WGRAD) X(KID_GEMM_C3_FWD) X(KID_GEMM_C3_DGRAD)                \
     X(KID_GEMM_C3_WGRAD) X(KID_SMALL_GEMM) X(KID_PW_PX_FWD) X(KID_PW_PX_DGRAD) X(KID_PW_WGRAD_PX) X(KID_PW_WGRAD_PX2) X(KID_C3_WGRAD_PX) X(KID_C3_WGRAD_PX2) X(KID_BN_RAW) X(KID_BN_DGRAD) X(KID_BN_WGRAD) X(KID_RELU_DGRAD) X(KID_DW_DGRAD) X(KID_DW_DGRAD_LDS)                \
@@ -2419,23 +2570,27 @@ constexpr long kC3LdsMinCols = 2048;      // measured: below this the 16 x 16 ti
 // The patch-stationary kernels: rows and pixels of a tile, pixels the patch may have.
 struct PatchKernel { int kid, tm, tn, pm; };
 constexpr PatchKernel kPatchKernels[] = {{KID_C3_P64, 64, 64, 256}, {KID_C3_P96, 96, 64, 256}, {KID_C3_Q32, 32, 128, 640},
-                                         {KID_C3_Q64, 64, 64, 640}, {KID_C3_Q128, 64, 128, 640}};
+                                         {KID_C3_Q64, 64, 64, 640}, {KID_C3_Q128, 64, 128, 640},
+                                         {KID_C3_SK, 32, 32, kSplitKPatch}};
 // Largest patch a run of tn consecutive output pixels can need: the rows it touches (a run can start at the end of a
 // row), stride apart, plus two, each W + 2 pad wide.
 long patch_pixels(long tn, long W, long Ho, long Wo, long stride, long pad) {
     const long rows = std::min(Ho, (tn - 2) / Wo + 2);
     return ((rows - 1) * stride + 3) * (W + 2 * pad);
 }
+// whole blocks of 16 channels; activations and packed weights (three 16-bit parts) within the reach of a buffer descriptor
+bool patch_reaches(const Shape& in, const Shape& out) {
+    return in.c % 16 == 0 && in.n * in.c * in.h * in.w * 4 < (1L << 31) && 9 * in.c * (out.c + 95) * 6 < (1L << 31);
+}
 // Which patch kernel a conv3x3 gets (KID_NONE: none fits). Decided from shapes: a workgroup's time goes with the rows of
 // its tile, a compute unit works its workgroups off side by side, so the estimate is (tiles per compute unit, rounded up)
 // x rows; one lone workgroup per compute unit cannot keep the matrix cores busy on its own (x 1.15).
 int choose_patch_kernel(const Shape& in, const Shape& out, long stride, long pad) {
-    // activations and packed weights (three 16-bit parts) within the reach of a buffer descriptor
-    if (in.c % 16 != 0 || in.n * in.c * in.h * in.w * 4 >= (1L << 31) || 9 * in.c * (out.c + 95) * 6 >= (1L << 31)) return KID_NONE;
+    if (!patch_reaches(in, out)) return KID_NONE;
     int best = KID_NONE;
     double best_cost = 0;
     for (const PatchKernel& k : kPatchKernels) {
-        if (patch_pixels(k.tn, in.w, out.h, out.w, stride, pad) > k.pm) continue;
+        if (k.kid == KID_C3_SK || patch_pixels(k.tn, in.w, out.h, out.w, stride, pad) > k.pm) continue;
         if ((k.tm == 32) != (out.c <= 32)) continue;                      // the 32-row kernel is for 32 output channels and fewer
         const long tiles = out.n * ceil_div(out.h * out.w, k.tn) * ceil_div(out.c, k.tm);
         const long rounds = ceil_div(tiles, 256);
@@ -2452,9 +2607,20 @@ PwChoice choose_c3(const ng_graph* g, int v) {
     const Shape& in = g->nodes[nd.preds[0]].out;
     const long cin = in.c;
     if (cin < 8) return c;
-    // many output pixels: the patch-stationary kernels
-    if (nd.out.n * nd.out.h * nd.out.w >= kC3LdsMinCols && !knob("NG_NO_PATCH_KERNELS")) {
-        const int kid = choose_patch_kernel(in, nd.out, nd.p.stride, nd.p.pad);
+    // The patch-stationary kernels. Few tiles of 64 x 64 (up to two for three compute units) leave the chip idle: 32 x 32 tiles
+    // with K over the wavefronts, where the patches are small enough and every wavefront gets a block of 16 channels (with 32
+    // channels 5.3 us against 4.1 of the gathering kernel). Us alone, gathering kernel / 64 x 64 tiles / these, tiles of 64 x 64:
+    // 17 x 17 192 -> 192 one image 11.5 / 20.9 / 9.2 (15), 14 x 14 192 -> 192 six images 31 / 20 / 10 (72), 35 x 35 96 -> 96
+    // four images 34 / 13.4 / 11.3 (160); 30 x 30 64 -> 96 six images 22.6 / 11.0 / 11.8 (180), 8 x 8 384 -> 768 twenty images
+    // 196 / 41.5 / 43 (240). Where they don't apply (a stride of 2), from 96 tiles of 64 x 64 on the large tiles: 30 x 30 ->
+    // 14 x 14 288 -> 384 six images 80 / 47 (144), one image of 35 x 35 -> 17 x 17 27 / 46 (30).
+    if (!knob("NG_NO_PATCH_KERNELS")) {
+        const long tiles64 = nd.out.n * ceil_div(nd.out.h * nd.out.w, 64) * ceil_div(nd.out.c, 64);
+        int kid = choose_patch_kernel(in, nd.out, nd.p.stride, nd.p.pad);
+        if (patch_reaches(in, nd.out) && cin >= 64 && tiles64 <= 170 && patch_pixels(32, in.w, nd.out.h, nd.out.w, nd.p.stride, nd.p.pad) <= kSplitKPatch)
+            kid = KID_C3_SK;
+        else if (nd.out.n * nd.out.h * nd.out.w < kC3LdsMinCols && (cin < 64 || tiles64 < 96))
+            kid = KID_NONE;
         for (const PatchKernel& k : kPatchKernels)
             if (k.kid == kid) {
                 c.kind = PwChoice::C3_PATCH, c.kid = kid;
@@ -2865,6 +3031,7 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
                     case KID_C3_P96: set_kernel<KID_C3_P96>(t, a, n); break;
                     case KID_C3_Q32: set_kernel<KID_C3_Q32>(t, a, n); break;
                     case KID_C3_Q64: set_kernel<KID_C3_Q64>(t, a, n); break;
+                    case KID_C3_SK: set_kernel<KID_C3_SK>(t, a, n); break;
                     default: set_kernel<KID_C3_Q128>(t, a, n); break;
                 }
                 break;

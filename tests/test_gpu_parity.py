@@ -174,6 +174,9 @@ def test_conv3x3_patch_kernels(shape, cout, kernel):
 @pytest.mark.parametrize("op,shape,cout,kernel", [
     ("conv3x3", (3, 48, 35, 37), 70, "conv3x3_patch_64x64"), ("conv3x3", (32, 32, 35, 35), 90, "conv3x3_patch_96x64"),
     ("conv3x3", (2, 32, 70, 71), 24, "conv3x3_patch_32x128_wide"), ("conv3x3", (4, 16, 150, 151), 64, "conv3x3_patch_64x128_wide"),
+    # K over the wavefronts: 4 blocks (one each), 5 (one wavefront has two), 12; an image smaller than a run, rows of patch 160 pixels
+    ("conv3x3", (1, 64, 35, 35), 70, "conv3x3_mfma_split_k"), ("conv3x3", (3, 80, 5, 5), 33, "conv3x3_mfma_split_k"),
+    ("conv3x3", (2, 192, 17, 38), 64, "conv3x3_mfma_split_k"),
     ("conv1x1", (3, 80, 31, 33), 130, "conv1x1_patch_32x64"), ("conv1x1", (5, 112, 41, 43), 130, "conv1x1_patch_64x64")])
 def test_split_products_against_64_bits(op, shape, cout, kernel):
     def build(b):
@@ -195,7 +198,7 @@ def test_split_products_against_64_bits(op, shape, cout, kernel):
         r.close()
 
 
-@pytest.mark.parametrize("op,shape,cout", [("conv3x3", (3, 48, 35, 37), 70), ("conv3x3", (32, 32, 35, 35), 90),
+@pytest.mark.parametrize("op,shape,cout", [("conv3x3", (3, 48, 35, 37), 70), ("conv3x3", (32, 32, 35, 35), 90), ("conv3x3", (3, 64, 33, 31), 70),
                                            ("conv1x1", (3, 80, 31, 33), 130), ("conv1x1", (5, 112, 41, 43), 130)])
 def test_split_products_of_infinities_and_huge_values(op, shape, cout):
     """Infinities have no split, and values next to the largest fp32 number round to an infinite bf16: results that see one

@@ -759,6 +759,12 @@ def test_kernel_choice_of_the_patch_stationary_convolutions():
     # 24 input channels are not whole blocks of 16; a run of 64 pixels of a 299-wide image can need 4 x 301 pixels of patch
     assert _kernels_on((2, 24, 97, 96), [c3(40)]) == ["conv3x3_lds_64x64"]
     assert _kernels_on((1, 16, 299, 299), [c3(64)]) == ["conv3x3_lds_64x64"]
+    # few tiles: K over the wavefronts; not with 32 channels, not where 32 pixels need a patch of more than 160 pixels (38 wide: 160,
+    # 39 wide: 164; stride 2); six images of 14 x 14 at a stride of 2 are 144 tiles of 64 x 64, one is 24
+    assert _kernels_on((1, 64, 38, 38), [c3(64)]) == _kernels_on((40, 64, 8, 8), [c3(64)]) == ["conv3x3_mfma_split_k"]
+    assert "conv3x3_mfma_split_k" not in _kernels_on((1, 64, 39, 39), [c3(64)]) + _kernels_on((1, 32, 32, 32), [c3(32)])
+    assert _kernels_on((6, 288, 30, 30), [c3(384, 2, 0)]) == ["conv3x3_patch_64x64_wide"]
+    assert _kernels_on((1, 288, 30, 30), [c3(384, 2, 0)])[0].startswith("conv3x3_mfma_")
     # 1225 output pixels: a small problem
     assert _kernels_on((1, 96, 35, 35), [c3(96)])[0].startswith("conv3x3_mfma_")
 
