@@ -2888,7 +2888,14 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
             for (int j = a.k; j < NG_MAX_PREDS; ++j) a.x[j] = a.x[0], a.first[j] = first;
             a.y = buf(v);
             a.C = (int)o.c, a.HW = hw_out, a.total = total;
-            if (hw_out % 4 == 0) set_kernel<KID_CONCAT_V4>(t, a, ceil_div(total / 4, kBlock));
+            // 128 bits at a time wherever four elements never straddle two blocks or two images, on either side: every block
+            // starts at and has a multiple of four elements (odd maps with channels in fours as well; an Inception-style
+            // network at batch 32, whose concats are of 35 x 35 and 17 x 17 maps, 3666 -> 3571 us)
+            bool quads = true;
+            for (int j = 0; j < a.k; ++j)
+                quads = quads && (long)a.first[j] * hw_out % 4 == 0 && (long)a.lo[j] * hw_out % 4 == 0 && (long)a.cin[j] * hw_out % 4 == 0;
+            quads = quads && (long)a.C * hw_out % 4 == 0;
+            if (quads) set_kernel<KID_CONCAT_V4>(t, a, ceil_div(total / 4, kBlock));
             else set_kernel<KID_CONCAT>(t, a, ceil_div(total, kBlock));
             break;
         }

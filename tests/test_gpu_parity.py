@@ -168,6 +168,23 @@ def test_conv3x3_patch_kernels(shape, cout, kernel):
     check_all_nodes(w, (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_DEVICE_RESIDENT))
 
 
+# concat 128 bits at a time on odd maps: blocks that start and end on multiples of four elements, and two that don't
+@pytest.mark.parametrize("shape,slices,kernel", [((3, 12, 5, 7), [(0, 12), (4, 8)], "concat_v4"), ((2, 8, 17, 17), [(4, 8), (0, 8)], "concat_v4"),
+                                                 ((3, 12, 5, 7), [(0, 12), (3, 7)], "concat"), ((2, 6, 5, 5), [(0, 6), (0, 6)], "concat")])
+def test_concat_of_odd_maps(shape, slices, kernel):
+    def build(b):
+        x = b.input(*shape)
+        b.concat([b.relu(x), b.bn_act(x, relu=False)], slices)
+    w = single_op(build)
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        assert B.ng_task_kernel(r.g, 3) == kernel
+    finally:
+        r.close()
+    check_all_nodes(w, (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_DEVICE_RESIDENT))
+
+
 # The patch-stationary convolutions multiply in three bf16 parts per value. Against 64 bits, ragged in every direction: their
 # large accumulator is rounded once per 16 products, and partial sums grow to the result, so the 2-norm of the error is at most
 # about 2^-24 sqrt(K / 16) of the result's; one more 2^-24 for the stored value.
