@@ -165,7 +165,10 @@ def test_training_step_all_operators_small():
 
 
 @pytest.mark.parametrize("shape,kernel", [((2, 5, 40, 36), "pool3x3_dgrad"), ((3, 7, 9, 10), "pool3x3_dgrad_lds"),
-                                          ((2, 3, 32, 32), "pool3x3_dgrad_lds"), ((5, 3, 16, 16), "pool3x3_dgrad_lds")])
+                                          ((2, 3, 32, 32), "pool3x3_dgrad_lds"), ((5, 3, 16, 16), "pool3x3_dgrad_lds"),
+                                          # the last four pixels of a row short by one, two, three; rows shorter than four
+                                          ((2, 3, 27, 31), "pool3x3_dgrad_lds"), ((2, 3, 30, 25), "pool3x3_dgrad_lds"),
+                                          ((2, 3, 3, 3), "pool3x3_dgrad_lds")])
 def test_training_pool_backward_plane_sizes(shape, kernel):
     """Pool backward through both of its kernels: planes a workgroup stages whole in LDS (up to 1024 pixels; several
     small planes per workgroup with a ragged last group) and larger ones; maximum and average, strides 1 and 2,
