@@ -45,6 +45,7 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 PEAK_MFMA_F32_TFLOPS = 157.3   # MI355X fp32 matrix
+PEAK_SPLIT_BF16_TFLOPS = 2500.0 / 6   # fp32 products as six bf16 ones (the patch-stationary and split-K convolutions)
 RIDGE_FLOP_PER_BYTE = PEAK_MFMA_F32_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
 
 # HBM bytes of one launch of the dominant kernel, from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB
@@ -308,8 +309,10 @@ def measure(name, batch, steps, warmup, args, headline):
         intensity = d["flops"] / max(d["bytes"], 1.0)
         if intensity >= RIDGE_FLOP_PER_BYTE:
             achieved = d["flops"] / d["us"] * 1e-6
-            roofline = {"kernel": dom, "bound": "mfma_f32", "achieved": achieved, "peak": PEAK_MFMA_F32_TFLOPS, "unit": "TFLOP/s",
-                        "frac": achieved / PEAK_MFMA_F32_TFLOPS}
+            split = "_patch_" in dom or dom.endswith("_split_k")
+            peak = PEAK_SPLIT_BF16_TFLOPS if split else PEAK_MFMA_F32_TFLOPS
+            roofline = {"kernel": dom, "bound": "mfma_bf16_split" if split else "mfma_f32", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+                        "frac": achieved / peak}
         else:
             achieved = d["bytes"] / d["us"] * 1e-3
             roofline = {"kernel": dom, "bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
