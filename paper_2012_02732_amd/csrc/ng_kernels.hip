@@ -769,7 +769,7 @@ __device__ __forceinline__ float conv3x3_fp32(const C3Args& a, int img, int m, i
 // which gets the same wavefront of every workgroup, share the work).
 // What bounds it: the vector L1 (weights: 3 KiB per fragment and wavefront), at 35 - 40 % of the matrix rate; with
 // v_mfma_f32_16x16x4_f32 the matrix rate did (0.65 - 0.75 of it). Layers at batch 32, us before and after: 17 x 17 192 -> 192
-// 58 -> 39, 8 x 8 448 -> 384 69 -> 47, 147 x 147 32 -> 64 282 -> 224, 73 x 73 80 -> 192 391 -> 295.
+// 58 -> 39, 8 x 8 448 -> 384 69 -> 44, 147 x 147 32 -> 64 282 -> 222, 73 x 73 80 -> 192 391 -> 288.
 // Needs Cin % 16 == 0 and a patch of at most PM pixels.
 // ------------------------------------------------------------------------------------
 template <int ROWS, int FN, int PM, bool FIN, class Wait>
