@@ -124,6 +124,19 @@ constexpr int kGroup = kBlock * kSubs;  // threads per workgroup of the resident
 constexpr int kArgBytes = 256;       // size of the per-task argument block of the resident kernel's task table
 constexpr int kLaunchArgBytes = 384; // size of a launched kernel's argument block (a launch of two tasks carries both blocks)
 
+// Where the kernels that multiply in three bf16 parts load a fragment of packed weights from (32 rows x 16 k: three parts x 64
+// lanes x 8 bf16; `slices` slices of 16 k, `fragments` of 32 rows each): the byte offset every lane adds to its own (`lane`),
+// and the one all lanes share (`scalar`). Their prefetch runs ahead of K's end. A buffer load checks the lanes' offset against
+// the size of the buffer, but not the shared one, so a slice that does not exist has to be outside by the lanes' offset
+// (kOutside: beyond any tensor, all are smaller than 2^31 bytes): nothing is read, the values are zeros.
+constexpr int kSplitFragBytes = 3 * 64 * 16;
+constexpr unsigned kOutside = 0x80000000u;
+struct FragmentOffset { unsigned lane, scalar; };
+constexpr FragmentOffset split_fragment(int slice, int slices, int fragment, int fragments) {
+    return slice < slices ? FragmentOffset{0u, ((unsigned)slice * (unsigned)fragments + (unsigned)fragment) * (unsigned)kSplitFragBytes}
+                          : FragmentOffset{kOutside, 0u};
+}
+
 // ---- argument blocks (plain data, <= kArgBytes) ---------------------------------------
 struct BnArgs {
     const float* x;

@@ -699,7 +699,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-constexpr int kSplitFragBytes = 3 * 64 * 16;            // 32 rows x 16 k of packed weights: three parts x 64 lanes x 8 bf16
 
 // two values at a time: the parts of x0 in the low halves of h, m, l, those of x1 in the high halves
 __device__ __forceinline__ void split_bf16x3(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
@@ -777,7 +776,6 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
     const bool fout = wait.far_out();
     constexpr int NW = ROWS == 32 ? 4 : 2, FM = ROWS == 96 ? 2 : 1, TM = ROWS, TN = 32 * FN * NW, ST = 3;
     constexpr int ITEMS = 2 * PM / kBlock, PLANE = 2 * PM;          // PLANE: one part of the patch, in units of 16 bytes
-    constexpr unsigned kOutside = 0x80000000u;          // beyond any tensor (num_records < 2^31): the load returns 0
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
     static_assert(PM * 24 <= (PM > 256 ? kSmemFloatsWide : kSmemFloatsPatch) && PM % 128 == 0 && (ROWS == 32 || ROWS == 64 || ROWS == 96), "LDS budget");
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -849,12 +847,12 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
     };
     u32x4 af[ST][FM][3];
     auto a_load = [&](int slice, int stage) {
-        const unsigned so = (unsigned)((slice * Mf + mw / 32) * kSplitFragBytes);
+        const FragmentOffset at = split_fragment(slice, 9 * blocks, mw / 32, Mf);
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             if (ROWS == 96 && i == 1 && wm == 1) break;
 #pragma unroll
-            for (int p = 0; p < 3; ++p) af[stage][i][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, so + (unsigned)((i * 3 + p) * 1024), 0);
+            for (int p = 0; p < 3; ++p) af[stage][i][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, at.lane + lane * 16, at.scalar + (unsigned)((i * 3 + p) * 1024), 0);
         }
     };
     auto b_load = [&](u32x4 (&bf)[FN][3], int tap) {
@@ -893,7 +891,7 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
 #pragma unroll
                     for (int jn = 0; jn < FN; ++jn) mfma_split(af[tap % ST][i], bf[tap & 1][jn], high[i][jn], low[i][jn]);
                 }
-                a_load(block * 9 + tap + ST, tap % ST);        // beyond the last slice: zeros
+                a_load(block * 9 + tap + ST, tap % ST);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -952,7 +950,6 @@ template <int PM, bool FIN, class Wait>
 __device__ __forceinline__ void conv3x3_split_k_tile(const C3Args& a, int tile, float* smem, int tid, bool live, Wait& wait) {
     const bool fout = wait.far_out();
     constexpr int ITEMS = (2 * PM + 63) / 64, PLANE = 2 * PM, ST = 3;    // PLANE: one part of a patch, in units of 16 bytes
-    constexpr unsigned kOutside = 0x80000000u;          // beyond any tensor (num_records < 2^31): the load returns 0
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
     static_assert(4 * PM * 24 <= kSmemFloatsWide && PM * 24 >= 16 * 64, "LDS budget: four patches; a quarter holds a wavefront's sums");
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1010,9 +1007,9 @@ __device__ __forceinline__ void conv3x3_split_k_tile(const C3Args& a, int tile, 
     };
     u32x4 af[ST][3];
     auto a_load = [&](int block, int tap, int stage) {
-        const unsigned so = (unsigned)(((block * 9 + tap) * Mf + by) * kSplitFragBytes);
+        const FragmentOffset at = split_fragment(block * 9 + tap, 9 * blocks, by, Mf);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) af[stage][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, so + (unsigned)(p * 1024), 0);
+        for (int p = 0; p < 3; ++p) af[stage][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, at.lane + lane * 16, at.scalar + (unsigned)(p * 1024), 0);
     };
     auto b_load = [&](u32x4 (&bf)[3], int tap) {
         const int pixel = base + (tap / 3) * Wp + tap % 3;
@@ -1046,7 +1043,7 @@ __device__ __forceinline__ void conv3x3_split_k_tile(const C3Args& a, int tile, 
             for (int tap = 0; tap < 9; ++tap) {
                 if (tap < 8) b_load(bf[(tap + 1) & 1], tap + 1);   // next tap's B fragments, before this tap's matrix instructions
                 mfma_split(af[tap % ST], bf[tap & 1], high, low);
-                a_load(tap + ST < 9 ? block : block + 4, (tap + ST) % 9, tap % ST);     // beyond the last block: zeros
+                a_load(tap + ST < 9 ? block : block + 4, (tap + ST) % 9, tap % ST);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1116,7 +1113,6 @@ __device__ __forceinline__ void conv1x1_patch_tile(const PwArgs& a, int tile, fl
     const bool fout = wait.far_out();
     constexpr int TM = ROWS, TN = 64, KW = ROWS == 32 ? 2 : 1, OWN = KB / KW;
     constexpr int PLANE = 2 * TN, BUFFER = KB * 3 * PLANE, ITEMS = KB / 2;                // LDS in units of 16 bytes
-    constexpr unsigned kOutside = 0x80000000u;          // beyond any tensor (num_records < 2^31): the load returns 0
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
     static_assert(2 * BUFFER * 4 <= (KB == 2 ? kSmemFloatsPatch : 2 * kSmemFloatsPatch) && KB % 2 == 0 && TN * 4 == kBlock && (ROWS == 32 || ROWS == 64), "LDS budget");
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1164,10 +1160,10 @@ __device__ __forceinline__ void conv1x1_patch_tile(const PwArgs& a, int tile, fl
         }
     };
     u32x4 af[OWN][3];
-    auto a_load = [&](int chunk, int own) {             // a block beyond Cin reads zeros
-        const unsigned so = (unsigned)(((chunk * KB + own * KW + kg) * Mf + mw / 32) * kSplitFragBytes);
+    auto a_load = [&](int chunk, int own) {             // a block beyond Cin: zeros
+        const FragmentOffset at = split_fragment(chunk * KB + own * KW + kg, blocks, mw / 32, Mf);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) af[own][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, so + (unsigned)(p * 1024), 0);
+        for (int p = 0; p < 3; ++p) af[own][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, at.lane + lane * 16, at.scalar + (unsigned)(p * 1024), 0);
     };
 
     wait();

@@ -833,3 +833,41 @@ def test_kernel_choice_of_conv1x1_on_odd_maps(shape, cout, prefix):
     """Maps without 128-bit loads take 16 x 16 tiles up to 512 of them (45 x 45 pixels: 508; 47 x 47: 556), which keeps
     a network of odd maps in the lean build of the resident kernel."""
     assert _kernels_on(shape, [lambda b, x: b.conv1x1(x, cout)])[0].startswith(prefix)
+
+
+def test_weight_prefetch_of_the_split_kernels_stays_inside_the_packed_copy(tmp_path):
+    """The prefetch runs ahead of K's end (three taps, four blocks of nine taps, a chunk of four blocks). Only a lane's own offset
+    is checked against a buffer's size, so every load is either whole inside the packed copy or, with a shared offset of 0,
+    outside by the lane's: for all slices any of the kernels asks for, up to the largest packed copies they accept."""
+    import subprocess
+    src = tmp_path / "fragments.cpp"
+    src.write_text(r"""
+#include <cstdio>
+#include "ng_device.h"
+int main() {
+    const int shapes[][2] = {{1, 1}, {5, 3}, {9 * 4, 24}, {9 * 12, 6}, {128, 10}, {9 * 2560, 30}};   // slices, fragments of 32 rows
+    for (const auto& s : shapes) {
+        const unsigned long long bytes = (unsigned long long)s[0] * s[1] * ng::kSplitFragBytes;
+        if (bytes >= (1ull << 31)) return 2;
+        for (int slice = 0; slice < s[0] + 36; ++slice)
+            for (int f = 0; f < s[1]; ++f) {
+                const ng::FragmentOffset at = ng::split_fragment(slice, s[0], f, s[1]);
+                for (unsigned part = 0; part < 3; ++part)
+                    for (unsigned lane = 0; lane < 64; ++lane) {
+                        const unsigned long long own = (unsigned long long)at.lane + lane * 16, shared = (unsigned long long)at.scalar + part * 1024;
+                        const bool inside = own + shared + 16 <= bytes, nothing = own >= (1ull << 31) && shared < 3072;
+                        const bool there = own + shared == ((unsigned long long)slice * s[1] + f) * ng::kSplitFragBytes + part * 1024 + lane * 16;
+                        if (slice < s[0] ? !(inside && there) : !nothing) return 1;
+                    }
+            }
+    }
+    std::puts("ok");
+}
+""")
+    exe = str(tmp_path / "fragments")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2012_02732_amd", "csrc"), str(src), "-o", exe], check=True)
+    assert subprocess.run([exe], check=True, capture_output=True, text=True).stdout.strip() == "ok"
+    # and the kernels take their offsets from nowhere else
+    kernels = open(os.path.join(ROOT, "paper_2012_02732_amd", "csrc", "ng_kernels.hip")).read()
+    loads = re.findall(r"raw_buffer_load_b128\(wr, (.*)", kernels)
+    assert sum(l.startswith("at.lane + lane * 16, at.scalar + ") for l in loads) == 3 and not [l for l in loads if l.startswith("lane * 16")]
