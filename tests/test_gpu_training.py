@@ -421,3 +421,55 @@ def test_training_replays_keep_training():
             cur.nodes[v].weights[j] = sgd_step([cur.nodes[v].weights[j]], [dw[v][j].reshape(cur.nodes[v].weights[j].shape)], lr)[0]
     for (v, j) in tw.update_of:
         assert rel_err(got[(v, j)], cur.nodes[v].weights[j]) <= TOL, (v, j)
+
+
+def _weight_gradient_of_infinities(fwd, conv, modes):
+    """Weight gradient of node `conv` (reads the network's input; what follows it makes dL/d(its result) independent of values) in
+    64 bits, tap by tap, against the replays: the same infinities and NaNs, everything else within the tolerance."""
+    out = fwd.outputs[0]
+    seeds = {out: np.random.default_rng(5).standard_normal(fwd.nodes[out].shape).astype(np.float32)}
+    tw = workloads.training_graph(fwd, 0.01, seeds)
+    nd = fwd.nodes[conv]
+    k, s = nd.params.get("k", 3), nd.params["stride"]
+    ho, wo = nd.shape[2:]
+    x = np.pad(fwd.input.astype(np.float64), ((0, 0), (0, 0), (k // 2, k // 2), (k // 2, k // 2)))
+    for mode in modes:
+        tensors, _ = run_training_step(tw, mode)
+        dy = tensors[tw.grad_of[conv]].astype(np.float64)
+        assert np.isfinite(dy).all()
+        ref = np.zeros(nd.weights[0].shape)
+        with np.errstate(invalid="ignore"):
+            for da in range(k):
+                for db in range(k):
+                    tap = x[:, :, da:da + s * (ho - 1) + 1:s, db:db + s * (wo - 1) + 1:s]
+                    for c in range(x.shape[1]):
+                        if nd.op == "dwconv":
+                            ref[c, da, db] = (dy[:, c] * tap[:, c]).sum()
+                        else:
+                            ref[:, c, da, db] = (dy * tap[:, c:c + 1]).sum((0, 2, 3))
+        node, off, numel = tw.wgrad_of[(conv, 0)]
+        got = tensors[node].reshape(-1)[off:off + numel].reshape(ref.shape)
+        finite = np.isfinite(ref)
+        assert 0 < finite.sum() < ref.size
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), (mode, "NaN", int(np.isnan(got).sum()), int(np.isnan(ref).sum()))
+        assert np.array_equal(got[~finite], ref[~finite], equal_nan=True), mode
+        assert rel_err(got[finite], ref[finite]) <= TOL, mode
+
+
+@pytest.mark.parametrize("shape,cout,kernel", [((60, 3, 5, 5), 44, "conv3x3_wgrad_px_16"), ((3, 3, 19, 21), 9, "conv3x3_wgrad_px_16"),
+                                               ((2, 20, 24, 25), 40, "conv3x3_wgrad_px_32"), ((4, 4, 18, 19), 33, "conv3x3_wgrad_px_16")])
+def test_training_conv3x3_weight_gradient_of_infinities_in_the_last_row(shape, cout, kernel):
+    """The upper row of taps never reads the last row of the input: an infinity or a NaN there must not reach it, in planes of
+    4 n + 1, 4 n + 2 and 4 n + 3 pixels neither (the last quad of such a plane has pixels behind the end)."""
+    from workloads.model import Builder
+    b = Builder("conv3x3_infinities")
+    f = b.fc(b.global_avgpool(b.conv3x3(b.input(*shape), cout, 1, 1)), 5)
+    rng = np.random.default_rng(16)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    fwd.input[0, 0, -1, :3] = np.inf
+    fwd.input[1, 1, -1, 1] = np.nan
+    fwd.input[1, 2, -1, -1] = -np.inf
+    seeds = {f: np.ones(fwd.nodes[f].shape, np.float32)}
+    assert _ragged_names(fwd, seeds, 0.01, "conv3x3_wgrad") == {kernel}
+    _weight_gradient_of_infinities(fwd, 1, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT))
