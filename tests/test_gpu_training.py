@@ -473,3 +473,19 @@ def test_training_conv3x3_weight_gradient_of_infinities_in_the_last_row(shape, c
     seeds = {f: np.ones(fwd.nodes[f].shape, np.float32)}
     assert _ragged_names(fwd, seeds, 0.01, "conv3x3_wgrad") == {kernel}
     _weight_gradient_of_infinities(fwd, 1, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT))
+
+
+@pytest.mark.parametrize("shape", [(9, 16, 27, 27), (31, 44, 7, 9), (3, 130, 30, 30), (40, 20, 10, 15)])
+@pytest.mark.parametrize("k,stride", [(3, 1), (3, 2), (5, 1), (5, 2)])
+def test_training_depthwise_weight_gradient_of_infinities(shape, k, stride):
+    """Rows that are no multiple of four outputs end with a quad that overlaps the one before it: what both see is counted once,
+    an infinite input value too (infinity, not NaN)."""
+    from workloads.model import Builder
+    b = Builder("depthwise_infinities")
+    f = b.fc(b.global_avgpool(b.dwconv(b.input(*shape), k, stride)), 4)
+    rng = np.random.default_rng(17)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    for c, col in enumerate((-1, -2, -4, -5, -6, -7)):
+        fwd.input[c % shape[0], c, shape[2] // 2, col] = np.inf if c % 2 else -np.inf
+    _weight_gradient_of_infinities(fwd, 1, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT))
