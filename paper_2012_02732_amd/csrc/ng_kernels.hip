@@ -685,15 +685,19 @@ __device__ __forceinline__ void conv3x3_lds_tile(const C3Args& a, int tile, floa
 }
 
 // ------------------------------------------------------------------------------------
-// fp32 products on the bf16 matrix cores. A value is split into three bf16 parts, x = h + m + l (each the rest rounded to
-// nearest even; 3 x 8 significant bits: the rest after l is below 2^-26 of x), and of the nine products of two split values
-// the six of 2^-18 and larger are formed: h h in an accumulator of its own, h m, m h, m m, h l and l h in a second one,
-// added once at the end. v_mfma_f32_32x32x16_bf16 does 16 times the work of v_mfma_f32_16x16x4_f32 per cycle, six of them
+// fp32 products on the bf16 matrix cores. A value is split into three bf16 parts, x = h + m + l: h the upper half of its bits, m
+// the rest rounded to nearest even, l what is left of it (24 = 8 + 8 + 8 bits: exact). Of the nine products of two split values
+// the six of 2^-16 and larger are formed: h h in an accumulator of its own, h m, m h, m m, h l and l h in a second one, added
+// once at the end. v_mfma_f32_32x32x16_bf16 does 16 times the work of v_mfma_f32_16x16x4_f32 per cycle, six of them
 // replace sixteen cycles by six. The large accumulator is rounded once per 16 k instead of once per 4 k, so that the results
 // are closer to 64 bits than those of the fp32 instructions: 2-norm of the error over that of the result, K = 288 - 4032:
-// 0.7 - 3.0e-7 against 2.2 - 7.6e-7. (All six in one accumulator: 2.3 - 8.3e-7, which is why there are two.)
-// Infinities have no such split (inf - inf), and values of 3.39e38 and more round to one: a wavefront that finds a result
-// that is not finite works its outputs out again with fp32 multiply-adds.
+// 0.7 - 2.7e-7 against 2.2 - 7.6e-7. (All six in one accumulator: 2.3 - 8.3e-7, which is why there are two.)
+// The method: G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", 2019.
+// Infinities and NaN. h is finite wherever x is (its bits are cut off, not rounded up), infinite where x is, NaN where x is (a
+// signalling NaN whose upper half is that of an infinity counts as one). So the sum of the h h has the infinities and NaNs that
+// the fp32 products have; the lower parts of an infinity are NaN, so where the sum of the h h is not finite it is the result
+// (split_sum). It is also where a sum outgrows fp32, which needs products whose magnitudes add up to more than the largest fp32 number.
 // ------------------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -702,8 +706,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // two values at a time: the parts of x0 in the low halves of h, m, l, those of x1 in the high halves
 __device__ __forceinline__ void split_bf16x3(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
-    h = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
-    const float r0 = x0 - __builtin_bit_cast(float, h << 16), r1 = x1 - __builtin_bit_cast(float, h & 0xffff0000u);
+    const unsigned b0 = __builtin_bit_cast(unsigned, x0), b1 = __builtin_bit_cast(unsigned, x1);
+    h = __builtin_amdgcn_perm(b1, b0, 0x07060302);              // the upper halves of both
+    const float r0 = x0 - __builtin_bit_cast(float, b0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, b1 & 0xffff0000u);
     m = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{r0, r1}), bf16x2));
     const float q0 = r0 - __builtin_bit_cast(float, m << 16), q1 = r1 - __builtin_bit_cast(float, m & 0xffff0000u);
     l = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{q0, q1}), bf16x2));
@@ -725,26 +730,11 @@ __device__ __forceinline__ void mfma_split(const u32x4 (&a)[3], const u32x4 (&b)
         d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[pa[p]]), __builtin_bit_cast(bf16x8, b[pb[p]]), d, 0, 0, 0);
     }
 }
-__device__ __forceinline__ bool all_finite(const f32x16& v) {
-    float z = 0.f;
+__device__ __forceinline__ f32x16 split_sum(const f32x16& high, const f32x16& low) {
+    f32x16 v;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) z = fmaf(v[q], 0.f, z);       // NaN if any is not finite
-    return z == 0.f;
-}
-
-// one output of a conv3x3 from memory in fp32
-template <bool FIN>
-__device__ __forceinline__ float conv3x3_fp32(const C3Args& a, int img, int m, int oy, int ox) {
-    float sum = 0.f;
-    for (int k = 0; k < 9 * a.Cin; ++k) {
-        const int ci = k / 9, tap = k - 9 * ci;
-        const int iy = oy * a.stride - a.pad + tap / 3, ix = ox * a.stride - a.pad + tap % 3;
-        const bool inside = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-        const size_t at = ((size_t)img * a.Cin + ci) * a.H * a.W + (inside ? iy * a.W + ix : 0);
-        const float x = ldg(a.x, a.x + at, FIN);
-        sum = fmaf(a.w[(size_t)m * a.Cin * 9 + k], inside ? x : 0.f, sum);
-    }
-    return sum;
+    for (int q = 0; q < 16; ++q) v[q] = __builtin_fabsf(high[q]) < __builtin_inff() ? high[q] + low[q] : high[q];
+    return v;
 }
 
 // ------------------------------------------------------------------------------------
@@ -900,27 +890,6 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
         __syncthreads();
     }
     if (!live) return;
-    bool finite = true;
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int jn = 0; jn < FN; ++jn) {
-            high[i][jn] += low[i][jn];
-            finite = finite && all_finite(high[i][jn]);
-        }
-    if (__any(!finite)) {                               // not the split's arithmetic: plain fp32, from memory
-        const int rows = ROWS == 96 && wm == 1 ? 32 : 32 * FM;
-        for (int jn = 0; jn < FN; ++jn) {
-            const int cl = (wn * FN + jn) * 32 + r;
-            if (cl >= npx) continue;
-            const int oy = (p0 + cl) / a.Wo, ox = (p0 + cl) - oy * a.Wo;
-            for (int m = mw + 16 * g; m < mw + rows; m += (m & 15) == 15 ? 17 : 1) {    // lane group g: rows 16 g .. 16 g + 15 of every 32
-                if (m >= a.Cout) break;
-                store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, conv3x3_fp32<FIN>(a, img, m, oy, ox), fout);
-            }
-        }
-        return;
-    }
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
         if (ROWS == 96 && i == 1 && wm == 1) break;
@@ -928,10 +897,11 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
         for (int jn = 0; jn < FN; ++jn) {
             const int cl = (wn * FN + jn) * 32 + r;
             if (cl >= npx) continue;
+            const f32x16 sum = split_sum(high[i][jn], low[i][jn]);
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
                 const int m = mw + i * 32 + 8 * (q / 4) + 4 * g + q % 4;
-                if (m < a.Cout) store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, high[i][jn][q], fout);
+                if (m < a.Cout) store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, sum[q], fout);
             }
         }
     }
@@ -1049,12 +1019,12 @@ __device__ __forceinline__ void conv3x3_split_k_tile(const C3Args& a, int tile, 
         }
     }
     // the four sums meet: each wavefront leaves its own where its patch was and adds up four rows of every eight
-    high += low;
+    const f32x16 own = split_sum(high, low);
     wave_fence();
     float* const sums = smem + wave * 3 * PLANE * 4;
     if (live) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) sums[q * 64 + lane] = high[q];
+        for (int q = 0; q < 16; ++q) sums[q * 64 + lane] = own[q];
     }
     __syncthreads();
     float v[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1067,15 +1037,10 @@ __device__ __forceinline__ void conv3x3_split_k_tile(const C3Args& a, int tile, 
     __syncthreads();                                    // the next tile's patches go here
     if (!live || r >= npx) return;
     const int mw = by * 32 + 8 * wave + 4 * g;
-    const float z = fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, v[3] * 0.f)));
-    const bool fp32 = __any(z != 0.f);                  // not the split's arithmetic: plain fp32, from memory
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int m = mw + q;
-        if (m >= a.Cout) continue;
-        float sum = v[q];
-        if (fp32) sum = conv3x3_fp32<FIN>(a, img, m, oy, ox);
-        store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + r, m, sum, fout);
+        if (m < a.Cout) store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + r, m, v[q], fout);
     }
 }
 
@@ -1192,36 +1157,27 @@ __device__ __forceinline__ void conv1x1_patch_tile(const PwArgs& a, int tile, fl
         }
         __syncthreads();                                // the chunk is used up, the next one is there
     }
-    high += low;
+    f32x16 sum = split_sum(high, low);
     if (KW > 1) {                                       // the second half of K joins the first
         if (kg == 1) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) smem[(wn * 16 + q) * 64 + lane] = high[q];
+            for (int q = 0; q < 16; ++q) smem[(wn * 16 + q) * 64 + lane] = sum[q];
         }
         __syncthreads();
         if (kg == 0) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) high[q] += smem[(wn * 16 + q) * 64 + lane];
+            for (int q = 0; q < 16; ++q) sum[q] += smem[(wn * 16 + q) * 64 + lane];
         }
         __syncthreads();                                // the next tile writes here
     }
     const int col = n0 + cl;
     if (!live || kg != 0 || col >= a.cols) return;
     const int img = col / a.HW, pix = col - img * a.HW;
-    if (__any(!all_finite(high))) {                     // not the split's arithmetic: plain fp32, from memory
-        for (int m = mw + 16 * g; m < mw + 16 * g + 16 && m < a.Cout; ++m) {
-            float sum = 0.f;
-            for (int k = 0; k < a.Cin; ++k)
-                sum = fmaf(a.w[(size_t)m * a.Cin + k], ldg(a.x, a.x + ((size_t)img * a.Cin + k) * a.HW + pix, FIN), sum);
-            store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * a.HW + pix, m, sum + (a.bias ? a.bias[m] : 0.f), fout);
-        }
-        return;
-    }
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int m = mw + 8 * (q / 4) + 4 * g + q % 4;
         if (m < a.Cout)
-            store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * a.HW + pix, m, high[q] + (a.bias ? a.bias[m] : 0.f), fout);
+            store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * a.HW + pix, m, sum[q] + (a.bias ? a.bias[m] : 0.f), fout);
     }
 }
 

@@ -254,6 +254,51 @@ def test_split_products_of_infinities_and_huge_values(op, shape, cout):
         r.close()
 
 
+# Whatever a network's values are, its replay takes the time it takes: networks that have diverged (every value NaN, infinities, sums
+# beyond the largest number) in every kernel of the family, with a second convolution behind the first.
+@pytest.mark.parametrize("op,shape,cout,kernel", [
+    ("conv3x3", (3, 48, 35, 37), 70, "conv3x3_patch_64x64"), ("conv3x3", (2, 64, 17, 17), 96, "conv3x3_mfma_split_k"),
+    ("conv1x1", (3, 80, 31, 33), 130, "conv1x1_patch_32x64"), ("conv1x1", (5, 112, 41, 43), 130, "conv1x1_patch_64x64")])
+def test_split_products_of_diverged_networks(op, shape, cout, kernel):
+    def build(b):
+        x = b.input(*shape)
+        y = b.conv3x3(x, cout, 1, 1) if op == "conv3x3" else b.conv1x1(x, cout)
+        y = b.conv1x1(b.bn_act(y, relu=False), shape[1])
+        b.conv3x3(y, cout, 1, 1) if op == "conv3x3" else b.conv1x1(y, cout)
+    w = single_op(build)
+    last = len(w.nodes) - 1
+    w64 = torch.from_numpy(w.nodes[1].weights[0]).double().view(cout, shape[1], *((3, 3) if op == "conv3x3" else (1, 1)))
+    conv = lambda x: torch.nn.functional.conv2d(torch.from_numpy(x).double(), w64, padding=1 if op == "conv3x3" else 0).numpy()
+    most, big = float(np.finfo(np.float32).max), w.input * np.float32(2.0 ** 120)
+    big[-1] = np.float32(2.0 ** 126) * np.sign(w64[0, :, w64.shape[2] // 2, w64.shape[3] // 2].numpy())[:, None, None]
+    ref = conv(big)
+    w64 = w64.abs()
+    inside, beyond = conv(np.abs(big)) < 0.999 * most, np.abs(ref) > 1.001 * most
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        assert B.ng_task_kernel(r.g, 1) == kernel
+        for mode in (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT, B.NG_MODE_AUTO):
+            B.ng_replay_mode(r.g, mode)
+            r.set_input(w.input)
+            usual = min(B.ng_time_replay(r.g, 20) for _ in range(3))
+            for fill in (np.nan, np.inf, -np.inf):
+                r.set_input(np.full(shape, fill, np.float32))
+                assert min(B.ng_time_replay(r.g, 20) for _ in range(3)) <= 2 * usual, (mode, fill)
+                got = r.output(1)
+                # sums of one sign and one magnitude cannot cancel; every output reads weights of both signs
+                assert np.isnan(got).all() and np.isnan(r.output(last)).all(), (mode, fill)
+            # results around the largest number: finite and as accurate as ever where the products' magnitudes add up to less than
+            # it, not finite where the result is more (the last image, whose values all push channel 0 up)
+            r.set_input(big)
+            assert min(B.ng_time_replay(r.g, 20) for _ in range(3)) <= 2 * usual, mode
+            got = r.output(1).astype(np.float64)
+            assert inside.any() and beyond.any() and np.isfinite(got[inside]).all() and not np.isfinite(got[beyond]).any()
+            assert np.linalg.norm((got[inside] - ref[inside]) / most) <= 1e-6 * np.linalg.norm(ref[inside] / most), mode
+    finally:
+        r.close()
+
+
 # pool3x3 on tensors of a million outputs and more: four outputs of a column per thread, both modes, strides and
 # paddings; heights that leave a partial block of 1, 2 and 3 output rows (and none)
 @pytest.mark.parametrize("shape", [(8, 64, 45, 47), (2, 48, 149, 147), (16, 32, 96, 101), (16, 32, 97, 96), (8, 64, 64, 88)])
