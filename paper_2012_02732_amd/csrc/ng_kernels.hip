@@ -692,6 +692,12 @@ __device__ __forceinline__ void conv3x3_lds_tile(const C3Args& a, int tile, floa
 // replace sixteen cycles by six. The large accumulator is rounded once per 16 k instead of once per 4 k, so that the results
 // are closer to 64 bits than those of the fp32 instructions: 2-norm of the error over that of the result, K = 288 - 4032:
 // 0.7 - 2.7e-7 against 2.2 - 7.6e-7. (All six in one accumulator: 2.3 - 8.3e-7, which is why there are two.)
+// Small values: bf16 has the exponents of fp32 and a quantum of 2^-133, and m and l lie 2^-8 and 2^-16 below x. All 24 bits are
+// there down to |x| = 2^-110, on either side of the product; below that x is taken to the next multiple of 2^-133 (2-norm of
+// the error for values around 2^-118: 9e-6, 2^-126: 2e-3; the fp32 instructions lose nothing there). Sums that also have
+// values of 2^-110 and more do not notice. Parts scaled by 64 and 4096 would keep all bits down to 2^-122, but take an
+// accumulator more and two multiplications per activation: conv3x3 1 - 3 % and conv1x1 up to 8 % slower, and the full build of
+// the resident kernel spills 622 registers instead of 184 (sixteen conv3x3_mfma_split_k of 28 x 28 128 and below 390 -> 552 us).
 // The method: G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
 // Higher-Precision Computations", 2019.
 // Infinities and NaN. h is finite wherever x is (its bits are cut off, not rounded up), infinite where x is, NaN where x is (a

@@ -299,6 +299,38 @@ def test_split_products_of_diverged_networks(op, shape, cout, kernel):
         r.close()
 
 
+# Small magnitudes on either side, the other side large so that the results are ordinary numbers. The three parts of a value end at
+# 2^-133, the smallest bf16 number: what they leave out is at most 2^-134, nothing from 2^-110 up, where fp32's precision ends
+# and the kernels' own begins to fall short of it.
+@pytest.mark.parametrize("op,shape,cout,kernel", [
+    ("conv3x3", (3, 48, 35, 37), 70, "conv3x3_patch_64x64"), ("conv3x3", (2, 64, 17, 17), 96, "conv3x3_mfma_split_k"),
+    ("conv1x1", (3, 80, 31, 33), 130, "conv1x1_patch_32x64"), ("conv1x1", (5, 112, 41, 43), 130, "conv1x1_patch_64x64")])
+@pytest.mark.parametrize("exponent", [-109, -118, -126])
+@pytest.mark.parametrize("small", ["activations", "weights"])
+def test_split_products_of_small_magnitudes(op, shape, cout, kernel, exponent, small):
+    def build(b):
+        x = b.input(*shape)
+        b.conv3x3(x, cout, 1, 1) if op == "conv3x3" else b.conv1x1(x, cout)
+    w = single_op(build)
+    k = shape[1] * (9 if op == "conv3x3" else 1)
+    weights = w.nodes[1].weights[0] * np.float32(5)                # std 1, as the input
+    tiny, large = np.float32(2.0 ** exponent), np.float32(2.0 ** 100)
+    w.input *= tiny if small == "activations" else large
+    w.nodes[1].weights = [weights * (large if small == "activations" else tiny)]
+    x, wt = torch.from_numpy(w.input).double(), torch.from_numpy(w.nodes[1].weights[0]).double()
+    ref = torch.nn.functional.conv2d(x, wt.view(cout, shape[1], *((3, 3) if op == "conv3x3" else (1, 1))), padding=1 if op == "conv3x3" else 0).numpy()
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        assert B.ng_task_kernel(r.g, 1) == kernel
+        for mode in (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT):
+            r.arena.zero_()
+            got = r.run(w.input, mode=mode)[1].astype(np.float64)
+            assert np.linalg.norm(got - ref) <= (2.0 ** -24 * (1 + np.sqrt(k / 16)) + 2.0 ** (-134 - exponent)) * np.linalg.norm(ref), mode
+    finally:
+        r.close()
+
+
 # pool3x3 on tensors of a million outputs and more: four outputs of a column per thread, both modes, strides and
 # paddings; heights that leave a partial block of 1, 2 and 3 output rows (and none)
 @pytest.mark.parametrize("shape", [(8, 64, 45, 47), (2, 48, 149, 147), (16, 32, 96, 101), (16, 32, 97, 96), (8, 64, 64, 88)])
