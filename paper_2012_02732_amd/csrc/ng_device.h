@@ -381,6 +381,32 @@ struct PairArgs {
     int na, nb;                // tiles of the first and of the second task
 };
 
+// Which share of a conv1x1's backward launch (input gradient and weight gradient together) workgroup `tile` takes. From kXcdSplits
+// splits of the weight gradient on, everything that reads the pixels of one split - na workgroups of the input gradient, nb
+// blocks of the weight gradient - runs on one XCD, one after the other (workgroups are dealt out to the 8 XCDs by index):
+// workgroup 8 j + x takes part j % (na + nb) of split 8 (j / (na + nb)) + x, weight gradient first. Fewer splits would leave XCDs
+// without any of the input gradient: there its na workgroups (over all pixels) and the nb blocks of every split are dealt out in
+// turns of eight, one for each XCD.
+// A training step of eight layers of 256 -> 256 channels on one image, single-stream graph: 16 x 16 pixels (one split) 218 us with
+// everything on one XCD, 175 so; 24 x 24 (three splits) 219 and 180; two images (five splits) 222 and 198.
+constexpr int kXcdSplits = 8;
+enum { SHARE_NONE = -1, SHARE_INPUT = 0, SHARE_WEIGHT = 1 };
+struct BackwardShare { int which, split, part; };       // input gradient of few splits: split 0, part = workgroup
+constexpr BackwardShare pw_backward_share(int tile, int na, int nb, int splits) {
+    if (splits >= kXcdSplits) {
+        const int per = na + nb, j = tile >> 3, split = 8 * (j / per) + (tile & 7), part = j % per;
+        return split >= splits ? BackwardShare{SHARE_NONE, 0, 0} : part < nb ? BackwardShare{SHARE_WEIGHT, split, part} : BackwardShare{SHARE_INPUT, split, part - nb};
+    }
+    const int weight = nb * splits, both = (na < weight ? na : weight) & ~7;            // workgroups of either kind, in eights
+    const int rest = tile - 2 * both, eight = tile >> 3;
+    const bool input = rest < 0 ? (eight & 1) == 0 : rest < na - both;
+    const int t = rest < 0 ? 8 * (eight >> 1) + (tile & 7) : input ? both + rest : rest - na + 2 * both;
+    return input ? BackwardShare{SHARE_INPUT, 0, t} : BackwardShare{SHARE_WEIGHT, t % splits, t / splits};
+}
+constexpr int pw_backward_tiles(int na, int nb, int splits) {
+    return splits >= kXcdSplits ? (splits + 7) / 8 * 8 * (na + nb) : na + nb * splits;
+}
+
 // ---- device-resident replay: the task schedule as data in device memory -------------------
 constexpr int kArgWords = 48;        // words of the argument block the resident kernel prefetches
 

@@ -1904,22 +1904,19 @@ using PairDwArgs = PairArgs<DwGradArgs, DwGradArgs>;
 using PairPwArgs = PairArgs<GemmArgs, GemmArgs>;
 // The input gradient (a) and the weight gradient (b) of a 1 x 1 convolution in one launch. Every block of 16 x 16 or 32 x 32
 // weights reads a row block of dY and of X, every 16 rows of dX read all of dY: with 44 channels each tensor is read three
-// times. The pixels are cut into the splits of the weight gradient, and everything that reads the pixels of one split - na
-// workgroups of the input gradient, nb blocks of the weight gradient - runs on one XCD, one after the other, so that
-// memory is read once and the rest comes from that XCD's L2 (workgroups are dealt out to the 8 XCDs by index):
-// workgroup 8 j + x takes part j % (na + nb) of split 8 (j / (na + nb)) + x.
+// times. The pixels are cut into the splits of the weight gradient, and everything that reads the pixels of one split runs on
+// one XCD (pw_backward_share), so that memory is read once and the rest comes from that XCD's L2.
 template <int KB, bool FIN, class Wait>
 __device__ __forceinline__ void pw_backward_tile(const PairPwArgs& p, int tile, float* smem, int tid, bool live, Wait& wait) {
-    const int per = p.na + p.nb, j = tile >> 3;
-    const int split = 8 * (j / per) + (tile & 7), part = j % per - p.nb;
-    if (split >= p.b.splits) return;                            // the whole workgroup (launched alone, never by the resident kernel)
-    if (part >= 0) {
+    const BackwardShare s = pw_backward_share(tile, p.na, p.nb, p.b.splits);
+    if (s.which == SHARE_NONE) return;                          // the whole workgroup (launched alone, never by the resident kernel)
+    if (s.which == SHARE_INPUT) {
         const int HW = p.a.Ho * p.a.Wo, quads = p.a.N / HW * ((HW + 3) >> 2);
-        const int MT = (p.a.M + 15) >> 4, PG = (quads + 15) >> 4, each = (PG + p.b.splits - 1) / p.b.splits;
-        const int task = part * 4 + (tid >> 6), pg = task / MT;
-        pw_px_wave<GEMM_PW_DGRAD, FIN>(p.a, split * each + pg, task - pg * MT, live && pg < each && split * each + pg < PG, tid, wait);
+        const int MT = (p.a.M + 15) >> 4, PG = (quads + 15) >> 4, each = p.b.splits >= kXcdSplits ? (PG + p.b.splits - 1) / p.b.splits : PG;
+        const int task = s.part * 4 + (tid >> 6), pg = task / MT;
+        pw_px_wave<GEMM_PW_DGRAD, FIN>(p.a, s.split * each + pg, task - pg * MT, live && pg < each && s.split * each + pg < PG, tid, wait);
     } else {
-        KernelOf<KB>::template tile<FIN>(p.b, (part + p.nb) * p.b.splits + split, smem, tid, live, wait);
+        KernelOf<KB>::template tile<FIN>(p.b, s.part * p.b.splits + s.split, smem, tid, live, wait);
     }
 }
 #define NG_PAIR(KID, ARGS, NAME, KA, KB)                                                       \
@@ -2388,11 +2385,11 @@ static void set_pw_backward(const Task& dgrad, const Task& wgrad, Task& t) {
     std::memcpy(&p.a, dgrad.args, sizeof p.a);
     std::memcpy(&p.b, wgrad.args, sizeof p.b);
     const long hw = (long)p.a.Ho * p.a.Wo, groups = ceil_div(p.a.N / hw * ceil_div(hw, 4), 16);
-    p.na = (int)ceil_div(ceil_div(groups, p.b.splits) * ceil_div(p.a.M, 16), 4);
+    p.na = (int)ceil_div((p.b.splits >= kXcdSplits ? ceil_div(groups, p.b.splits) : groups) * ceil_div(p.a.M, 16), 4);
     p.nb = (int)(wgrad.ntiles / p.b.splits);
     t = Task();
     t.block[0] = kBlock;
-    set_kernel<KID>(t, p, ceil_div(p.b.splits, 8) * 8 * (p.na + p.nb));
+    set_kernel<KID>(t, p, pw_backward_tiles(p.na, p.nb, p.b.splits));
 }
 void make_pair_task(const Task& first, const Task& second, Task& t) {
     switch (pair_kid(first.kid, second.kid)) {

@@ -871,3 +871,45 @@ int main() {
     kernels = open(os.path.join(ROOT, "paper_2012_02732_amd", "csrc", "ng_kernels.hip")).read()
     loads = re.findall(r"raw_buffer_load_b128\(wr, (.*)", kernels)
     assert sum(l.startswith("at.lane + lane * 16, at.scalar + ") for l in loads) == 3 and not [l for l in loads if l.startswith("lane * 16")]
+
+
+def test_shares_of_the_conv1x1_backward_launch(tmp_path):
+    """Every workgroup of the input gradient and every block of every split of the weight gradient is taken exactly once, and the
+    eight XCDs (workgroups are dealt out to them by index) get the same share of both, to one split where there are eight and more,
+    to one workgroup where there are fewer splits than XCDs."""
+    import subprocess
+    src = tmp_path / "shares.cpp"
+    src.write_text(r"""
+#include <cstdio>
+#include <set>
+#include <utility>
+#include "ng_device.h"
+int main() {
+    for (int splits : {1, 2, 3, 7, 8, 9, 16, 17, 128})
+        for (int na : {1, 5, 16, 128})
+            for (int nb : {1, 4, 64}) {
+                std::set<std::pair<int, int>> input, weight;
+                int on_xcd[2][8] = {};
+                const int tiles = ng::pw_backward_tiles(na, nb, splits);
+                for (int t = 0; t < tiles; ++t) {
+                    const ng::BackwardShare s = ng::pw_backward_share(t, na, nb, splits);
+                    if (s.which == ng::SHARE_NONE) continue;
+                    if (s.split < 0 || s.split >= splits || s.part < 0 || s.part >= (s.which == ng::SHARE_INPUT ? na : nb)) return 1;
+                    if (!(s.which == ng::SHARE_INPUT ? input : weight).insert({s.split, s.part}).second) return 2;
+                    ++on_xcd[s.which][t & 7];
+                }
+                const bool by_xcd = splits >= 8;
+                if ((int)input.size() != (by_xcd ? na * splits : na) || (int)weight.size() != nb * splits) return 3;
+                for (int w = 0; w < 2; ++w) {
+                    int lo = on_xcd[w][0], hi = lo;
+                    for (int x : on_xcd[w]) lo = x < lo ? x : lo, hi = x > hi ? x : hi;
+                    if (hi - lo > (!by_xcd ? 1 : splits % 8 == 0 ? 0 : w == ng::SHARE_INPUT ? na : nb)) return 4;
+                }
+            }
+    std::puts("ok");
+}
+""")
+    exe = str(tmp_path / "shares")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2012_02732_amd", "csrc"), str(src), "-o", exe], check=True)
+    done = subprocess.run([exe], capture_output=True, text=True)
+    assert (done.returncode, done.stdout.strip()) == (0, "ok")
