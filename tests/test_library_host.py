@@ -913,3 +913,19 @@ int main() {
     subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2012_02732_amd", "csrc"), str(src), "-o", exe], check=True)
     done = subprocess.run([exe], capture_output=True, text=True)
     assert (done.returncode, done.stdout.strip()) == (0, "ok")
+
+
+@pytest.mark.parametrize("stride", [0, 3, 4])
+def test_pools_and_their_gradients_take_strides_of_one_and_two(stride):
+    """Kernels exist for these two only."""
+    g = B.ng_create()
+    x = B.ng_add_input(g, (2, 4, 9, 9))
+    p = B.ng_op_params()
+    p.stride, p.pad, p.pool_mode = stride, 0, 0
+    with pytest.raises(B.NgError):
+        B.ng_add_node(g, B.NG_OP_POOL, p, [x], [])
+    size = (9 - 3) // max(stride, 1) + 1
+    dy = B.ng_add_input(g, (2, 4, size, size))
+    with pytest.raises(B.NgError):
+        B.ng_add_node(g, B.NG_OP_POOL_DGRAD, p, [dy, x], [])
+    B.ng_destroy(g)
