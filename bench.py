@@ -5,9 +5,9 @@ One "step" = one replay of the whole recorded DAG (every task of the workload) o
 already sits in the arena, followed by a wait for its completion: the DAG latency. The timed
 region uses the replay mode the library itself found fastest for the DAG in its trial at capture
 time (NG_MODE_AUTO). Prints ONE JSON line: the contract fields for the headline workload
-(nasnet_style, batch 1) and, under "configs", the same measurements for all five configurations
-and for inception_style at batch 32 (the paper's Table 1 compares multi- and single-stream replay
-per network). Per configuration:
+(nasnet_style, batch 1) and, under "configs", the main figures of all five configurations, of
+inception_style at batch 32 (the paper's Table 1 compares multi- and single-stream replay per network)
+and of a training step; stderr has each configuration's measurements in full. Per configuration:
 
   * latency of replay + wait (median, p10, p90), device-side time, throughput;
   * the critical-path time of Section 3 in two forms - `all_tasks`: longest path of the DAG weighted
@@ -46,7 +46,6 @@ if ROOT not in sys.path:
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 PEAK_MFMA_F32_TFLOPS = 157.3   # MI355X fp32 matrix
 PEAK_SPLIT_BF16_TFLOPS = 2500.0 / 6   # fp32 products as six bf16 ones (the patch-stationary and split-K convolutions)
-RIDGE_FLOP_PER_BYTE = PEAK_MFMA_F32_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)
 
 # HBM bytes of one launch of the dominant kernel, from two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB
 # per dispatch) scaled by what the same counters read for a plain 256 MiB copy (2.00 and 1.00). Key:
@@ -259,7 +258,7 @@ def measure(name, batch, steps, warmup, args, headline):
                           "fraction_of_bound_device_side": t_cp_exe / dev_us, "sum_isolated_us": sum(t_exe),
                           "kernels_run": sum(1 for t in t_exe if t > 0),
                           "note": "weights = the kernels the replay mode really runs, fused variants timed as themselves, tasks "
-                                  "without a kernel of their own weigh 0: the harder of the two, the one the 0.80 target is judged on"},
+                                  "without a kernel of their own weigh 0: the harder of the two, the one the 0.80 target is for"},
           "launch_and_wait_floor_us": floor_us,
           "fraction_as_executed_above_floor": t_cp_exe / max(t_e2e - floor_us, 1e-9)}
     if name == "chain50":
@@ -307,11 +306,10 @@ def measure(name, batch, steps, warmup, args, headline):
         d = per_kernel[dom]
         avg_us = d["us"] / d["launches"]
         intensity = d["flops"] / max(d["bytes"], 1.0)
-        if intensity >= RIDGE_FLOP_PER_BYTE:
+        bound, peak = matrix_peak(dom)
+        if intensity >= peak * 1e12 / (PEAK_HBM_GBS * 1e9):     # the ridge of the rate that this kernel's products run at
             achieved = d["flops"] / d["us"] * 1e-6
-            split = "_patch_" in dom or dom.endswith("_split_k")
-            peak = PEAK_SPLIT_BF16_TFLOPS if split else PEAK_MFMA_F32_TFLOPS
-            roofline = {"kernel": dom, "bound": "mfma_bf16_split" if split else "mfma_f32", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+            roofline = {"kernel": dom, "bound": bound, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                         "frac": achieved / peak}
         else:
             achieved = d["bytes"] / d["us"] * 1e-3
@@ -361,6 +359,31 @@ def measure(name, batch, steps, warmup, args, headline):
     del runner
     torch.cuda.empty_cache()
     return out
+
+
+def matrix_peak(kernel):
+    """(name, TFLOP/s) of the matrix rate that bounds a kernel's products."""
+    split = "_patch_" in kernel or kernel.endswith("_split_k")
+    return ("mfma_bf16_split", PEAK_SPLIT_BF16_TFLOPS) if split else ("mfma_f32", PEAK_MFMA_F32_TFLOPS)
+
+
+def figures(value):
+    """The same without texts that explain, numbers to six digits."""
+    if isinstance(value, dict):
+        return {k: figures(v) for k, v in value.items() if k not in ("note", "definition", "timing")}
+    return float("%.6g" % value) if isinstance(value, float) else value
+
+
+def brief(r):
+    """What the result line says of a configuration. Its full measurements go to stderr: all seven of them are 25 KB, more than
+    what keeps a program's last output holds (8 KB)."""
+    cp, roof = r["critical_path"], r["roofline"]
+    return figures({
+        "replay": r["replay"], "steps": r["steps"], "latency_us": {k: r["latency_us"][k] for k in ("median", "p10", "p90")},
+        "fraction_of_critical_path": {k: cp[k]["fraction_of_bound"] for k in ("all_tasks", "as_executed")},
+        "overhead_us_per_task": cp["overhead_us_per_task"], "modes_median_us": r["modes_median_us"],
+        "multi_stream_graph_check": r["auto_mode"]["multi_stream_graph_check"]["state"],
+        "roofline": {k: roof[k] for k in ("kernel", "bound", "achieved", "unit", "frac")}})
 
 
 def solo_launches(args):
@@ -567,6 +590,7 @@ def main():
         results[label(name, batch)] = measure(name, batch, steps, warmup, args, is_head)
         print(f"[bench] {label(name, batch)}: {results[label(name, batch)]['latency_us']['median']:.1f} us per replay "
               f"({results[label(name, batch)]['replay']}), measured in {time.perf_counter() - t0:.1f} s", file=sys.stderr, flush=True)
+        print(f"[bench] {json.dumps(results[label(name, batch)])}", file=sys.stderr, flush=True)
 
     h = results[label(*head)]
     ms_per_step = h.pop("_ms_per_step")
@@ -574,26 +598,19 @@ def main():
         r.pop("_ms_per_step", None)
     out = {
         "metric": "DAG latency (µs) at batch 1; % of critical-path bound; µs overhead/task",
-        "metric_note": "value = wall time of the K timed steps (each: replay + wait) / K on the headline workload, input resident in HBM; "
-                       "the other two parts of the metric are critical_path.as_executed.fraction_of_bound (the harder of the two bounds) "
-                       "and critical_path.overhead_us_per_task; every configuration is under 'configs'",
+        "metric_note": "value = wall time of the K timed steps (each: replay + wait) / K on the headline workload; the other parts: "
+                       "critical_path.as_executed.fraction_of_bound, critical_path.overhead_us_per_task; in full on stderr",
         "value": ms_per_step * 1e3, "unit": "us",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": h["workload"], "input_shape": h["input_shape"], "tasks": h["tasks"], "streams": h["streams"],
                    "sync_edges": h["sync_edges"], "events": h["events"], "replay": h["replay"]},
-        "latency_us": h["latency_us"],
-        "throughput_replays_per_s": h["throughput_replays_per_s"],
-        "critical_path": h["critical_path"],
-        "modes_median_us": h["modes_median_us"],
-        "roofline": h["roofline"],
+        **figures({k: h[k] for k in ("latency_us", "throughput_replays_per_s", "critical_path", "modes_median_us", "roofline")}),
     }
-    if "resident_timeline" in h:
-        out["resident_timeline"] = h["resident_timeline"]
     if "cpu_baseline" in h:
-        out["cpu_baseline"] = h.pop("cpu_baseline")
-    out["configs"] = results
+        out["cpu_baseline"] = figures(h["cpu_baseline"])
+    out["configs"] = {name: brief(r) for name, r in results.items() if r is not h}
     print(json.dumps(out))
 
 

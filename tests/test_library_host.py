@@ -929,3 +929,24 @@ def test_pools_and_their_gradients_take_strides_of_one_and_two(stride):
     with pytest.raises(B.NgError):
         B.ng_add_node(g, B.NG_OP_POOL_DGRAD, p, [dy, x], [])
     B.ng_destroy(g)
+
+
+def test_benchmark_line_of_all_configurations_stays_short():
+    """Seven configurations in brief: what is printed on one line has to fit what is kept of a program's output (8 KB)."""
+    import json
+    import bench
+    full = {"workload": "inception_style_b32", "tasks": 180, "streams": 4, "replay": "device_resident", "steps": 500,
+            "latency_us": {k: 3604.9595000005042 for k in ("median", "p10", "p90", "device_side", "mean_over_timed_region")},
+            "throughput_images_per_s": 8908.942820188953,
+            "critical_path": {"definition": "x" * 300, "overhead_us_per_task": 7.835225234731814,
+                              **{k: {"fraction_of_bound": 0.6722821556814721, "note": "x" * 300} for k in ("all_tasks", "as_executed")}},
+            "modes_median_us": {k: 645.8790000003489 for k in bench.MODES},
+            "auto_mode": {"chosen": "graph_multi", "trial_us": {k: 644.322021484375 for k in bench.MODES},
+                          "multi_stream_graph_check": {"state": 1, "replays_compared": 58}},
+            "roofline": {"kernel": "conv1x1_px_dgrad+wgrad_32", "bound": "mfma_bf16_split", "achieved": 19.88604495884629,
+                         "peak": 416.6666666666667, "unit": "TFLOP/s", "frac": 0.0477265079012311, "timing": "x" * 300}}
+    line = json.dumps({bench.label(*c): bench.brief(full) for c in bench.ALL_CONFIGS if c != bench.HEADLINE})
+    assert len(line) < 3800 and '"fraction_of_critical_path": {"all_tasks": 0.672282, "as_executed": 0.672282}' in line
+    # a kernel's ridge is that of the rate its own products run at
+    assert bench.matrix_peak("conv3x3_mfma_split_k") == bench.matrix_peak("conv1x1_patch_64x64") == ("mfma_bf16_split", 2500.0 / 6)
+    assert bench.matrix_peak("conv1x1_s3") == bench.matrix_peak("conv3x3_mfma_3") == ("mfma_f32", 157.3)
