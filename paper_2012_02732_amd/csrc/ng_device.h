@@ -32,21 +32,21 @@ enum Kid : int {
     // conv1x1 for many output pixels on the same plan (activations pixel-major in LDS, 32 or 64 channels at a time, weights
     // straight from memory): 32 x 64 and 64 x 64 output tiles
     KID_PW_P32, KID_PW_P64,
-    KID_DW_LDS,                      // depthwise 3 x 3 / 5 x 5, stride 1 / 2 on planes of up to 1024 pixels staged in LDS, four outputs side by side per thread
+    KID_DW_LDS,                      // depthwise 3 x 3 / 5 x 5, stride 1 / 2 on planes of up to 256 quads of pixels staged in LDS, four outputs side by side per thread
     KID_POOL_ROW_S1, KID_POOL_ROW_S2,   // pool3x3 for large tensors: a thread computes 4 outputs of a column, lanes run along the row (stride 1 / 2)
     // graphs that train (weights change between replays, so nothing is repacked): convolutions and fc, forward and backward,
     // as one LDS-staged MFMA GEMM that gathers its operands from the natural layouts; the other backward operators; the update
     KID_GEMM_PW_FWD, KID_GEMM_PW_DGRAD, KID_GEMM_PW_WGRAD, KID_GEMM_C3_FWD, KID_GEMM_C3_DGRAD, KID_GEMM_C3_WGRAD,
     KID_SMALL_GEMM,                  // C = A B (+ bias) of a few thousand outputs at most (the classifier of a network that trains, forward and backward): no tiles, no LDS
-    KID_PW_PX_FWD, KID_PW_PX_DGRAD,  // conv1x1 forward / input gradient for few channels: pixels read 128 bits at a time straight into matrix-instruction operands (HW % 4 == 0)
-    KID_C3_WGRAD_PX, KID_C3_WGRAD_PX2,  // the same for conv3x3 (stride 1, padding 1, rows of a multiple of 16 pixels): the second operand is the input shifted by the tap
-    KID_PW_WGRAD_PX, KID_PW_WGRAD_PX2,  // conv1x1 weight gradient with both operands read along the pixels, 128 bits at a time (HW % 16 == 0): blocks of 16 x 16 / 32 x 32 weights
+    KID_PW_PX_FWD, KID_PW_PX_DGRAD,  // conv1x1 forward / input gradient for few channels: pixels read 128 bits at a time straight into matrix-instruction operands (HW >= 4)
+    KID_C3_WGRAD_PX, KID_C3_WGRAD_PX2,  // the same for conv3x3 (stride 1, padding 1, rows of four pixels and more): the second operand is the input shifted by the tap
+    KID_PW_WGRAD_PX, KID_PW_WGRAD_PX2,  // conv1x1 weight gradient with both operands read along the pixels, 128 bits at a time (HW >= 4): blocks of 16 x 16 / 32 x 32 weights
     KID_BN_RAW, KID_BN_DGRAD, KID_BN_WGRAD, KID_RELU_DGRAD, KID_DW_DGRAD, KID_DW_DGRAD_LDS, KID_DW_WGRAD, KID_POOL_DGRAD, KID_POOL_DGRAD_LDS, KID_GAP_DGRAD,
     KID_CHANNEL_SUM, KID_SLICE_PAD, KID_SGD,
     KID_SGD_BATCH,                   // several update nodes in one launch (launch-based replay modes only, in no build of the resident kernel)
     KID_BN_BACKWARD,                 // batch-norm input gradient and parameter gradients of the same (dy, x) in one launch (likewise)
-    // two tasks that read the same gradient, in one launch with their workgroups interleaved (likewise): depthwise input and
-    // weight gradient; conv1x1 input gradient with the weight gradient in blocks of 16 x 16 / 32 x 32
+    // two tasks that read the same gradient, in one launch (likewise): depthwise input and weight gradient, dealt out alternately;
+    // conv1x1 input gradient with the weight gradient in blocks of 16 x 16 / 32 x 32 (pw_backward_share)
     KID_PAIR_DW, KID_PAIR_DW_LDS, KID_PAIR_PW16, KID_PAIR_PW32,
     KID_COUNT
 };
@@ -373,7 +373,7 @@ struct SgdBatchArgs {
     const SgdTile* tiles;      // [ntiles]
 };
 
-// Two tasks in one launch: tiles of both, dealt out alternately while both have tiles left.
+// Two tasks in one launch: tiles of both, dealt out alternately while both have tiles left (depthwise; conv1x1: pw_backward_share).
 template <class A, class B>
 struct PairArgs {
     A a;

@@ -2509,6 +2509,9 @@ PwChoice choose_pw(const ng_graph* g, int v) {
     // the resident kernel has room for: a NAS cell on 25 x 25 maps (240 tiles) replays in 356 us with 16 x 16 tiles (lean
     // build) and in 474 us with two of its tasks on 32 x 32 tiles, which take 4.2 us there against 2.9 us; an
     // Inception-style network at batch 1 (31 layers of 17 x 17 and 35 x 35 maps, 228 - 385 tiles) 765 against 810 us.
+    // Graphs in the full build and launched ones gain as well: of chains of twelve layers between 44 - 2048 channels, 7 x 7 to 45 x 45
+    // (121 - 512 tiles), 17 of 17 are faster as a single-stream graph and 15 in the resident kernel (two 2 % slower): 17 x 17 768 <-> 192 86 / 175 -> 63 / 123 us, 35 x 35
+    // 64 <-> 64 46 / 80 -> 42 / 46, 7 x 7 2048 <-> 1000 162 / 350 -> 103 / 115, 35 x 35 1024 <-> 64 120 / 197 -> 113 / 183.
     if (!vec && tiles16 > 512) {
         c.kind = PwChoice::DIRECT32;
         c.in_flight = pw_chunk(cin);
@@ -2568,7 +2571,11 @@ PwChoice choose_c3(const ng_graph* g, int v) {
     // 17 x 17 192 -> 192 one image 11.5 / 20.9 / 9.2 (15), 14 x 14 192 -> 192 six images 31 / 20 / 10 (72), 35 x 35 96 -> 96
     // four images 34 / 13.4 / 11.3 (160); 30 x 30 64 -> 96 six images 22.6 / 11.0 / 11.8 (180), 8 x 8 384 -> 768 twenty images
     // 196 / 41.5 / 43 (240). Where they don't apply (a stride of 2), from 96 tiles of 64 x 64 on the large tiles: 30 x 30 ->
-    // 14 x 14 288 -> 384 six images 80 / 47 (144), one image of 35 x 35 -> 17 x 17 27 / 46 (30).
+    // 14 x 14 288 -> 384 six images 80 / 47 (144), one image of 35 x 35 -> 17 x 17 27 / 46 (30). 22 more layers of 64 - 512 channels
+    // around the first line, 64 x 64 tiles / these: 120 - 144 tiles 10.3 - 53 / 7.4 - 30.4 (six, these 20 - 45 % faster), 156 - 160
+    // 10.6 - 23.9 / 10.6 - 21.5, 180 - 192 10.5 - 52.5 / 10.7 - 40.6, 200 - 250 10.9 - 22.6 / 12.9 - 25.0 (these 9 - 33 % slower). 14 more
+    // with a stride of 2 around the second, gathering kernel / 64 x 64: 48 tiles 35 / 44.5, 60 - 96 within 7 % of each other, 108
+    // 26 / 18 and 67 / 47.5.
     if (!knob("NG_NO_PATCH_KERNELS")) {
         const long tiles64 = nd.out.n * ceil_div(nd.out.h * nd.out.w, 64) * ceil_div(nd.out.c, 64);
         int kid = choose_patch_kernel(in, nd.out, nd.p.stride, nd.p.pad);
