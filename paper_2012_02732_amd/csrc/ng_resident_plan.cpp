@@ -559,6 +559,13 @@ int plan_resident(const ng_graph* g, int n_wg, int xcds, const PlanKnobs& knobs,
         static_assert(sizeof d.args <= sizeof t.args, "argument blocks");
         std::memcpy(d.args, t.args, sizeof d.args);
     }
+    // Where a tensor's values come from: the XCD of its task, -1: several. Inputs that were produced inside a concat's result
+    // come from where their own producers ran, whether the concat has other inputs to copy or not.
+    std::vector<int> origin = best.xcd;
+    for (int v = 0; v < n; ++v)
+        if (g->nodes[v].op == NG_OP_CONCAT && !g->alias_of.empty())
+            for (int u : g->nodes[v].preds)
+                if (g->alias_of[u] == v && g->tasks[u].fn && origin[u] != origin[v]) origin[v] = -1;
     // A tensor crosses XCDs when a direct reader (any edge of E, not only E') runs elsewhere.
     for (int v = 0; v < n; ++v) {
         if (!g->tasks[v].fn) continue;
@@ -566,7 +573,7 @@ int plan_resident(const ng_graph* g, int n_wg, int xcds, const PlanKnobs& knobs,
         for (size_t j = 0; j < preds.size(); ++j) {
             const int u = preds[j];
             if (!g->tasks[u].fn) continue;          // network input: written before the launch
-            const bool far = best.xcd[u] < 0 || best.xcd[v] < 0 || best.xcd[u] != best.xcd[v] || g->resident_all_far;
+            const bool far = origin[u] < 0 || best.xcd[v] < 0 || origin[u] != best.xcd[v] || g->resident_all_far;
             if (far) plan.tasks[v].far_in |= 1u << j;
         }
         if (plan.tasks[v].far_in)                    // one far operand: every operand comes through the memory side
@@ -574,10 +581,11 @@ int plan_resident(const ng_graph* g, int n_wg, int xcds, const PlanKnobs& knobs,
                 if (g->tasks[u].fn) plan.tasks[u].release_far = 1;
         if (g->resident_all_far) plan.tasks[v].release_far = 1;
     }
-    // the stores into an in-place concat are its producers' stores
+    // the stores into the part of a concat that is in place are its producers' stores
     for (int v = n - 1; v >= 0; --v)
-        if (best.elided[v] && plan.tasks[v].release_far)
-            for (int u : g->nodes[v].preds) plan.tasks[u].release_far = 1;
+        if (g->nodes[v].op == NG_OP_CONCAT && !g->alias_of.empty() && plan.tasks[v].release_far)
+            for (int u : g->nodes[v].preds)
+                if (g->alias_of[u] == v) plan.tasks[u].release_far = 1;
     // fused pairs: the convolution's argument block gets the batch-norm's coefficients and output
     for (int v = 0; v < n; ++v) {
         const int u = best.fused_into[v];
@@ -807,6 +815,30 @@ bool resident_plan_is_consistent(const ng_graph* g, const ResidentPlan& plan) {
             const int part = partition_of(plan.tasks[u].kid);
             ok = ok && !plan.elided[u] && plan.fused_into[v] < 0 && part != PART_NONE && part == partition_of(d.kid) &&
                  plan.tasks[u].ntiles == d.ntiles && g->nodes[u].out == g->nodes[v].out && where[src] == where[v];
+        }
+    }
+    // Every load sees the stores it reads: a task whose loads are device-scope accesses reads what was stored that way, any other
+    // one only what workgroups of its own XCD stored. Into an in-place concat its inputs' producers store, into one that is
+    // in place for some of its inputs both they and the concat.
+    std::vector<unsigned> xcds_of(n, 0);
+    for (int w = 0; w < plan.n_wg; ++w)
+        for (int e = plan.wg_first[w]; e < plan.wg_first[w + 1]; ++e) xcds_of[plan.entries[e].task] |= 1u << (w % 8);
+    std::function<void(int, std::vector<int>&)> stores_of = [&](int u, std::vector<int>& list) {
+        if (!g->tasks[u].fn) return;                                              // written before the launch
+        if (!plan.elided[u]) list.push_back(plan.fused_into[u] >= 0 ? plan.fused_into[u] : u);
+        if (g->nodes[u].op == NG_OP_CONCAT && !g->alias_of.empty())
+            for (int p : g->nodes[u].preds)
+                if (g->alias_of[p] == u) stores_of(p, list);
+    };
+    for (size_t v = 0; v < n && ok; ++v) {
+        if (!g->tasks[v].fn || plan.elided[v]) continue;
+        const int dst = plan.fused_into[v] >= 0 ? plan.fused_into[v] : (int)v;
+        std::vector<int> stores;
+        for (int u : g->nodes[v].preds) stores_of(u, stores);
+        for (int s : stores) {
+            if (s == dst) continue;                                               // in the registers of its own tile
+            const unsigned both = xcds_of[s] | xcds_of[dst];
+            ok = ok && (plan.tasks[v].far_in != 0 ? plan.tasks[s].release_far != 0 : (both & (both - 1)) == 0);
         }
     }
     // epilogues are there exactly where a task was fused; late parents only with a fused add_n

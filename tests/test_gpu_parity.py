@@ -185,6 +185,18 @@ def test_concat_of_odd_maps(shape, slices, kernel):
     check_all_nodes(w, (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_DEVICE_RESIDENT))
 
 
+# A concat that copies one input and finds the other in place: whoever reads it on another XCD reads what the other input's
+# producer stored, not only what the concat did.
+@pytest.mark.parametrize("nested", [False, True])
+def test_concat_partly_in_place(nested):
+    def build(b):
+        x = b.input(1, 16, 18, 19)
+        c = b.concat([x, b.bn_act(x, relu=False)], [(8, 16), (0, 16)])
+        y = b.dwconv(b.bn_act(b.conv3x3(c, 70, 1, 1), relu=True), 5, 1)
+        b.concat([y, c] if nested else [y, y], [(0, 70), (0, 24)])
+    check_all_nodes(single_op(build), (B.NG_MODE_DEVICE_RESIDENT, B.NG_MODE_AUTO, B.NG_MODE_GRAPH_MULTI))
+
+
 # The patch-stationary convolutions multiply in three bf16 parts per value. Against 64 bits, ragged in every direction: their
 # large accumulator is rounded once per 16 products, and partial sums grow to the result, so the 2-norm of the error is at most
 # about 2^-24 sqrt(K / 16) of the result's; one more 2^-24 for the stored value.

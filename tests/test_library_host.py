@@ -950,3 +950,37 @@ def test_benchmark_line_of_all_configurations_stays_short():
     # a kernel's ridge is that of the rate its own products run at
     assert bench.matrix_peak("conv3x3_mfma_split_k") == bench.matrix_peak("conv1x1_patch_64x64") == ("mfma_bf16_split", 2500.0 / 6)
     assert bench.matrix_peak("conv1x1_s3") == bench.matrix_peak("conv3x3_mfma_3") == ("mfma_f32", 157.3)
+
+
+def test_resident_plans_of_concats_partly_in_place():
+    """Random stacks of concats with slices, some inputs in place and some not, read by tasks on one XCD and on all: the plans pass
+    their self-check, which follows every tensor to the workgroups that store it."""
+    rng = np.random.default_rng(77)
+    far = 0
+    for case in range(60):
+        b = Builder("concats")
+        h, w = int(rng.integers(5, 24)), int(rng.integers(5, 24))
+        tensors = [b.input(1, 16, h, w)]
+        for _ in range(int(rng.integers(3, 7))):
+            y = tensors[int(rng.integers(max(0, len(tensors) - 3), len(tensors)))]
+            kind = int(rng.integers(0, 4))
+            if kind == 0:
+                y = b.bn_act(y, relu=True)
+            elif kind == 1:
+                y = b.conv3x3(y, int(rng.choice([16, 40, 70])), 1, 1)
+            else:
+                other = tensors[int(rng.integers(0, len(tensors)))]
+                pair = [b.relu(y), other] if kind == 2 else [other, b.dwconv(y, 3, 1)]
+                slices = [(0 if i == kind - 2 or rng.integers(0, 2) else b.shape(t)[1] // 2, b.shape(t)[1]) for i, t in enumerate(pair)]
+                y = b.concat(pair, slices)
+            tensors.append(y)
+        b.draw_weights(rng, 0.2, "random")
+        r = GraphRunner(b.finish(rng))
+        r.schedule()
+        r.plan()
+        for xcds in (0, 1, 2, 8):
+            d = B.ng_resident_dry_plan(r.g, 256, xcds)
+            assert d["ok"], (case, xcds)
+            far += d["n_far_edges"]
+        r.close()
+    assert far > 0
