@@ -696,8 +696,10 @@ __device__ __forceinline__ void conv3x3_lds_tile(const C3Args& a, int tile, floa
 // there down to |x| = 2^-110, on either side of the product; below that x is taken to the next multiple of 2^-133 (2-norm of
 // the error for values around 2^-118: 9e-6, 2^-126: 2e-3; the fp32 instructions lose nothing there). Sums that also have
 // values of 2^-110 and more do not notice. Parts scaled by 64 and 4096 would keep all bits down to 2^-122, but take an
-// accumulator more and two multiplications per activation: conv3x3 1 - 3 % and conv1x1 up to 8 % slower, and the full build of
-// the resident kernel spills 622 registers instead of 184 (sixteen conv3x3_mfma_split_k of 28 x 28 128 and below 390 -> 552 us).
+// accumulator more and two multiplications per activation: conv3x3 1 - 3 % and conv1x1 up to 8 % slower, an Inception-style network
+// at batch 1, 6 and 32 711 -> 725, 1151 -> 1170, 3613 -> 3633 us; and the full build of the resident kernel spills 622 registers
+// instead of 184 (a network of sixteen conv3x3_mfma_split_k, 28 x 28 128 and below, 386 -> 552 us; with two slices of weights
+// ahead there instead of three 208 registers and 447 us).
 // The method: G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
 // Higher-Precision Computations", 2019.
 // Infinities and NaN. h is finite wherever x is (its bits are cut off, not rounded up), infinite where x is, NaN where x is (a
