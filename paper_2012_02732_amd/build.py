@@ -3,14 +3,14 @@
 Every source is compiled to an object of its own (in parallel) and the objects are linked
 into the shared library. ``build()`` recompiles everything; ``build(incremental=True)`` or
 ``python -m paper_2012_02732_amd.build --incremental`` skips objects that are newer than
-their source and every header. ``--knobs`` adds -DNG_MEASUREMENT_KNOBS: the build that reads
+their source and every file it includes. ``--knobs`` adds -DNG_MEASUREMENT_KNOBS: the build that reads
 the ablation switches from the environment (the product build reads no environment variable).
 """
 from __future__ import annotations
 
 import concurrent.futures
-import glob
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -20,7 +20,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnimble_graph.so")
-SOURCES = ["ng_graph.cpp", "ng_schedule.cpp", "ng_launch_graph.cpp", "ng_resident_plan.cpp", "ng_kernels.hip", "ng_runtime.hip"]
+# object -> (source, extra flags); the resident kernel's three builds compile side by side
+OBJECTS = {s: (s, []) for s in ("ng_graph.cpp", "ng_schedule.cpp", "ng_launch_graph.cpp", "ng_resident_plan.cpp", "ng_tasks.hip", "ng_runtime.hip")}
+OBJECTS.update({f"ng_resident_{n}": ("ng_resident.hip", [f"-DNG_RESIDENT_BUILD={i}"]) for i, n in enumerate(("lean", "full", "train"))})
 
 
 def hipcc() -> str:
@@ -41,23 +43,36 @@ def _flags(knobs: bool):
     return flags
 
 
+def _reads(path: str, seen=None) -> set:
+    """The file and every file of this repository that it includes, directly or through others (ng_kernels.hip, the tile functions, is
+    included by the files that build kernels from them)."""
+    seen = set() if seen is None else seen
+    if path in seen:
+        return seen
+    seen.add(path)
+    with open(path) as f:
+        for name in re.findall(r'^#include "([^"]+)"', f.read(), re.M):
+            for folder in (CSRC, os.path.join(ROOT, "include")):
+                if os.path.exists(os.path.join(folder, name)):
+                    _reads(os.path.join(folder, name), seen)
+    return seen
+
+
 def build(verbose: bool = True, incremental: bool = False, knobs: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    sources = list(SOURCES)
-    headers = glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(CSRC, "*.inc")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
-    newest_header = max(os.path.getmtime(h) for h in headers)
     stamp = os.path.join(OBJ, "flags.txt")
     flag_text = " ".join(_flags(knobs))
     if incremental and (not os.path.exists(stamp) or open(stamp).read() != flag_text):
         incremental = False
     jobs = []
-    for s in sources:
-        src, obj = os.path.join(CSRC, s), os.path.join(OBJ, s + ".o")
-        if incremental and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header):
+    # the slowest first
+    for o, (s, extra) in sorted(OBJECTS.items(), key=lambda kv: not kv[1][0].endswith(".hip")):
+        src, obj = os.path.join(CSRC, s), os.path.join(OBJ, o + ".o")
+        if incremental and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(f) for f in _reads(src)):
             continue
         # .cpp files are host-only: compile them as plain C++ (no device pass)
         lang = ["-x", "hip"] if s.endswith(".hip") else ["-x", "c++"]
-        jobs.append([hipcc()] + _flags(knobs) + lang + ["-c", src, "-o", obj])
+        jobs.append([hipcc()] + _flags(knobs) + extra + lang + ["-c", src, "-o", obj])
 
     def run(cmd):
         if verbose:
@@ -68,7 +83,7 @@ def build(verbose: bool = True, incremental: bool = False, knobs: bool = False) 
         list(pool.map(run, jobs))
     with open(stamp, "w") as f:
         f.write(flag_text)
-    run([hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950"] + [os.path.join(OBJ, s + ".o") for s in sources] + ["-o", LIB])
+    run([hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950"] + [os.path.join(OBJ, o + ".o") for o in OBJECTS] + ["-o", LIB])
     return LIB
 
 

@@ -163,11 +163,12 @@ struct ng_graph {
 namespace ng {
 // ng_schedule.cpp
 void compute_schedule(int n, const std::vector<std::pair<int, int>>& edges, Schedule& out, bool exact);
-// ng_kernels.hip: fill the launch descriptor of node v (addresses resolved against `arena`;
+// ng_tasks.hip: fill the launch descriptor of node v (addresses resolved against `arena`;
 // `packed` = node v's share of the library-owned constant memory, see packed_floats).
 int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t);
 size_t packed_floats(const ng_graph* g, int v);
 int pack_constants(ng_graph* g, int v, float* packed, void* stream);
+template <int BUILD> const void* resident_build_handle();   // defined in ng_resident.hip, one specialisation per object
 const void* resident_kernel_handle(int build);
 const void* empty_kernel_handle();
 const void* standalone_kernel_handle(int kid, const char** name);
