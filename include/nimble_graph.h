@@ -202,8 +202,9 @@ int ng_set_memory_reuse(ng_graph* g, int on);
  * and x) are computed in one walk over dy and x by the launch of whichever of the two comes first, if
  * both are on one stream (always, in modes 1 and 2); likewise the input gradient and the weight gradient
  * of a depthwise or 1 x 1 convolution (same dy) share one launch, their workgroups interleaved, if
- * everything the later one reads is complete when the earlier one starts. on = 0 switches the
- * exceptions off: one kernel per task. Call before ng_bind (NG_ESTATE after). */
+ * everything the later one reads is complete when the earlier one starts. In modes 1 and 2 tasks of the
+ * same kernel that do not wait for each other share a launch as well, and the launches follow each other in an
+ * order that lets them (ng_get_single_launches). on = 0 switches the exceptions off: one kernel per task. Call before ng_bind (NG_ESTATE after). */
 int ng_set_launch_fusion(ng_graph* g, int on);
 /* offset[n_nodes], bytes[n_nodes] of each node's output inside the arena (host arrays). */
 int ng_get_offsets(const ng_graph* g, size_t* offset, size_t* bytes);
@@ -227,6 +228,13 @@ int ng_critical_path(const ng_graph* g, const float* t, float* total, int* path,
  *   *n_edges: the number of edges; with max_edges = 0 only the count is returned, a positive
  *     max_edges that is too small gives NG_ENOMEM. All arrays are caller-owned host memory. */
 int ng_get_graph_edges(ng_graph* g, int fuse, int* launched_by, int* n_edges, int* src, int* dst, int max_edges);
+
+/* The launches of the single-stream modes (1 and 2) in the order in which they are issued, computed on the host (needs
+ * ng_plan_memory, no GPU): position[n_nodes] (may be NULL) receives the place of the launch that writes node v's tensor,
+ * 0 .. *n_launches - 1; -1 for a network input, -2 for a concat whose inputs are produced in place. Tasks at one place
+ * share a launch: those that ng_set_launch_fusion describes and, unless it is off or memory is reused, tasks of the same
+ * kernel none of which waits for another (their workgroups side by side, the same arithmetic). */
+int ng_get_single_launches(ng_graph* g, int* position, int* n_launches);
 /* Name of the kernel node `id` will be bound to, worked out on the host from the shapes alone (needs
  * ng_plan_memory, no GPU; after ng_bind the same as ng_task_kernel): which of the hand-written kernels a
  * task runs is decided by the library, per node, from its operator, shapes and the graph's being a

@@ -26,7 +26,7 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libnimble_g
 # every symbol include/nimble_graph.h declares
 SYMBOLS = ("ng_create", "ng_destroy", "ng_add_input", "ng_add_node", "ng_mark_output", "ng_num_nodes",
            "ng_node_shape", "ng_schedule", "ng_set_assignment", "ng_schedule_sizes", "ng_get_schedule", "ng_get_scaffold",
-           "ng_plan_memory", "ng_set_memory_reuse", "ng_set_launch_fusion", "ng_get_graph_edges", "ng_get_offsets",
+           "ng_plan_memory", "ng_set_memory_reuse", "ng_set_launch_fusion", "ng_get_graph_edges", "ng_get_single_launches", "ng_get_offsets",
            "ng_graph_multi_check", "ng_graph_multi_recheck", "ng_graph_multi_distrust", "ng_critical_path", "ng_bind", "ng_capture",
            "ng_tensor_ptr", "ng_replay_mode", "ng_replay", "ng_replay_static", "ng_sync", "ng_resident_config",
            "ng_auto_mode", "ng_resident_dry_plan", "ng_resident_dry_plan_setting", "ng_resident_xcd_mapping", "ng_resident_fusion", "ng_resident_plan_trials", "ng_resident_plan_kept", "ng_resident_sizes", "ng_resident_trace", "ng_time_replay", "ng_time_chain", "ng_time_task",
@@ -64,6 +64,7 @@ _sig = {
     "ng_get_offsets": (_I, [_P, _SZP, _SZP]),
     "ng_set_launch_fusion": (_I, [_P, _I]),
     "ng_get_graph_edges": (_I, [_P, _I, _IP, _IP, _IP, _IP, _I]),
+    "ng_get_single_launches": (_I, [_P, _IP, _IP]),
     "ng_graph_multi_check": (_I, [_P, _IP, _IP]),
     "ng_graph_multi_recheck": (_I, [_P, _I]),
     "ng_graph_multi_distrust": (_I, [_P]),
@@ -215,6 +216,13 @@ def ng_get_offsets(g):
 
 def ng_set_launch_fusion(g, on: bool):
     check(g, lib.ng_set_launch_fusion(g, int(bool(on))))
+
+
+def ng_get_single_launches(g):
+    """(position[n_nodes], number of launches) of the single-stream modes."""
+    pos, n = _ints(ng_num_nodes(g)), C.c_int()
+    check(g, lib.ng_get_single_launches(g, pos, C.byref(n)))
+    return list(pos), n.value
 
 
 def ng_get_graph_edges(g, fuse=True):

@@ -21,7 +21,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnimble_graph.so")
 # object -> (source, extra flags); the resident kernel's three builds compile side by side
-OBJECTS = {s: (s, []) for s in ("ng_graph.cpp", "ng_schedule.cpp", "ng_launch_graph.cpp", "ng_resident_plan.cpp", "ng_tasks.hip", "ng_runtime.hip")}
+OBJECTS = {s: (s, []) for s in ("ng_graph.cpp", "ng_schedule.cpp", "ng_launch_graph.cpp", "ng_resident_plan.cpp", "ng_tasks.hip", "ng_gather.hip", "ng_runtime.hip")}
 OBJECTS.update({f"ng_resident_{n}": ("ng_resident.hip", [f"-DNG_RESIDENT_BUILD={i}"]) for i, n in enumerate(("lean", "full", "train"))})
 
 

@@ -381,6 +381,16 @@ struct PairArgs {
     int na, nb;                // tiles of the first and of the second task
 };
 
+// Several tasks of one kernel in one launch: task i's tiles are the workgroups end[i - 1] .. end[i] - 1; unused places end where the
+// last task does.
+constexpr int kGatherMax = 6;
+template <class A>
+struct GatherArgs {
+    int end[kGatherMax];
+    int pad_[2];
+    A task[kGatherMax];
+};
+
 // Which share of a conv1x1's backward launch (input gradient and weight gradient together) workgroup `tile` takes. From kXcdSplits
 // splits of the weight gradient on, everything that reads the pixels of one split - na workgroups of the input gradient, nb
 // blocks of the weight gradient - runs on one XCD, one after the other (workgroups are dealt out to the 8 XCDs by index):

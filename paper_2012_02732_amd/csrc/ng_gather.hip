@@ -1,0 +1,86 @@
+// Several independent tasks of one kernel in one launch (single-stream replay modes).
+//
+// Nimble (arXiv 2012.02732), Section 4.2, runs independent tasks of a network side by side on several streams. On this GPU a
+// second stream costs a hand-over through the command processor per crossing, more than most of these tasks take; tasks of the
+// same kernel need no second stream: their workgroups go out in one launch, which costs one launch gap and one tail instead
+// of one of each per task. The kernels are those of the tasks themselves (one instantiation per kernel id, so nothing is shared
+// with other kernels' registers); a workgroup finds its task by its index and takes that task's argument block from the kernel
+// arguments with uniform loads. Launches and time of a replay, one task at a time -> gathered: training step of a NAS cell, batch 32
+// 132 -> 63, 1049 -> 822 us, batch 96 2107 -> 1822 us, ten images of 27 x 27 635 -> 405 us; Inception-style network at batch 1
+// 92 -> 56, 719 -> 585 us, six images 103 -> 65, 1148 -> 1039 us. The order this takes is that of plan_single_launches.
+#include "ng_kernels.hip"
+
+namespace ng {
+namespace {
+
+template <int KID>
+__global__ __launch_bounds__(kBlock) void gathered_kernel(GatherArgs<typename KernelOf<KID>::Args> p) {
+    __shared__ __align__(16) float smem[smem_floats(KID)];
+    int which = 0, first = 0;
+#pragma unroll
+    for (int i = 0; i + 1 < kGatherMax; ++i)
+        if ((int)blockIdx.x >= p.end[i]) which = i + 1, first = p.end[i];
+    const typename KernelOf<KID>::Args a = p.task[which];
+    NoWait wait;
+    KernelOf<KID>::template tile<false>(a, (int)blockIdx.x - first, smem, threadIdx.x, true, wait);
+}
+
+// the kernels that a network runs several of side by side
+#define NG_FOR_EACH_GATHERED(X)                                                                                         \
+    X(KID_BN) X(KID_BN_V4) X(KID_ADD) X(KID_ADD_V4) X(KID_CONCAT) X(KID_CONCAT_V4) X(KID_POOL) X(KID_POOL_ROW_S1)       \
+    X(KID_POOL_ROW_S2) X(KID_DW_K3S1) X(KID_DW_K3S2) X(KID_DW_K5S1) X(KID_DW_K5S2) X(KID_DW_LDS)                        \
+    X(KID_PW_D4) X(KID_PW_D8) X(KID_PW_D16) X(KID_PW_64) X(KID_PW_V1) X(KID_PW_V2) X(KID_PW_V3) X(KID_PW_V4)            \
+    X(KID_PW_S1) X(KID_PW_S2) X(KID_PW_S3) X(KID_PW_S4) X(KID_PW_P32) X(KID_PW_P64)                                     \
+    X(KID_C3_M1) X(KID_C3_M2) X(KID_C3_M3) X(KID_C3_M4) X(KID_C3_L32) X(KID_C3_L64)                                     \
+    X(KID_C3_P64) X(KID_C3_P96) X(KID_C3_Q32) X(KID_C3_Q64) X(KID_C3_Q128) X(KID_C3_SK)                                 \
+    X(KID_PW_PX_FWD) X(KID_BN_RAW) X(KID_BN_BACKWARD) X(KID_PAIR_DW) X(KID_PAIR_DW_LDS) X(KID_PAIR_PW16)                \
+    X(KID_PAIR_PW32) X(KID_POOL_DGRAD) X(KID_POOL_DGRAD_LDS) X(KID_SLICE_PAD) X(KID_SMALL_GEMM)
+
+template <int KID>
+void fill(const std::vector<const Task*>& tasks, SingleLaunch& out) {
+    GatherArgs<typename KernelOf<KID>::Args> p{};
+    long total = 0;
+    for (int i = 0; i < kGatherMax; ++i) {
+        const Task* t = i < (int)tasks.size() ? tasks[i] : nullptr;
+        if (t) std::memcpy(&p.task[i], t->args, sizeof p.task[i]), total += t->ntiles;
+        p.end[i] = (int)total;
+    }
+    if (total <= 0 || total >= (1L << 31)) return;
+    out.fn = reinterpret_cast<const void*>(&gathered_kernel<KID>);
+    out.grid = (unsigned)total;
+    out.args.resize(sizeof p);
+    std::memcpy(out.args.data(), &p, sizeof p);
+}
+
+}  // namespace
+
+bool can_gather(int kid) {
+    switch (kid) {
+#define NG_CASE(KID) case KID:
+        NG_FOR_EACH_GATHERED(NG_CASE)
+#undef NG_CASE
+            return true;
+        default: return false;
+    }
+}
+
+// The launch that carries out `tasks`: one task as it is, several of one kernel by that kernel's gathered form.
+void make_gathered_launch(const std::vector<const Task*>& tasks, SingleLaunch& out) {
+    out = SingleLaunch();
+    if (tasks.size() == 1) {
+        const Task& t = *tasks[0];
+        out.fn = t.fn, out.grid = t.grid[0], out.lds_bytes = t.lds_bytes;
+        out.args.assign(t.args, t.args + sizeof t.args);
+        return;
+    }
+    for (const Task* t : tasks)
+        if (t->kid != tasks[0]->kid || !t->fn) return;
+    switch (tasks[0]->kid) {
+#define NG_CASE(KID) case KID: fill<KID>(tasks, out); break;
+        NG_FOR_EACH_GATHERED(NG_CASE)
+#undef NG_CASE
+        default: break;
+    }
+}
+
+}  // namespace ng

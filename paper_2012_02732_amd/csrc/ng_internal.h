@@ -92,6 +92,13 @@ struct ResidentPlan {
     std::vector<double> model_run_us;          // [n_nodes] modelled time from a task's last wait to its last store (0: no workgroups of its own)
 };
 
+// One launch of the single-stream modes: a task's own kernel, or several tasks of one kernel.
+struct SingleLaunch {
+    const void* fn = nullptr;
+    unsigned grid = 0, lds_bytes = 0;
+    std::vector<unsigned char> args;
+};
+
 // What modes 0-3 launch and how the multi-stream HIP graph orders it (ng_launch_graph.cpp).
 struct LaunchGraph {
     std::vector<int> nodes;                    // tasks with a kernel node of their own, in submission order
@@ -129,6 +136,7 @@ struct ng_graph {
     std::vector<ng::Task> launch_tasks;                  // what modes 0-3 launch: the same, except that a batch-norm / ReLU directly behind
                                                          // a convolution is applied by that convolution's kernel and has no launch of its own
     std::vector<ng::Task> single_tasks;                  // what the single-stream modes launch: the same, with the weight updates of all streams in one launch
+    std::vector<ng::SingleLaunch> single_launches;       // ... in the order in which they launch it
     std::vector<int> launch_fused_into;                  // [n_nodes] that convolution (the node itself: a concat with nothing to copy), or -1
     ng::Runtime* rt = nullptr;
     int mode = NG_MODE_AUTO;
@@ -173,6 +181,9 @@ const void* resident_kernel_handle(int build);
 const void* empty_kernel_handle();
 const void* standalone_kernel_handle(int kid, const char** name);
 const void* timed_kernel_handle(int kid);
+// ng_gather.hip: several tasks of one kernel in one launch
+bool can_gather(int kid);
+void make_gathered_launch(const std::vector<const Task*>& tasks, SingleLaunch& out);
 const void* xcd_probe_kernel_handle();
 // ng_launch_graph.cpp
 void decide_launch_fusion(const ng_graph* g, const std::vector<Task>& tasks, bool fuse, bool one_stream, std::vector<int>& fused_into);
@@ -184,6 +195,9 @@ void leave_sum_to_later_launch(Task& wgrad);
 void gradients_left_in_parts(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, std::vector<char>& in_parts);
 void make_sgd_batch_task(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& members, const std::vector<char>& in_parts,
                          std::vector<SgdTile>& table, const SgdTile* table_dev, Task& t);
+int launch_kid(const std::vector<Task>& tasks, const std::vector<int>& fused_into, int v);
+void plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, bool gather,
+                          std::vector<std::vector<int>>& launches);
 void build_launch_graph(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, LaunchGraph& out);
 // ng_resident_plan.cpp: xcds = 0 lets the cost model choose among 1, 2, 4, 8.
 int plan_resident(const ng_graph* g, int n_wg, int xcds, const PlanKnobs& knobs, ResidentPlan& plan);

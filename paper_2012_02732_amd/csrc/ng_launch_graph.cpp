@@ -141,6 +141,108 @@ void gradients_left_in_parts(const ng_graph* g, const std::vector<Task>& tasks, 
     }
 }
 
+// The launches of the single-stream modes, in order, each a list of launched tasks. `gather`: launches of one kernel that do not
+// depend on each other (a cell's depthwise convolutions, the 1 x 1 convolutions at the head of an Inception module, the
+// gradients of both) become one launch, for which the launches are taken in another order than the submission order, one that
+// every dependency allows: among the kernels with a task whose inputs are complete, one that no further task could join by
+// waiting (all its other tasks come after one of these) goes first, with all of its tasks that are ready; if there is none,
+// the kernel with the most ready tasks. On one stream a task waits for everything before it anyway, and a batch-1 task or a
+// CIFAR-sized gradient fills a fraction of the chip for a few microseconds, of which 1.6 us are the launch gap.
+void plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, bool gather,
+                          std::vector<std::vector<int>>& launches) {
+    const int n = (int)g->nodes.size();
+    launches.clear();
+    std::vector<int> index(n, -1), node_of;                     // launched task <-> its place in submission order
+    for (int v : g->sched.order)
+        if (tasks[v].fn && fused_into[v] < 0) index[v] = (int)node_of.size(), node_of.push_back(v);
+    const int m = (int)node_of.size();
+    if (!gather) {
+        for (int v : node_of) launches.emplace_back(1, v);
+        return;
+    }
+    // dependencies between launches: whoever writes (part of) a tensor before whoever reads it
+    std::vector<std::vector<int>> writers(n), next(m);
+    std::vector<int> waiting(m, 0);
+    for (int v : g->sched.order) {
+        if (fused_into[v] == v) {                               // a concat whose inputs are in place: written by their launches
+            for (int p : g->nodes[v].preds) writers[v].insert(writers[v].end(), writers[p].begin(), writers[p].end());
+            std::sort(writers[v].begin(), writers[v].end());
+            writers[v].erase(std::unique(writers[v].begin(), writers[v].end()), writers[v].end());
+        } else if (tasks[v].fn) {
+            writers[v].push_back(index[fused_into[v] >= 0 ? fused_into[v] : v]);
+        }
+    }
+    for (int v = 0; v < n; ++v) {
+        if (!tasks[v].fn || fused_into[v] == v) continue;
+        const int to = writers[v][0];
+        for (int p : g->nodes[v].preds)
+            for (int from : writers[p])
+                if (from != to && std::find(next[from].begin(), next[from].end(), to) == next[from].end()) next[from].push_back(to), ++waiting[to];
+    }
+    // a topological order (a launch that carries two tasks sits at the place of the earlier one, so ascending indices need not be one)
+    std::vector<int> topo, left = waiting;
+    for (int i = 0; i < m; ++i)
+        if (left[i] == 0) topo.push_back(i);
+    for (size_t at = 0; at < topo.size(); ++at)
+        for (int to : next[topo[at]])
+            if (--left[to] == 0) topo.push_back(to);
+    const size_t words = ((size_t)m + 63) / 64;
+    std::vector<uint64_t> after((size_t)m * words, 0);          // bit j of row i: launch j comes after launch i
+    for (size_t at = topo.size(); at-- > 0;) {
+        uint64_t* row = &after[(size_t)topo[at] * words];
+        for (int to : next[topo[at]]) {
+            row[to / 64] |= 1ull << (to % 64);
+            for (size_t w = 0; w < words; ++w) row[w] |= after[(size_t)to * words + w];
+        }
+    }
+    // kernels (their ids), or tasks that always launch alone
+    std::vector<int> kind(m);
+    for (int i = 0; i < m; ++i) {
+        const int kid = launch_kid(tasks, fused_into, node_of[i]);
+        kind[i] = can_gather(kid) ? kid : -1 - i;
+    }
+    std::vector<int> ready;
+    std::vector<char> launched(m, 0);
+    for (int i = 0; i < m; ++i)
+        if (waiting[i] == 0) ready.push_back(i);
+    std::vector<uint64_t> behind(words);
+    while (!ready.empty()) {
+        int best = -1;
+        size_t best_count = 0;
+        bool best_closed = false;
+        for (size_t r = 0; r < ready.size(); ++r) {
+            const int c = kind[ready[r]];
+            bool first = true;                                  // once per kernel, at its earliest ready task
+            for (size_t q = 0; q < r; ++q) first = first && kind[ready[q]] != c;
+            if (!first) continue;
+            size_t count = 0;
+            std::fill(behind.begin(), behind.end(), 0);
+            std::vector<char> here(m, 0);
+            for (int i : ready)
+                if (kind[i] == c) {
+                    ++count, here[i] = 1;
+                    for (size_t w = 0; w < words; ++w) behind[w] |= after[(size_t)i * words + w];
+                }
+            bool closed = true;
+            for (int i = 0; i < m && closed; ++i)
+                closed = kind[i] != c || launched[i] || here[i] || ((behind[i / 64] >> (i % 64)) & 1);
+            if (best < 0 || closed > best_closed || (closed == best_closed && !closed && count > best_count)) best = c, best_count = count, best_closed = closed;
+        }
+        std::vector<int> now, rest;
+        for (int i : ready) (kind[i] == best ? now : rest).push_back(i);
+        ready.swap(rest);
+        for (size_t at = 0; at < now.size(); at += kGatherMax) {
+            launches.emplace_back();
+            for (size_t q = at; q < std::min(now.size(), at + kGatherMax); ++q) launches.back().push_back(node_of[now[q]]);
+        }
+        for (int i : now) launched[i] = 1;
+        for (int i : now)
+            for (int to : next[i])
+                if (--waiting[to] == 0) ready.push_back(to);
+        std::sort(ready.begin(), ready.end());
+    }
+}
+
 // The multi-stream graph: one kernel node per launched task, in submission order; a node
 // depends on the previous task of its stream (FIFO order within a stream) and on the
 // producer of every planned event wait (Lambda). A task without a launch of its own keeps
@@ -236,6 +338,26 @@ extern "C" int ng_get_graph_edges(ng_graph* g, int fuse, int* launched_by, int* 
         }
     if (n_edges) *n_edges = count;
     if (count > max_edges && max_edges > 0) return g->fail(NG_ENOMEM, "ng_get_graph_edges: %d edges, room for %d", count, max_edges);
+    return NG_OK;
+}
+
+extern "C" int ng_get_single_launches(ng_graph* g, int* position, int* n_launches) {
+    if (!g) return NG_EINVAL;
+    if (g->phase < PLANNED) return g->fail(NG_ESTATE, "ng_get_single_launches: call ng_plan_memory first");
+    TaskView view(g);
+    if (view.rc != NG_OK) return view.rc;
+    std::vector<int> fused_into;
+    decide_launch_fusion(g, g->tasks, g->launch_fusion, true, fused_into);
+    std::vector<std::vector<int>> launches;
+    plan_single_launches(g, g->tasks, fused_into, g->launch_fusion && !g->memory_reuse, launches);
+    if (position) {
+        const int n = (int)g->nodes.size();
+        std::vector<int> of(n, -1);
+        for (size_t i = 0; i < launches.size(); ++i)
+            for (int v : launches[i]) of[v] = (int)i;
+        for (int v = 0; v < n; ++v) position[v] = !g->tasks[v].fn ? -1 : fused_into[v] == v ? -2 : of[fused_into[v] >= 0 ? fused_into[v] : v];
+    }
+    if (n_launches) *n_launches = (int)launches.size();
     return NG_OK;
 }
 

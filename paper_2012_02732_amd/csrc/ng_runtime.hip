@@ -77,14 +77,16 @@ int launch(ng_graph* g, const Task& t, hipStream_t s) {
 
 // Issue the whole task table once, in submission order. multi = true: every task on its
 // assigned stream with the planned event records / waits plus fork and join scaffolding;
-// multi = false: everything on the origin stream, no events at all.
+// multi = false: everything on the origin stream, no events at all, in the order of plan_single_launches.
 int issue_all(ng_graph* g, bool multi) {
     Runtime& rt = *g->rt;
     const Schedule& sc = g->sched;
     hipStream_t origin = rt.streams[0];
     if (!multi) {
-        for (int v : sc.order)
-            if (int rc = launch(g, g->single_tasks[v], origin)) return rc;
+        for (const SingleLaunch& l : g->single_launches) {
+            void* args[1] = {const_cast<unsigned char*>(l.args.data())};
+            NG_HIP(hipLaunchKernel(l.fn, dim3(l.grid), dim3(kBlock), args, l.lds_bytes, origin));
+        }
         return NG_OK;
     }
     if (!sc.fork.empty()) {
@@ -685,6 +687,16 @@ int ng_bind(ng_graph* g, void* arena, size_t arena_bytes, void* const* hip_strea
     fuse_launches(g->launch_fused_into, in_parts, g->launch_tasks);
     gradients_left_in_parts(g, g->tasks, single_fused_into, in_parts);
     fuse_launches(single_fused_into, in_parts, g->single_tasks);
+    std::vector<std::vector<int>> launches;
+    plan_single_launches(g, g->tasks, single_fused_into, g->launch_fusion && !g->memory_reuse, launches);
+    g->single_launches.clear();
+    for (const std::vector<int>& members : launches) {
+        std::vector<const Task*> of;
+        for (int v : members) of.push_back(&g->single_tasks[v]);
+        g->single_launches.emplace_back();
+        make_gathered_launch(of, g->single_launches.back());
+        if (!g->single_launches.back().fn) return g->fail(NG_EINVAL, "ng_bind: no kernel for the launch of task %d", members[0]);
+    }
     if (sgd_table.size() > sgd_shares) return g->fail(NG_EINVAL, "ng_bind: %zu shares of weight updates, room for %zu", sgd_table.size(), sgd_shares);
     if (!sgd_table.empty()) NG_HIP(hipMemcpy(rt.sgd_tiles, sgd_table.data(), sgd_table.size() * sizeof(SgdTile), hipMemcpyHostToDevice));
 

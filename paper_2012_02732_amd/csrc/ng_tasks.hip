@@ -227,6 +227,18 @@ static int pair_kid(int kid_first, int kid_second) {
     return KID_NONE;
 }
 bool can_pair(int kid_first, int kid_second) { return pair_kid(kid_first, kid_second) != KID_NONE; }
+// The kernel of the launch of task v with everything that rides on it (`fused_into` as decided).
+int launch_kid(const std::vector<Task>& tasks, const std::vector<int>& fused_into, int v) {
+    for (size_t w = 0; w < tasks.size(); ++w) {
+        if (fused_into[w] != v || (int)w == v) continue;
+        const int a = tasks[v].kid, b = tasks[w].kid;
+        if (b == KID_SGD) return KID_SGD_BATCH;
+        if ((a == KID_BN_DGRAD && b == KID_BN_WGRAD) || (a == KID_BN_WGRAD && b == KID_BN_DGRAD)) return KID_BN_BACKWARD;
+        if (can_pair(a, b)) return pair_kid(a, b);
+        if (can_pair(b, a)) return pair_kid(b, a);
+    }
+    return tasks[v].kid;
+}
 template <int KID>
 static void set_pair(const Task& first, const Task& second, Task& t) {
     typename KernelOf<KID>::Args p{};

@@ -984,3 +984,55 @@ def test_resident_plans_of_concats_partly_in_place():
             far += d["n_far_edges"]
         r.close()
     assert far > 0
+
+
+# ---- the launches of the single-stream modes: order, and tasks of one kernel that share a launch ----
+
+def _single_launch_workloads():
+    for name in workloads.CONFIG_NAMES:
+        yield workloads.make(name)
+    yield workloads.make("random200", seed=12, n_nodes=80, n_layers=12, max_width=10, shape=(1, 16, 14, 14))
+    yield workloads.make("inception_style", batch=6, image=139)
+    for kw in (dict(batch=2), dict(batch=3, c=24, image=27)):
+        fw = workloads.nas_cell_cifar(**kw)
+        yield workloads.training_graph(fw, 0.1, {fw.outputs[0]: np.ones(fw.nodes[fw.outputs[0]].shape, np.float32)})
+
+
+@pytest.mark.parametrize("fusion", [True, False])
+def test_single_stream_launches_follow_every_dependency_and_share_only_one_kernel(fusion):
+    shared = 0
+    for w in _single_launch_workloads():
+        n = len(w.nodes)
+        r = GraphRunner(w)
+        B.ng_set_launch_fusion(r.g, fusion)
+        r.schedule()
+        r.plan()
+        pos, launches = B.ng_get_single_launches(r.g)
+        by, _ = B.ng_get_graph_edges(r.g, 2 if fusion else 0)
+        kernel = [None if nd.op == "input" else B.ng_planned_task_kernel(r.g, v) for v, nd in enumerate(w.nodes)]
+        r.close()
+        assert set(p for p in pos if p >= 0) == set(range(launches))
+        # tasks that ride on another's launch are where it is; nothing else changes who writes what
+        assert all(pos[v] == (pos[by[v]] if by[v] >= 0 else by[v]) for v in range(n))
+
+        def writers(t):
+            if by[t] == -1:
+                return set()
+            return set().union(*[writers(p) for p in w.nodes[t].preds]) if by[t] == -2 else {by[t]}
+
+        # every launch that writes (part of) what a task reads comes before the task's: strictly, unless it is the very same
+        # launched task - two tasks that share a launch never wait for each other
+        for u, v in w.edges:
+            if by[v] >= 0:
+                assert all(k == by[v] or pos[k] < pos[v] for k in writers(u)), (w.name, u, v)
+        groups = {}
+        for v in range(n):
+            if by[v] == v:
+                groups.setdefault(pos[v], []).append(v)
+        for members in groups.values():
+            riders = [sorted(kernel[q] for q in range(n) if by[q] == v and q != v and "px_fwd" not in kernel[v] and
+                             w.nodes[q].op not in ("bn_act", "relu")) for v in members]
+            assert len({tuple(sorted([kernel[v]] + q)) for v, q in zip(members, riders)}) == 1, (w.name, [kernel[v] for v in members])
+            shared += len(members) - 1
+        assert fusion or all(len(m) == 1 for m in groups.values())
+    assert (shared > 100) if fusion else shared == 0
