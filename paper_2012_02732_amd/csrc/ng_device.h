@@ -70,6 +70,7 @@ constexpr bool is_pw16(int kid) { return plain_variant(kid) >= KID_PW_V1 && plai
 constexpr bool is_c3m(int kid) { return plain_variant(kid) >= KID_C3_M1 && plain_variant(kid) <= KID_C3_M4; }
 constexpr bool has_add_epilogue(int kid) { return plain_variant(kid) != kid; }
 constexpr bool is_c3_patch(int kid) { return kid >= KID_C3_P64 && kid <= KID_C3_SK; }
+constexpr bool is_pw_columns(int kid) { return (kid >= KID_PW_V1 && kid <= KID_PW_S4) || kid == KID_PW_P32 || kid == KID_PW_P64; }   // tiles = row tiles x column blocks
 constexpr bool is_pw_patch(int kid) { return kid == KID_PW_P32 || kid == KID_PW_P64; }
 // windowed kernels for large tensors (batches): not in the lean build, but in the full and the train build
 constexpr bool is_large_tensor_kernel(int kid) { return kid == KID_POOL_ROW_S1 || kid == KID_POOL_ROW_S2 || kid == KID_DW_LDS; }
@@ -383,13 +384,24 @@ struct PairArgs {
 
 // Several tasks of one kernel in one launch: task i's tiles are the workgroups end[i - 1] .. end[i] - 1; unused places end where the
 // last task does.
+// Kernels whose tiles are row tiles x column blocks of one matrix (conv1x1): with eights > 0 the column blocks are dealt out to
+// the XCDs, eight at a time (xcd_share), and end[] counts row tiles instead: the row tiles of all tasks, which then read the same
+// columns of one input, share its blocks.
 constexpr int kGatherMax = 6;
 template <class A>
 struct GatherArgs {
     int end[kGatherMax];
-    int pad_[2];
+    int eights;                // groups of eight column blocks, 0: tiles in the tasks' own order
+    int pad_;
     A task[kGatherMax];
 };
+// Which column block and which of `rows` row tiles workgroup w takes when everything that reads a column block runs on one XCD, one
+// after the other (workgroups are dealt out to the 8 XCDs by index): its input then comes from memory once and from that XCD's L2
+// for the other row tiles. Column blocks beyond the last one: none there, nothing to do.
+struct XcdShare { int column, row; };
+constexpr XcdShare xcd_share(int w, int rows) {
+    return XcdShare{8 * ((w >> 3) / rows) + (w & 7), (w >> 3) % rows};
+}
 
 // Which share of a conv1x1's backward launch (input gradient and weight gradient together) workgroup `tile` takes. From kXcdSplits
 // splits of the weight gradient on, everything that reads the pixels of one split - na workgroups of the input gradient, nb

@@ -16,13 +16,25 @@ namespace {
 template <int KID>
 __global__ __launch_bounds__(kBlock) void gathered_kernel(GatherArgs<typename KernelOf<KID>::Args> p) {
     __shared__ __align__(16) float smem[smem_floats(KID)];
+    int place = (int)blockIdx.x, column = -1;
+    if constexpr (is_pw_columns(KID)) {
+        if (p.eights > 0) {
+            const XcdShare s = xcd_share(place, p.end[kGatherMax - 1]);
+            place = s.row, column = s.column;
+        }
+    }
     int which = 0, first = 0;
 #pragma unroll
     for (int i = 0; i + 1 < kGatherMax; ++i)
-        if ((int)blockIdx.x >= p.end[i]) which = i + 1, first = p.end[i];
+        if (place >= p.end[i]) which = i + 1, first = p.end[i];
     const typename KernelOf<KID>::Args a = p.task[which];
+    int tile = place - first;
+    if constexpr (is_pw_columns(KID)) {
+        if (column >= a.tiles_n) return;                        // the whole workgroup
+        if (column >= 0) tile = is_pw_patch(KID) ? column * a.mtiles + tile : tile * a.tiles_n + column;
+    }
     NoWait wait;
-    KernelOf<KID>::template tile<false>(a, (int)blockIdx.x - first, smem, threadIdx.x, true, wait);
+    KernelOf<KID>::template tile<false>(a, tile, smem, threadIdx.x, true, wait);
 }
 
 // the kernels that a network runs several of side by side
@@ -36,15 +48,33 @@ __global__ __launch_bounds__(kBlock) void gathered_kernel(GatherArgs<typename Ke
     X(KID_PW_PX_FWD) X(KID_BN_RAW) X(KID_BN_BACKWARD) X(KID_PAIR_DW) X(KID_PAIR_DW_LDS) X(KID_PAIR_PW16)                \
     X(KID_PAIR_PW32) X(KID_POOL_DGRAD) X(KID_POOL_DGRAD_LDS) X(KID_SLICE_PAD) X(KID_SMALL_GEMM)
 
+// conv1x1 from this many column blocks on: they are dealt out to the XCDs (xcd_share). In the tiles' own order the row tiles of a
+// column block run on up to 8 XCDs and each fetches the block: 387 MB a launch on average for the 1 x 1 convolutions at the heads
+// of the Inception-style modules at batch 32, 70 MB being what they have to read and write. Four layers from 768 channels of
+// 17 x 17 in one launch 94 -> 85 us, three of 288 channels and 35 x 35 60 -> 55; the whole network 3585 -> 3545 us. With fewer
+// column blocks eight of them are too coarse a unit: 19 blocks are three for some XCDs and two for others.
+constexpr int kXcdColumns = 32;
+
 template <int KID>
 void fill(const std::vector<const Task*>& tasks, SingleLaunch& out) {
     GatherArgs<typename KernelOf<KID>::Args> p{};
+    const int n = (int)tasks.size();
+    for (int i = 0; i < n; ++i) std::memcpy(&p.task[i], tasks[i]->args, sizeof p.task[i]);
+    if constexpr (is_pw_columns(KID)) {
+        bool same = true;
+        for (int i = 1; i < n; ++i) same = same && p.task[i].tiles_n == p.task[0].tiles_n;
+        if (same && p.task[0].tiles_n >= kXcdColumns) p.eights = (p.task[0].tiles_n + 7) / 8;
+    }
     long total = 0;
     for (int i = 0; i < kGatherMax; ++i) {
-        const Task* t = i < (int)tasks.size() ? tasks[i] : nullptr;
-        if (t) std::memcpy(&p.task[i], t->args, sizeof p.task[i]), total += t->ntiles;
+        if constexpr (is_pw_columns(KID)) {
+            if (i < n && p.eights > 0) { p.end[i] = (int)(total += p.task[i].mtiles); continue; }
+        }
+        if (i < n) total += tasks[i]->ntiles;
         p.end[i] = (int)total;
     }
+    if (p.eights > 0) total *= 8L * p.eights;
+    else if (n == 1) return;                                    // launched as it is
     if (total <= 0 || total >= (1L << 31)) return;
     out.fn = reinterpret_cast<const void*>(&gathered_kernel<KID>);
     out.grid = (unsigned)total;
@@ -64,17 +94,18 @@ bool can_gather(int kid) {
     }
 }
 
-// The launch that carries out `tasks`: one task as it is, several of one kernel by that kernel's gathered form.
+// The launch that carries out `tasks`: one task as it is (unless its column blocks are dealt out to the XCDs), several of one kernel
+// by that kernel's gathered form.
 void make_gathered_launch(const std::vector<const Task*>& tasks, SingleLaunch& out) {
     out = SingleLaunch();
+    for (const Task* t : tasks)
+        if (t->kid != tasks[0]->kid || !t->fn) return;
     if (tasks.size() == 1) {
         const Task& t = *tasks[0];
         out.fn = t.fn, out.grid = t.grid[0], out.lds_bytes = t.lds_bytes;
         out.args.assign(t.args, t.args + sizeof t.args);
-        return;
+        if (!is_pw_columns(t.kid)) return;
     }
-    for (const Task* t : tasks)
-        if (t->kid != tasks[0]->kid || !t->fn) return;
     switch (tasks[0]->kid) {
 #define NG_CASE(KID) case KID: fill<KID>(tasks, out); break;
         NG_FOR_EACH_GATHERED(NG_CASE)

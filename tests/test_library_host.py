@@ -1036,3 +1036,34 @@ def test_single_stream_launches_follow_every_dependency_and_share_only_one_kerne
             shared += len(members) - 1
         assert fusion or all(len(m) == 1 for m in groups.values())
     assert (shared > 100) if fusion else shared == 0
+
+
+def test_columns_dealt_out_to_the_xcds_cover_every_tile_once(tmp_path):
+    """xcd_share: workgroup w of a conv1x1 launch -> (column block, row tile). Every pair exactly once, all row tiles of a column
+    block on one XCD (equal w mod 8), and one after the other there."""
+    import subprocess
+    src = tmp_path / "share.cpp"
+    src.write_text(r"""
+    #include "ng_device.h"
+    #include <cstdio>
+    #include <vector>
+    int main() {
+        for (int rows = 1; rows <= 40; ++rows)
+            for (int columns : {1, 7, 8, 9, 32, 33, 145, 257}) {
+                std::vector<int> seen(rows * columns, 0), xcd(columns, -1), last(columns, -1);
+                for (int w = 0; w < (columns + 7) / 8 * 8 * rows; ++w) {
+                    const ng::XcdShare s = ng::xcd_share(w, rows);
+                    if (s.row < 0 || s.row >= rows || s.column < 0 || s.column >= (columns + 7) / 8 * 8) return 1;
+                    if (s.column >= columns) continue;
+                    ++seen[s.column * rows + s.row];
+                    if (xcd[s.column] >= 0 && (xcd[s.column] != w % 8 || w - last[s.column] != 8)) return 2;
+                    xcd[s.column] = w % 8, last[s.column] = w;
+                }
+                for (int n : seen) if (n != 1) return 3;
+            }
+        std::puts("ok");
+    }
+    """)
+    exe = str(tmp_path / "share")
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2012_02732_amd", "csrc"), str(src), "-o", exe], check=True)
+    assert subprocess.run([exe], check=True, capture_output=True, text=True).stdout.strip() == "ok"
