@@ -14,7 +14,7 @@ namespace ng {
 namespace {
 
 template <int KID>
-__global__ __launch_bounds__(kBlock) void gathered_kernel(GatherArgs<typename KernelOf<KID>::Args> p) {
+__global__ __launch_bounds__(kBlock, min_waves(KID)) void gathered_kernel(GatherArgs<typename KernelOf<KID>::Args> p) {
     __shared__ __align__(16) float smem[smem_floats(KID)];
     int place = (int)blockIdx.x, column = -1;
     if constexpr (is_pw_columns(KID)) {

@@ -100,13 +100,11 @@ __device__ __forceinline__ float4 ldg4_any_far(const float* p) {
 
 // LDS floats every workgroup owns: the largest user is the conv3x3 input patch of the vector-ALU kernel (4 x 33 x 34).
 constexpr int kSmemFloats = 5120;
-// ... and what the patch-stationary kernels get instead: 24 floats (16 channels in three bf16 parts) for 256 pixels, or for up
-// to 640. Stand-alone kernels: only they; the resident kernel: every workgroup of the build that contains them.
+// ... and what the patch-stationary kernels get instead: 24 floats (16 channels in three bf16 parts) for every pixel of their patches,
+// 640 at most. Stand-alone kernels: only they; the resident kernel: every workgroup of the build that contains them.
 constexpr int kSmemFloatsPatch = 24 * 256, kSmemFloatsWide = 24 * 640;
-constexpr int kSplitKPatch = 160;                       // pixels of each of the four patches of conv3x3_mfma_split_k
-constexpr bool has_wide_patch(int kid) { return kid == KID_C3_Q32 || kid == KID_C3_Q64 || kid == KID_C3_Q128 || kid == KID_C3_SK; }
 constexpr int smem_floats(int kid) {
-    return has_wide_patch(kid) ? kSmemFloatsWide : kid == KID_PW_P32 ? 2 * kSmemFloatsPatch : is_c3_patch(kid) || is_pw_patch(kid) ? kSmemFloatsPatch : kSmemFloats;
+    return is_c3_patch(kid) ? 24 * c3_patches(kid) * c3_patch_pixels(kid) : kid == KID_PW_P32 ? 2 * kSmemFloatsPatch : is_pw_patch(kid) ? kSmemFloatsPatch : kSmemFloats;
 }
 
 // ------------------------------------------------------------------------------------
@@ -738,49 +736,65 @@ __device__ __forceinline__ f32x16 split_sum(const f32x16& high, const f32x16& lo
 
 // ------------------------------------------------------------------------------------
 // conv3x3 for many output pixels (large maps, batches), patch-stationary: Y[Cout x pixels] = W[Cout x 9 Cin] * patches.
-// A tile is TM output channels by a run of TN consecutive output pixels of one image (row-major, so a run may wrap over
-// several rows). K is walked in blocks of 16 input channels, and within a block tap by tap, in split bf16 (above):
-//   * B operand. The input pixels the run needs - its rows plus the halo, (W + 2 pad) wide with the padding stored as
-//     zeros - are kept in LDS for one block of 16 channels, already split: three planes, 32 bytes per pixel and plane. Lane
-//     (r, g) takes channels 8 g .. 8 g + 7 of pixel r with one 128-bit read per part; which half of a pixel's 32 bytes holds
-//     which eight channels alternates every four pixels, so that eight consecutive lanes hit all banks. A tap is an
-//     address shift ((dr (W + 2 pad) + dc) pixels): the nine taps of a block run off ONE patch without a barrier between
-//     them, and each input element is fetched and split once per tile and block instead of once per tap.
+// A tile is TM output channels by a run of TN consecutive output pixels of one strip of an image: columns [x0, x0 + ws), row-major,
+// so a run may wrap over several rows. Narrow images are one strip; wide ones are cut so that a run's patch fits into LDS
+// (choose_strips; 64 pixels of a 147-wide image need 3 x 147 pixels of patch, of a 49-wide strip 197). K is walked in blocks
+// of 16 input channels, and within a block tap by tap, in split bf16 (above):
+//   * B operand. The input pixels the run needs - from its first pixel's upper left neighbour to its last one's lower right, rows of
+//     the strip and its halo, the padding stored as zeros - are kept in LDS for one block of 16 channels, already split: three
+//     planes, 32 bytes per pixel and plane. Lane (r, g) takes channels 8 g .. 8 g + 7 of pixel r with one 128-bit read per part;
+//     which half of a pixel's 32 bytes holds which eight channels alternates every four pixels, so that eight lanes that are read
+//     together hit all banks. A tap is an address shift (dr Wp + dc pixels): the nine taps of a block run off ONE patch without a
+//     barrier between them, and each input element is fetched and split once per tile and block instead of once per tap.
 //   * A operand. The weights were split and repacked at bind time into [block * 9 + tap][CoutP / 32][part][lane][8], so a
-//     fragment is three 128-bit loads of 1 KiB in a row, straight from memory (L2) into registers, three slices ahead.
+//     fragment is three 128-bit loads of 1 KiB in a row, straight from memory (L2) into registers, two or three slices ahead.
 //   * Filling the patch: a thread owns up to 2 PM / 256 (pixel, 8 channels) items; their global offsets are worked out once
 //     per tile (out-of-image and padding positions get an offset beyond the buffer's size, for which a buffer load returns
-//     0), so a fill is eight 32-bit loads with a scalar channel offset and three 128-bit LDS writes per item. The loads of
-//     block b + 1 are issued in the middle of block b's taps.
-// A wavefront owns 32 FM x 32 FN outputs. ROWS = 64: 2 x 2 wavefronts; 32: 1 x 4; 96: 2 x 2 of which the upper two own 64
-// rows and the lower two 32 (which are which alternates from tile to tile, so that the SIMDs of a compute unit, each of
-// which gets the same wavefront of every workgroup, share the work).
-// What bounds it: the vector L1 (weights: 3 KiB per fragment and wavefront), at 35 - 40 % of the matrix rate; with
-// v_mfma_f32_16x16x4_f32 the matrix rate did (0.65 - 0.75 of it). Layers at batch 32, us before and after: 17 x 17 192 -> 192
-// 58 -> 39, 8 x 8 448 -> 384 69 -> 44, 147 x 147 32 -> 64 282 -> 222, 73 x 73 80 -> 192 391 -> 288.
+//     0), so a fill is eight 32-bit loads with a scalar channel offset and three 128-bit LDS writes per item. With two patches
+//     (BUFFERS) the next block's is split and stored between the matrix instructions of this one: one barrier per block.
+// A wavefront owns 32 rows x 64 pixels, so a weight fragment (3 KiB through the vector L1) serves twelve matrix instructions. 64
+// rows x 128 pixels: 2 x 2 wavefronts. 64 x 64 and 32 x 128: two wavefronts side by side and K over two pairs (WK), by taps: of the nine
+// of a block one pair takes five and the other four, in turns. 96 x 64: two wavefronts in each pair, of which one owns the upper 32 rows
+// and the other the lower ones, and each one half of the middle rows.
+// What bounds it: power. While these kernels run the clock goes down to 1.6 - 1.9 GHz (2.4 nominal), matrix cores busy 60 % of the
+// cycles; the register-only loop of the same products reaches 302 - 354 TFLOP/s at 1.8 - 2.1 GHz. Without the bank conflicts at the ends of
+// rows, with half the barriers or three instead of two wavefronts per SIMD it takes the same time. Before, a wavefront owned 32 x 32
+// (96 rows: 64 x 32), and wide images had patches of up to 640 pixels, whole rows. Layers at batch 32, us before and after: 147 x 147 32 -> 64
+// 274 -> 256, 149 x 149 32 -> 32 165 -> 141, 73 x 73 80 -> 192 296 -> 282, 35 x 35 96 -> 96 59.8 -> 53.8, 35 x 35 288 -> 384 stride 2
+// 150 -> 133, 17 x 17 192 -> 192 46.2 -> 44.1, 8 x 8 384 -> 768 73.5 -> 64.7; six images, 63 x 63 80 -> 192 59.8 -> 51.0. Two patches
+// against one: 149 x 149 32 -> 32 147, 17 x 17 192 -> 192 44.3; for 64 x 128 and the wide 64 x 64 one is faster (256 against 280, 133 against 166:
+// the strips that two patches have room for are too narrow).
 // Needs Cin % 16 == 0 and a patch of at most PM pixels.
 // ------------------------------------------------------------------------------------
-template <int ROWS, int FN, int PM, bool FIN, class Wait>
+template <int ROWS, int WN, int WK, int PM, int BUFFERS, bool FIN, class Wait>
 __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, float* smem, int tid, bool live, Wait& wait) {
     const bool fout = wait.far_out();
-    constexpr int NW = ROWS == 32 ? 4 : 2, FM = ROWS == 96 ? 2 : 1, TM = ROWS, TN = 32 * FN * NW, ST = 3;
-    constexpr int ITEMS = 2 * PM / kBlock, PLANE = 2 * PM;          // PLANE: one part of the patch, in units of 16 bytes
+    constexpr int FM = ROWS == 96 ? 2 : 1, UNITS = FM + 1, TM = ROWS, TN = 64 * WN;
+    constexpr int TAPS = WK == 1 ? 9 : 4, ST = WK == 1 ? 3 : 2;     // slices of every block that a wavefront has, and how far ahead it loads weights
+    constexpr int ITEMS = (2 * PM + kBlock - 1) / kBlock, PLANE = 2 * PM;           // PLANE: one part of a patch, in units of 16 bytes
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
-    static_assert(PM * 24 <= (PM > 256 ? kSmemFloatsWide : kSmemFloatsPatch) && PM % 128 == 0 && (ROWS == 32 || ROWS == 64 || ROWS == 96), "LDS budget");
+    static_assert((ROWS == 96 ? 2 : ROWS / 32) * WN * WK == 4 && (WK == 1 || 4 * (8 + 8 * FM) * 64 <= BUFFERS * PM * 24), "four wavefronts; the sums that are handed over fit");
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, g = lane >> 5;
     const int by = tile % a.co_groups, bt = tile / a.co_groups;
-    const int wn = wave % NW, wm = ROWS == 96 ? (wave / NW + bt) & 1 : wave / NW;
+    // the wavefront's share of K, and its blocks of the tile: rows `top` (96 rows: and the middle ones) x pixels n[0] and n[1]
+    const int kg = WK == 2 ? wave >> 1 : 0, wm = ROWS == 64 ? (WK == 2 ? wave & 1 : wave >> 1) : ROWS == 96 ? wave & 1 : 0, wn = WN == 2 ? wave & 1 : 0;
+    const int top = ROWS == 96 ? 2 * wm : wm;
+    const int n[2] = {ROWS == 96 ? wm : 2 * wn, ROWS == 96 ? 1 - wm : 2 * wn + 1};
     const int img = bt / a.tiles_xy, seg = bt - img * a.tiles_xy;
-    const int m0 = by * TM, mw = m0 + wm * 32 * FM;     // this wavefront's first row
     const int HWo = a.Ho * a.Wo, HW = a.H * a.W;
-    const int p0 = seg * TN, npx = min(TN, HWo - p0);
-    const int oy_a = p0 / a.Wo, oy_b = (p0 + npx - 1) / a.Wo;
-    const int iy_a = oy_a * a.stride - a.pad, Wp = a.W + 2 * a.pad, P = ((oy_b - oy_a) * a.stride + 3) * Wp;
+    // the strip of the image (all but the last are tiles_x wide) and the run of its pixels
+    const int per_strip = (a.tiles_x * a.Ho + TN - 1) / TN, strip = seg / per_strip, x0 = strip * a.tiles_x, ws = min(a.tiles_x, a.Wo - x0);
+    const int p0 = (seg - strip * per_strip) * TN, npx = min(TN, ws * a.Ho - p0);
+    const int oy_a = p0 / ws, ox_a = p0 - oy_a * ws, oy_b = (p0 + npx - 1) / ws, ox_b = p0 + npx - 1 - oy_b * ws;
+    // the patch: rows of Wp input pixels, from the first to the last one that the run needs, one after the other
+    const int iy_a = oy_a * a.stride - a.pad, ix_a = x0 * a.stride - a.pad, Wp = (ws - 1) * a.stride + 3;
+    const int skip = ox_a * a.stride, P = ((oy_b - oy_a) * a.stride + 2) * Wp + ox_b * a.stride + 3 - skip;
     const int blocks = a.groups / 16, Mf = a.co_groups * (TM / 32);
     const __amdgpu_buffer_rsrc_t xr =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.x), 0, (a.tiles_n / a.tiles_xy) * a.Cin * HW * 4, 0x00020000);
     const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.wp), 0, 9 * blocks * Mf * kSplitFragBytes, 0x00020000);
+    u32x4* const patches = reinterpret_cast<u32x4*>(smem);           // BUFFERS of them, of the blocks in turn
 
     // this thread's fill items: (pixel of the patch, channels 8 j .. 8 j + 7 of the block)
     unsigned goff[ITEMS];
@@ -789,29 +803,27 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
     for (int t = 0; t < ITEMS; ++t) {
         const int idx = tid + kBlock * t;
         const int j = idx >= P ? 1 : 0, pixel = idx - (idx >= P ? P : 0);
-        const int pr = pixel / Wp, pc = pixel - pr * Wp;
-        const int iy = iy_a + pr, ix = pc - a.pad;
+        const int pr = (pixel + skip) / Wp, pc = pixel + skip - pr * Wp;
+        const int iy = iy_a + pr, ix = ix_a + pc;
         const bool item = live && idx < 2 * P;
         const bool inside = item && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
         goff[t] = inside ? (unsigned)(((img * a.Cin + 8 * j) * HW + iy * a.W + ix) * 4) : kOutside;
         loff[t] = item ? 2 * pixel + (j ^ ((pixel >> 2) & 1)) : -1;     // in units of 16 bytes
     }
     // the patch pixel under tap 0 of this lane's output pixels
-    int base[FN];
+    int base[2];
 #pragma unroll
-    for (int jn = 0; jn < FN; ++jn) {
-        const int px = p0 + min((wn * FN + jn) * 32 + r, npx - 1);
-        const int oy = px / a.Wo, ox = px - oy * a.Wo;
-        base[jn] = (oy - oy_a) * a.stride * Wp + ox * a.stride;
+    for (int jn = 0; jn < 2; ++jn) {
+        const int px = p0 + min(n[jn] * 32 + r, npx - 1);
+        const int oy = px / ws, ox = px - oy * ws;
+        base[jn] = (oy - oy_a) * a.stride * Wp + ox * a.stride - skip;
     }
 
-    f32x16 high[FM][FN], low[FM][FN];
+    f32x16 high[UNITS], low[UNITS];
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int u = 0; u < UNITS; ++u)
 #pragma unroll
-        for (int jn = 0; jn < FN; ++jn)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) high[i][jn][q] = 0.f, low[i][jn][q] = 0.f;
+        for (int q = 0; q < 16; ++q) high[u][q] = 0.f, low[u][q] = 0.f;
 
     float pv[ITEMS][8];
     // Loads are issued unconditionally and in a fixed order (idle items read "outside"): the compiler then counts
@@ -823,86 +835,131 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
             for (int q = 0; q < 8; ++q)
                 pv[t][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xr, goff[t], (unsigned)((block * 16 + q) * HW * 4), kIn));
     };
-    auto fill_store = [&]() {
+    auto fill_store = [&](int block) {
 #pragma unroll
         for (int t = 0; t < ITEMS; ++t) {
             u32x4 part[3];
             split8(pv[t], part);
             if (loff[t] >= 0) {
-                u32x4* s = reinterpret_cast<u32x4*>(smem) + loff[t];
+                u32x4* s = patches + block % BUFFERS * 3 * PLANE + loff[t];
                 s[0] = part[0], s[PLANE] = part[1], s[2 * PLANE] = part[2];
             }
         }
     };
-    u32x4 af[ST][FM][3];
-    auto a_load = [&](int slice, int stage) {
-        const FragmentOffset at = split_fragment(slice, 9 * blocks, mw / 32, Mf);
+    u32x4 af[ST][FM][3], am[FM][3];
+    auto a_load = [&](u32x4 (&to)[3], int i, int block, int tap) {
+        const FragmentOffset at = split_fragment(block * 9 + tap, 9 * blocks, by * (TM / 32) + (i == 0 ? top : 1), Mf);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            if (ROWS == 96 && i == 1 && wm == 1) break;
-#pragma unroll
-            for (int p = 0; p < 3; ++p) af[stage][i][p] = __builtin_amdgcn_raw_buffer_load_b128(wr, at.lane + lane * 16, at.scalar + (unsigned)((i * 3 + p) * 1024), 0);
-        }
+        for (int p = 0; p < 3; ++p) to[p] = __builtin_amdgcn_raw_buffer_load_b128(wr, at.lane + lane * 16, at.scalar + (unsigned)(p * 1024), 0);
     };
-    auto b_load = [&](u32x4 (&bf)[FN][3], int tap) {
-        const int shift = (tap / 3) * Wp + tap % 3;
-#pragma unroll
-        for (int jn = 0; jn < FN; ++jn) {
-            const int pixel = base[jn] + shift;
-            const u32x4* s = reinterpret_cast<const u32x4*>(smem) + 2 * pixel + (g ^ ((pixel >> 2) & 1));
-            bf[jn][0] = s[0], bf[jn][1] = s[PLANE], bf[jn][2] = s[2 * PLANE];
-        }
+    u32x4 bf[2][3];
+    auto b_load = [&](int jn, int block, int tap) {
+        const int pixel = base[jn] + tap / 3 * Wp + tap % 3;
+        const u32x4* s = patches + block % BUFFERS * 3 * PLANE + 2 * pixel + (g ^ ((pixel >> 2) & 1));
+        bf[jn][0] = s[0], bf[jn][1] = s[PLANE], bf[jn][2] = s[2 * PLANE];
     };
+    // One slice: every operand is loaded again, for the next slice that needs its registers, as soon as it has been used.
+    auto slice = [&](u32x4 (&w)[FM][3], int block, int b_tap, bool more, int a_block, int a_tap) {
+        mfma_split(w[0], bf[1], high[1], low[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) b_load(1, block, b_tap);
+        mfma_split(w[0], bf[0], high[0], low[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        a_load(w[0], 0, a_block, a_tap);
+        if constexpr (FM == 2) {
+            mfma_split(w[1], bf[0], high[2], low[2]);
+            __builtin_amdgcn_sched_barrier(0);
+            a_load(w[1], 1, a_block, a_tap);
+        }
+        if (more) b_load(0, block, b_tap);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the first of a wavefront's TAPS taps of a block; the middle tap goes to the share that has the taps before it
+    auto first_tap = [&](int block) { return WK == 2 && ((kg ^ block) & 1) ? 5 : 0; };
 
     wait();
     if (live) {
         fill_load(0);
 #pragma unroll
-        for (int d = 0; d < ST; ++d) a_load(d, d);
-        fill_store();
+        for (int i = 0; i < FM; ++i) {
+#pragma unroll
+            for (int d = 0; d < ST; ++d) a_load(af[d][i], i, 0, first_tap(0) + d);
+            if (WK == 2) a_load(am[i], i, kg, 4);
+        }
+        fill_store(0);
+        if (BUFFERS == 2) fill_load(min(1, blocks - 1));
     }
     __syncthreads();
 #pragma unroll 1                                        // unrolled twice it holds 64 registers more and runs 10 - 15 % slower
     for (int block = 0; block < blocks; ++block) {
         if (live) {
-            u32x4 bf[2][FN][3];
-            b_load(bf[0], 0);
+            const int t0 = first_tap(block), t1 = first_tap(block + 1);
+            const bool middle = WK == 2 && t0 == 0;
+            b_load(1, block, t0);
+            b_load(0, block, t0);
 #pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                if (tap < 8) b_load(bf[(tap + 1) & 1], tap + 1);   // next tap's B fragments, before this tap's matrix instructions
-                if (tap == 3) {
-                    fill_load(min(block + 1, blocks - 1));
+            for (int d = 0; d < TAPS; ++d) {
+                slice(af[d % ST], block, t0 + d + 1, d + 1 < TAPS || middle, d + ST < TAPS ? block : block + 1, d + ST < TAPS ? t0 + d + ST : t1 + d + ST - TAPS);
+                if (d == (BUFFERS == 2 ? 0 : TAPS / 2)) {
+                    if (BUFFERS == 2 && block + 1 < blocks) fill_store(block + 1);   // between the matrix instructions
+                    fill_load(min(block + BUFFERS, blocks - 1));
                     __builtin_amdgcn_sched_barrier(0);  // keep the loads here: the compiler would sink them to their use
                 }
-#pragma unroll
-                for (int i = 0; i < FM; ++i) {
-                    if (ROWS == 96 && i == 1 && wm == 1) break;
-#pragma unroll
-                    for (int jn = 0; jn < FN; ++jn) mfma_split(af[tap % ST][i], bf[tap & 1][jn], high[i][jn], low[i][jn]);
-                }
-                a_load(block * 9 + tap + ST, tap % ST);
-                __builtin_amdgcn_sched_barrier(0);
             }
+            if (middle) slice(am, block, 0, false, block + 2, 4);
         }
-        __syncthreads();                                // every wavefront is done with this block's patch
-        if (live && block + 1 < blocks) fill_store();
-        __syncthreads();
+        __syncthreads();                                // this block's patch has been read (and the next one's is there)
+        if (BUFFERS == 1) {
+            if (live && block + 1 < blocks) fill_store(block + 1);
+            __syncthreads();
+        }
     }
-    if (!live) return;
+    // `count` rows of this lane in a block of 32: m0 + 8 (q / 4) + 4 g + q % 4
+    auto store = [&](const f32x16& sum, int count, int m0, int cl) {
+        if (cl >= npx) return;
+        const int px = p0 + cl, oy = px / ws;
+        const size_t at = (size_t)img * a.Cout * HWo + oy * a.Wo + x0 + px - oy * ws;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-        if (ROWS == 96 && i == 1 && wm == 1) break;
+        for (int q = 0; q < 16; ++q) {
+            const int m = m0 + 8 * (q / 4) + 4 * g + q % 4;
+            if (q < count && m < a.Cout) store_with_epilogue(a.y, a.ep, at + (size_t)m * HWo, m, sum[q], fout);
+        }
+    };
+    const int mw = by * TM + 32 * top;
+    f32x16 sum[UNITS];
 #pragma unroll
-        for (int jn = 0; jn < FN; ++jn) {
-            const int cl = (wn * FN + jn) * 32 + r;
-            if (cl >= npx) continue;
-            const f32x16 sum = split_sum(high[i][jn], low[i][jn]);
+    for (int u = 0; u < UNITS; ++u) sum[u] = split_sum(high[u], low[u]);
+    if constexpr (WK == 1) {
+        if (!live) return;
+        store(sum[0], 16, mw, n[0] * 32 + r);
+        store(sum[1], 16, mw, n[1] * 32 + r);
+    } else {
+        // The two shares of K meet: the wavefronts of the first finish pixels n[0], those of the second n[1] (of the middle rows
+        // one half each); what the other one finishes is handed over in LDS.
+        constexpr int GIVEN = 16 + 8 * (FM - 1);
+        float* const given = smem + (wave * GIVEN) * 64 + lane;
+        const float* const taken = smem + ((wave ^ 2) * GIVEN) * 64 + lane;
+        if (live) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int m = mw + i * 32 + 8 * (q / 4) + 4 * g + q % 4;
-                if (m < a.Cout) store_with_epilogue(a.y, a.ep, ((size_t)img * a.Cout + m) * HWo + p0 + cl, m, sum[q], fout);
+            for (int q = 0; q < 16; ++q) given[q * 64] = kg ? sum[0][q] : sum[1][q];
+            if constexpr (FM == 2) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) given[(16 + q) * 64] = kg ? sum[2][q] : sum[2][8 + q];
             }
         }
+        __syncthreads();
+        if (live) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) sum[0][q] = (kg ? sum[1][q] : sum[0][q]) + taken[q * 64];
+            if constexpr (FM == 2) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) sum[2][q] = (kg ? sum[2][8 + q] : sum[2][q]) + taken[(16 + q) * 64];
+            }
+        }
+        __syncthreads();                                // the next tile's patches go here
+        if (!live) return;
+        store(sum[0], 16, mw, (kg ? n[1] : n[0]) * 32 + r);
+        if constexpr (FM == 2) store(sum[2], 8, by * TM + 32 + 16 * kg, n[0] * 32 + r);
     }
 }
 
@@ -920,7 +977,7 @@ __device__ __forceinline__ void conv3x3_split_k_tile(const C3Args& a, int tile, 
     const bool fout = wait.far_out();
     constexpr int ITEMS = (2 * PM + 63) / 64, PLANE = 2 * PM, ST = 3;    // PLANE: one part of a patch, in units of 16 bytes
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
-    static_assert(4 * PM * 24 <= kSmemFloatsWide && PM * 24 >= 16 * 64, "LDS budget: four patches; a quarter holds a wavefront's sums");
+    static_assert(4 * PM * 24 == smem_floats(KID_C3_SK) && PM * 24 >= 16 * 64, "LDS budget: four patches; a quarter holds a wavefront's sums");
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, g = lane >> 5;
     const int by = tile % a.co_groups, bt = tile / a.co_groups;
@@ -1780,12 +1837,12 @@ NG_KERNEL(KID_C3_L32, C3Args, "conv3x3_lds_32x128", conv3x3_lds_tile < 32, 128, 
 NG_KERNEL(KID_C3_L64, C3Args, "conv3x3_lds_64x64", conv3x3_lds_tile < 64, 64, 32)
 NG_KERNEL(KID_PW_P32, PwArgs, "conv1x1_patch_32x64", conv1x1_patch_tile < 32, 4)
 NG_KERNEL(KID_PW_P64, PwArgs, "conv1x1_patch_64x64", conv1x1_patch_tile < 64, 2)
-NG_KERNEL(KID_C3_P64, C3Args, "conv3x3_patch_64x64", conv3x3_patch_tile < 64, 1, 256)
-NG_KERNEL(KID_C3_P96, C3Args, "conv3x3_patch_96x64", conv3x3_patch_tile < 96, 1, 256)
-NG_KERNEL(KID_C3_Q32, C3Args, "conv3x3_patch_32x128_wide", conv3x3_patch_tile < 32, 1, 640)
-NG_KERNEL(KID_C3_Q64, C3Args, "conv3x3_patch_64x64_wide", conv3x3_patch_tile < 64, 1, 640)
-NG_KERNEL(KID_C3_Q128, C3Args, "conv3x3_patch_64x128_wide", conv3x3_patch_tile < 64, 2, 640)
-NG_KERNEL(KID_C3_SK, C3Args, "conv3x3_mfma_split_k", conv3x3_split_k_tile < kSplitKPatch)
+NG_KERNEL(KID_C3_P64, C3Args, "conv3x3_patch_64x64", conv3x3_patch_tile < 64, 1, 2, c3_patch_pixels(KID_C3_P64), c3_patches(KID_C3_P64))
+NG_KERNEL(KID_C3_P96, C3Args, "conv3x3_patch_96x64", conv3x3_patch_tile < 96, 1, 2, c3_patch_pixels(KID_C3_P96), c3_patches(KID_C3_P96))
+NG_KERNEL(KID_C3_Q32, C3Args, "conv3x3_patch_32x128_wide", conv3x3_patch_tile < 32, 2, 2, c3_patch_pixels(KID_C3_Q32), c3_patches(KID_C3_Q32))
+NG_KERNEL(KID_C3_Q64, C3Args, "conv3x3_patch_64x64_wide", conv3x3_patch_tile < 64, 1, 2, c3_patch_pixels(KID_C3_Q64), c3_patches(KID_C3_Q64))
+NG_KERNEL(KID_C3_Q128, C3Args, "conv3x3_patch_64x128_wide", conv3x3_patch_tile < 64, 2, 1, c3_patch_pixels(KID_C3_Q128), c3_patches(KID_C3_Q128))
+NG_KERNEL(KID_C3_SK, C3Args, "conv3x3_mfma_split_k", conv3x3_split_k_tile < c3_patch_pixels(KID_C3_SK))
 NG_KERNEL(KID_GEMM_PW_FWD, GemmArgs, "gemm_conv1x1_fwd", gemm_tile < GEMM_PW_FWD)
 NG_KERNEL(KID_GEMM_PW_DGRAD, GemmArgs, "gemm_conv1x1_dgrad", gemm_tile < GEMM_PW_DGRAD)
 NG_KERNEL(KID_GEMM_PW_WGRAD, GemmArgs, "gemm_conv1x1_wgrad", gemm_tile < GEMM_PW_WGRAD)

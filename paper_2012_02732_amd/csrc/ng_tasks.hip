@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kBlock) void pack_pw_weights_k4_kernel(const float*
 }
 // Stand-alone kernel of one tile function: one workgroup per tile.
 template <int KID>
-__global__ __launch_bounds__(kBlock) void standalone_kernel(typename KernelOf<KID>::Args a) {
+__global__ __launch_bounds__(kBlock, min_waves(KID)) void standalone_kernel(typename KernelOf<KID>::Args a) {
     __shared__ __align__(16) float smem[smem_floats(KID)];
     NoWait wait;
     KernelOf<KID>::template tile<false>(a, blockIdx.x, smem, threadIdx.x, true, wait);
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(kBlock) void standalone_kernel(typename KernelOf<KI
 // latest end minus the earliest start is the time the GPU is busy with the task when it runs alone,
 // without what the command processor spends around a dispatch.
 template <int KID>
-__global__ __launch_bounds__(kBlock) void timed_kernel(typename KernelOf<KID>::Args a, unsigned long long* stamps) {
+__global__ __launch_bounds__(kBlock, min_waves(KID)) void timed_kernel(typename KernelOf<KID>::Args a, unsigned long long* stamps) {
     __shared__ __align__(16) float smem[smem_floats(KID)];
     unsigned long long t0 = 0;
     if (threadIdx.x == 0) t0 = wall_clock64();
@@ -396,16 +396,41 @@ PwChoice choose_pw(const ng_graph* g, int v) {
 }
 // conv3x3 with at least 8 input channels runs as an implicit GEMM with K = 9 Cin
 constexpr long kC3LdsMinCols = 2048;      // measured: below this the 16 x 16 tiles (more workgroups, shorter K loops each) win
-// The patch-stationary kernels: rows and pixels of a tile, pixels the patch may have.
+// The patch-stationary kernels: rows and pixels of a tile; pm: what a run's rows of whole width may need (it decides between the
+// kernels for narrow and for wide images).
 struct PatchKernel { int kid, tm, tn, pm; };
 constexpr PatchKernel kPatchKernels[] = {{KID_C3_P64, 64, 64, 256}, {KID_C3_P96, 96, 64, 256}, {KID_C3_Q32, 32, 128, 640},
                                          {KID_C3_Q64, 64, 64, 640}, {KID_C3_Q128, 64, 128, 640},
-                                         {KID_C3_SK, 32, 32, kSplitKPatch}};
+                                         {KID_C3_SK, 32, 32, c3_patch_pixels(KID_C3_SK)}};
 // Largest patch a run of tn consecutive output pixels can need: the rows it touches (a run can start at the end of a
 // row), stride apart, plus two, each W + 2 pad wide.
 long patch_pixels(long tn, long W, long Ho, long Wo, long stride, long pad) {
     const long rows = std::min(Ho, (tn - 2) / Wo + 2);
     return ((rows - 1) * stride + 3) * (W + 2 * pad);
+}
+// The strips that an image is cut into, so that the patch of every run of tn pixels of a strip fits into the kernel's LDS: the width
+// of all but the last (0: none fits) and the runs of an image. As few runs as possible, then as few strips.
+struct Strips { long width, runs; };
+long largest_patch(long tn, long width, long Ho, long stride) {              // as the kernel counts it, over the runs of one strip
+    long most = 0;
+    const long row = (width - 1) * stride + 3;
+    for (long p = 0; p < width * Ho; p += tn) {
+        const long last = std::min(p + tn, width * Ho) - 1;
+        most = std::max(most, ((last / width - p / width) * stride + 2) * row + last % width * stride + 3 - p % width * stride);
+    }
+    return most;
+}
+Strips choose_strips(int kid, long tn, long Ho, long Wo, long stride) {
+    auto fits = [&](long width) { return largest_patch(tn, width, Ho, stride) <= c3_patch_pixels(kid); };
+    Strips best{0, 0};
+    for (long n = 1; n <= Wo; ++n) {
+        const long width = ceil_div(Wo, n), rest = Wo - (ceil_div(Wo, width) - 1) * width;
+        if (n > 1 && ceil_div(Wo, width) != n) continue;                      // the same width as with fewer strips
+        if (!fits(width) || !fits(rest)) continue;
+        const long runs = (n - 1) * ceil_div(width * Ho, tn) + ceil_div(rest * Ho, tn);
+        if (best.width == 0 || runs * 33 < best.runs * 32) best = Strips{width, runs};
+    }
+    return best;
 }
 // whole blocks of 16 channels; activations and packed weights (three 16-bit parts) within the reach of a buffer descriptor
 bool patch_reaches(const Shape& in, const Shape& out) {
@@ -418,9 +443,11 @@ int choose_patch_kernel(const Shape& in, const Shape& out, long stride, long pad
     if (!patch_reaches(in, out)) return KID_NONE;
     int best = KID_NONE;
     double best_cost = 0;
+    // the 32-row kernel is for 32 output channels and fewer; those take the others only where its runs of 128 pixels have no patch that fits
+    const bool rows32 = out.c <= 32 && choose_strips(KID_C3_Q32, 128, out.h, out.w, stride).width > 0;
     for (const PatchKernel& k : kPatchKernels) {
         if (k.kid == KID_C3_SK || patch_pixels(k.tn, in.w, out.h, out.w, stride, pad) > k.pm) continue;
-        if ((k.tm == 32) != (out.c <= 32)) continue;                      // the 32-row kernel is for 32 output channels and fewer
+        if ((k.tm == 32) != rows32 || choose_strips(k.kid, k.tn, out.h, out.w, stride).width == 0) continue;
         const long tiles = out.n * ceil_div(out.h * out.w, k.tn) * ceil_div(out.c, k.tm);
         const long rounds = ceil_div(tiles, 256);
         double cost = (double)rounds * k.tm * (k.tn / 64) * (rounds == 1 ? 1.15 : 1.0) * (k.pm > 256 ? 1.08 : 1.0);
@@ -450,7 +477,7 @@ PwChoice choose_c3(const ng_graph* g, int v) {
     if (!knob("NG_NO_PATCH_KERNELS")) {
         const long tiles64 = nd.out.n * ceil_div(nd.out.h * nd.out.w, 64) * ceil_div(nd.out.c, 64);
         int kid = choose_patch_kernel(in, nd.out, nd.p.stride, nd.p.pad);
-        if (patch_reaches(in, nd.out) && cin >= 64 && tiles64 <= 170 && patch_pixels(32, in.w, nd.out.h, nd.out.w, nd.p.stride, nd.p.pad) <= kSplitKPatch)
+        if (patch_reaches(in, nd.out) && cin >= 64 && tiles64 <= 170 && patch_pixels(32, in.w, nd.out.h, nd.out.w, nd.p.stride, nd.p.pad) <= c3_patch_pixels(KID_C3_SK))
             kid = KID_C3_SK;
         else if (nd.out.n * nd.out.h * nd.out.w < kC3LdsMinCols && (cin < 64 || tiles64 < 96))
             kid = KID_NONE;
@@ -861,7 +888,9 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
                 a.cols = (int)(o.n * o.h * o.w);
                 for (const PatchKernel& k : kPatchKernels) {
                     if (k.kid != c.kid) continue;
-                    a.tiles_xy = (int)ceil_div(o.h * o.w, k.tn);          // runs of pixels per image
+                    // runs of pixels per image; conv3x3_mfma_split_k takes rows of whole width
+                    const Strips strips = k.kid == KID_C3_SK ? Strips{o.w, ceil_div(o.h * o.w, k.tn)} : choose_strips(k.kid, k.tn, o.h, o.w, nd.p.stride);
+                    a.tiles_x = (int)strips.width, a.tiles_xy = (int)strips.runs;
                     a.tiles_n = (int)o.n * a.tiles_xy;
                     a.co_groups = (int)ceil_div(a.Cout, k.tm);
                 }

@@ -197,6 +197,28 @@ def test_concat_partly_in_place(nested):
     check_all_nodes(single_op(build), (B.NG_MODE_DEVICE_RESIDENT, B.NG_MODE_AUTO, B.NG_MODE_GRAPH_MULTI))
 
 
+# Strips and shares of K of the patch-stationary conv3x3 kernels. Wide images are cut into strips of columns, the last one narrower
+# (one column of it at 129); a run of pixels starts and ends anywhere in a row, runs of a strip's end are short. K by taps over two
+# pairs of wavefronts: one, two, three and five blocks of 16 channels.
+@pytest.mark.parametrize("shape,cout,stride,pad,kernel", [
+    ((2, 16, 40, 129), 96, 1, 1, "conv3x3_patch_64x64_wide"),
+    ((12, 48, 33, 71), 64, 2, 1, "conv3x3_patch_64x64_wide"),
+    ((6, 80, 35, 61), 70, 2, 0, "conv3x3_patch_64x64_wide"),
+    ((2, 32, 60, 101), 32, 1, 0, "conv3x3_patch_32x128_wide"),
+    ((7, 48, 40, 131), 5, 1, 1, "conv3x3_patch_32x128_wide"),
+    ((4, 48, 149, 147), 64, 1, 1, "conv3x3_patch_64x128_wide"),
+    ((32, 48, 35, 36), 96, 1, 1, "conv3x3_patch_96x64")])
+def test_conv3x3_patch_kernels_on_strips(shape, cout, stride, pad, kernel):
+    w = single_op(lambda b: b.conv3x3(b.input(*shape), cout, stride, pad))
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        assert B.ng_task_kernel(r.g, 1) == kernel
+    finally:
+        r.close()
+    check_all_nodes(w, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT))
+
+
 # The patch-stationary convolutions multiply in three bf16 parts per value. Against 64 bits, ragged in every direction: their
 # large accumulator is rounded once per 16 products, and partial sums grow to the result, so the 2-norm of the error is at most
 # about 2^-24 sqrt(K / 16) of the result's; one more 2^-24 for the stored value.
