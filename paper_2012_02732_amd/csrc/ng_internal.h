@@ -188,7 +188,7 @@ const void* xcd_probe_kernel_handle();
 // ng_launch_graph.cpp
 void decide_launch_fusion(const ng_graph* g, const std::vector<Task>& tasks, bool fuse, bool one_stream, std::vector<int>& fused_into);
 void make_bn_backward_task(const Task& dgrad, const Task& wgrad, Task& t);
-bool can_pair(int kid_first, int kid_second);
+bool can_pair(const Task& first, const Task& second);
 void make_pair_task(const Task& first, const Task& second, Task& t);
 SgdTile gradient_parts(const Task& wgrad);
 void leave_sum_to_later_launch(Task& wgrad);

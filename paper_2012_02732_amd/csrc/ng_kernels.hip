@@ -1705,53 +1705,111 @@ __device__ __forceinline__ void pool3x3_col_tile(const PoolArgs& a, int tile, fl
 }
 
 // ------------------------------------------------------------------------------------
+// floor(e / d) for 0 <= e < 2^20 and 1 <= d, with rcp = 1 / d up to one unit in the last place: (e + 0.5) / d is at least 0.5 / d
+// away from an integer, the rounding errors of the reciprocal and the product are below e 2^-22 / d.
+__device__ __forceinline__ int small_div(int e, float rcp) { return (int)(((float)e + 0.5f) * rcp); }
+__device__ __forceinline__ float small_rcp(int d) { return __builtin_amdgcn_rcpf((float)d); }
+
+// Whole planes in LDS for the depthwise kernels, forward and backward: quads of four columns, every row with four zeros before it
+// (and so, with those of the next row, after it) and K / 2 rows of zeros above and below. A thread's quad of outputs starts at a
+// multiple of four columns, so everything it reads is a few aligned 128-bit reads per row - lanes side by side read 16 bytes side
+// by side - where single values four columns apart hit every fourth bank. Reads go up to 12 floats beyond the last plane (kPlaneSlack).
+constexpr int kPlaneSlack = 16;
+__host__ __device__ constexpr int plane_pitch(int W) { return ((W + 3) >> 2) * 4 + 4; }
+__host__ __device__ constexpr int plane_floats(int H, int W, int K) { return (H + 2 * (K / 2)) * plane_pitch(W); }
+__host__ __device__ constexpr int planes_in_lds(int H, int W, int K) {            // planes of at most 256 quads that a workgroup takes at a time
+    const int quads = H * ((W + 3) >> 2), by_quads = quads > 0 && quads <= kBlock ? kBlock / quads : 0, by_floats = (kSmemFloats - kPlaneSlack) / plane_floats(H, W, K);
+    return by_quads < by_floats ? by_quads : by_floats;
+}
+__device__ __forceinline__ void clear_planes(float* xs, int floats, int tid) {   // floats: a multiple of four
+    for (int i = 4 * tid; i < floats + kPlaneSlack; i += 4 * kBlock) *reinterpret_cast<float4*>(xs + i) = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+// four values of row y from column x on (in a row that is no multiple of four columns the last quad starts four before its end)
+__device__ __forceinline__ void store_quad(float* plane, int pitch, int K, int y, int x, float4 v) {
+    float* dst = plane + (y + K / 2) * pitch + 4 + x;
+    if ((x & 3) == 0) {
+        *reinterpret_cast<float4*>(dst) = v;
+    } else {
+        dst[0] = v.x, dst[1] = v.y, dst[2] = v.z, dst[3] = v.w;
+    }
+}
+// What four outputs of a K x K filter with stride S have above them in one row; v[i] is column 4 - K / 2 + i of `src`. Three columns
+// and a stride of 1: the quad itself and one value on either side, otherwise whole quads.
+template <int K, int S>
+__device__ __forceinline__ void load_row(const float* src, float (&v)[3 * S + K]) {
+    if constexpr (K == 3 && S == 1) {
+        const float4 f = *reinterpret_cast<const float4*>(src + 4);
+        v[0] = src[3], v[1] = f.x, v[2] = f.y, v[3] = f.z, v[4] = f.w, v[5] = src[8];
+    } else {
+        constexpr int FIRST = 4 - K / 2, N = (FIRST + 3 * S + K + 3) / 4;
+        float q[4 * N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float4 f = *reinterpret_cast<const float4*>(src + 4 * i);
+            q[4 * i] = f.x, q[4 * i + 1] = f.y, q[4 * i + 2] = f.z, q[4 * i + 3] = f.w;
+        }
+#pragma unroll
+        for (int i = 0; i < 3 * S + K; ++i) v[i] = q[FIRST + i];
+    }
+}
+// the filter of plane p0 + g
+template <int KK>
+__device__ __forceinline__ void load_filter(const float* w, int p0, int g, int C, float (&f)[KK]) {
+    const int c = p0 % C + g;                                   // p0: of the whole workgroup
+    const float* wt = w + (c < C ? c : c % C) * KK;
+#pragma unroll
+    for (int q = 0; q < KK; ++q) f[q] = wt[q];
+}
+
 // dwconv for large tensors of small planes (batches of CIFAR-sized maps): a workgroup takes as many whole
 // (image, channel) planes as fit 256 quads of input pixels, stages them in LDS with a border of zeros (one 128-bit load per
-// thread; the taps then need no bounds and no index arithmetic beyond a row pitch) and every thread computes four
-// outputs side by side from K rows of 3 S + K values, stored with one 128-bit store. A quad is four pixels of a row; in a
-// row that is no multiple of four the last quad starts four pixels before the end, and the values it shares with the quad
-// before it are loaded, computed and stored twice.
+// thread; the taps then need no bounds) and every thread computes four outputs side by side, stored with one 128-bit store.
+// In a row that is no multiple of four the last quad of the input starts four pixels before the end, and the last quad of the
+// output is stored value by value. Vector instructions bound it: with single LDS values (bank conflicts in 2 of 3 LDS cycles), the border
+// cleared value by value and divisions by the plane's sizes 5 x 5 on 96 images of 44 channels of 32 x 32 took 14.9 us, with quads 10.8
+// (3.2 TB/s); 3 x 3 9.1 and 9.7, on 88 channels of 16 x 16 6.7 and 6.2.
 // ------------------------------------------------------------------------------------
 template <int K, int S, bool FIN, class Wait>
 __device__ __forceinline__ void dwconv_lds_impl(const DwArgs& a, int tile, float* smem, int tid, bool live, Wait& wait) {
-    constexpr int p = K / 2, SPAN = 3 * S + K;
+    constexpr int SPAN = 3 * S + K;
     const bool fout = wait.far_out();
     const int HW = a.H * a.W, HWo = a.Ho * a.Wo;
-    const int PW = a.W + 2 * p, PHW = (a.H + 2 * p) * PW;
+    const int pitch = plane_pitch(a.W), plane = plane_floats(a.H, a.W, K);
     const int G = a.planes_per_tile;
     const int p0 = tile * G, np = live ? min(G, a.total / HWo - p0) : 0;
     const int QW = (a.W + 3) >> 2, QWo = (a.Wo + 3) >> 2;
-    const int gi = tid / (a.H * QW), xrem = tid - gi * (a.H * QW), iy = xrem / QW, ix = min(4 * (xrem - iy * QW), a.W - 4);
-    const int go = tid / (a.Ho * QWo), orem = tid - go * (a.Ho * QWo), oy = orem / QWo, ox = min(4 * (orem - oy * QWo), a.Wo - 4);
+    const int gi = small_div(tid, small_rcp(a.H * QW)), xrem = tid - gi * (a.H * QW), iy = small_div(xrem, small_rcp(QW)), ix = min(4 * (xrem - iy * QW), a.W - 4);
+    const int go = small_div(tid, small_rcp(a.Ho * QWo)), orem = tid - go * (a.Ho * QWo), oy = small_div(orem, small_rcp(QWo)), ox = 4 * (orem - oy * QWo);
     const bool xin = gi < np, oin = go < np;
     float w[K * K];
-    const float* wt = a.w + ((p0 + min(go, max(np - 1, 0))) % a.C) * (K * K);
-#pragma unroll
-    for (int q = 0; q < K * K; ++q) w[q] = wt[q];              // filter taps: not produced by any task
+    load_filter(a.w, p0, min(go, max(np - 1, 0)), a.C, w);   // filter taps: not produced by any task
     wait();
     const float4 x4 = xin ? ldg4_any(a.x, a.x + (size_t)(p0 + gi) * HW + iy * a.W + ix, FIN) : make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();                                            // a previous tile of this workgroup has been read to the end
-    for (int i = tid; i < G * PHW; i += kBlock) smem[i] = 0.f;
+    clear_planes(smem, G * plane, tid);
     __syncthreads();
-    if (xin) {
-        float* dst = smem + gi * PHW + (iy + p) * PW + ix + p;
-        dst[0] = x4.x, dst[1] = x4.y, dst[2] = x4.z, dst[3] = x4.w;
-    }
+    if (xin) store_quad(smem + gi * plane, pitch, K, iy, ix, x4);
     __syncthreads();
     if (!oin) return;
-    const float* src = smem + go * PHW + oy * S * PW + ox * S;  // tap (0, 0) of the first of the four outputs
+    const float* src = smem + go * plane + oy * S * pitch + ox * S;   // row of tap row 0, four columns before the first output's
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int da = 0; da < K; ++da) {
         float v[SPAN];
-#pragma unroll
-        for (int s = 0; s < SPAN; ++s) v[s] = src[da * PW + s];
+        load_row<K, S>(src + da * pitch, v);
 #pragma unroll
         for (int db = 0; db < K; ++db)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[j] = fmaf(w[da * K + db], v[j * S + db], acc[j]);   // taps in ascending order, as dwconv_tile
     }
-    stg4_any(a.y, a.y + (size_t)(p0 + go) * HWo + oy * a.Wo + ox, make_float4(acc[0], acc[1], acc[2], acc[3]), fout);
+    float* out = a.y + (size_t)(p0 + go) * HWo + oy * a.Wo + ox;
+    if (ox + 4 <= a.Wo) {
+        stg4_any(a.y, out, make_float4(acc[0], acc[1], acc[2], acc[3]), fout);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if (ox + j < a.Wo) stg(a.y, out + j, acc[j], fout);
+    }
 }
 template <bool FIN, class Wait>
 __device__ __forceinline__ void dwconv_lds_tile(const DwArgs& a, int tile, float* smem, int tid, bool live, Wait& wait) {
@@ -1893,6 +1951,7 @@ __device__ __forceinline__ void pair_tile(const PairArgs<typename KernelOf<KA>::
     const bool first = tile < 2 * fewer ? (tile & 1) == 0 : p.na > p.nb;
     const int t = tile < 2 * fewer ? tile >> 1 : tile - fewer;
     if (first) KernelOf<KA>::template tile<FIN>(p.a, t, smem, tid, live, wait);
+    else if constexpr (KA == KID_DW_DGRAD_LDS) dw_wgrad_impl<true, FIN>(p.b, t, smem, tid, live, wait);
     else KernelOf<KB>::template tile<FIN>(p.b, t, smem, tid, live, wait);
 }
 using PairDwArgs = PairArgs<DwGradArgs, DwGradArgs>;

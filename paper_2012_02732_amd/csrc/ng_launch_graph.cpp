@@ -83,7 +83,7 @@ void decide_launch_fusion(const ng_graph* g, const std::vector<Task>& tasks, boo
         for (int w = 0; w < n; ++w) {
             const Node& nw = g->nodes[w];
             if (nw.op != (nd.op == NG_OP_DWCONV_DGRAD ? NG_OP_DWCONV_WGRAD : NG_OP_CONV1X1_WGRAD) || !tasks[w].fn || fused_into[w] >= 0 ||
-                nw.preds.empty() || nd.preds.empty() || nw.preds[0] != nd.preds[0] || !can_pair(tasks[d].kid, tasks[w].kid))
+                nw.preds.empty() || nd.preds.empty() || nw.preds[0] != nd.preds[0] || !can_pair(tasks[d], tasks[w]))
                 continue;
             if (!one_stream && sc.stream_of[w] != sc.stream_of[d]) continue;
             const int early = pos[d] < pos[w] ? d : w, late = early == d ? w : d;

@@ -659,9 +659,9 @@ int ng_bind(ng_graph* g, void* arena, size_t arena_bytes, void* const* hip_strea
                 make_bn_backward_task(tasks[v], tasks[u], out[u]);
             } else if (tasks[v].kid == KID_BN_WGRAD && tasks[u].kid == KID_BN_DGRAD) {
                 make_bn_backward_task(tasks[u], tasks[v], out[u]);
-            } else if (can_pair(tasks[u].kid, tasks[v].kid)) {
+            } else if (can_pair(tasks[u], tasks[v])) {
                 make_pair_task(tasks[u], tasks[v], out[u]);
-            } else if (can_pair(tasks[v].kid, tasks[u].kid)) {
+            } else if (can_pair(tasks[v], tasks[u])) {
                 make_pair_task(tasks[v], tasks[u], out[u]);
             } else if (tasks[v].kid == KID_BN_RAW && tasks[u].kid == KID_PW_PX_FWD) {
                 const BnRawArgs* bn = reinterpret_cast<const BnRawArgs*>(tasks[v].args);

@@ -219,14 +219,16 @@ void make_sgd_batch_task(const ng_graph* g, const std::vector<Task>& tasks, cons
 }
 
 // Which two stand-alone kernels have a launch of their own together (pair_tile): input gradient first, weight gradient second.
-static int pair_kid(int kid_first, int kid_second) {
+static int pair_kid(const Task& first, const Task& second) {
+    const int kid_first = first.kid, kid_second = second.kid;
     if (kid_first == KID_DW_DGRAD && kid_second == KID_DW_WGRAD) return KID_PAIR_DW;
-    if (kid_first == KID_DW_DGRAD_LDS && kid_second == KID_DW_WGRAD) return KID_PAIR_DW_LDS;
+    if (kid_first == KID_DW_DGRAD_LDS && kid_second == KID_DW_WGRAD)
+        return dw_wgrad_by_quads(*reinterpret_cast<const DwGradArgs*>(second.args)) ? KID_PAIR_DW_LDS : KID_NONE;
     if (kid_first == KID_PW_PX_DGRAD && kid_second == KID_PW_WGRAD_PX) return KID_PAIR_PW16;
     if (kid_first == KID_PW_PX_DGRAD && kid_second == KID_PW_WGRAD_PX2) return KID_PAIR_PW32;
     return KID_NONE;
 }
-bool can_pair(int kid_first, int kid_second) { return pair_kid(kid_first, kid_second) != KID_NONE; }
+bool can_pair(const Task& first, const Task& second) { return pair_kid(first, second) != KID_NONE; }
 // The kernel of the launch of task v with everything that rides on it (`fused_into` as decided).
 int launch_kid(const std::vector<Task>& tasks, const std::vector<int>& fused_into, int v) {
     for (size_t w = 0; w < tasks.size(); ++w) {
@@ -234,8 +236,8 @@ int launch_kid(const std::vector<Task>& tasks, const std::vector<int>& fused_int
         const int a = tasks[v].kid, b = tasks[w].kid;
         if (b == KID_SGD) return KID_SGD_BATCH;
         if ((a == KID_BN_DGRAD && b == KID_BN_WGRAD) || (a == KID_BN_WGRAD && b == KID_BN_DGRAD)) return KID_BN_BACKWARD;
-        if (can_pair(a, b)) return pair_kid(a, b);
-        if (can_pair(b, a)) return pair_kid(b, a);
+        if (can_pair(tasks[v], tasks[w])) return pair_kid(tasks[v], tasks[w]);
+        if (can_pair(tasks[w], tasks[v])) return pair_kid(tasks[w], tasks[v]);
     }
     return tasks[v].kid;
 }
@@ -262,7 +264,7 @@ static void set_pw_backward(const Task& dgrad, const Task& wgrad, Task& t) {
     set_kernel<KID>(t, p, pw_backward_tiles(p.na, p.nb, p.b.splits));
 }
 void make_pair_task(const Task& first, const Task& second, Task& t) {
-    switch (pair_kid(first.kid, second.kid)) {
+    switch (pair_kid(first, second)) {
         case KID_PAIR_DW: set_pair<KID_PAIR_DW>(first, second, t); break;
         case KID_PAIR_DW_LDS: set_pair<KID_PAIR_DW_LDS>(first, second, t); break;
         case KID_PAIR_PW16: set_pw_backward<KID_PAIR_PW16>(first, second, t); break;
@@ -776,10 +778,9 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
             DwArgs a{buf(nd.preds[0]), wf(0), buf(v), (int)o.c, (int)i0.h, (int)i0.w, (int)o.h, (int)o.w, total};
             const long n = ceil_div(total, kBlock);
             // large tensors of small planes (batches): whole planes through LDS, four outputs per thread
-            const long quads = i0.h * ceil_div(i0.w, 4), per_wg = quads <= kBlock ? kBlock / quads : 0;
-            const int bd = nd.p.k / 2;
+            const long quads = i0.h * ceil_div(i0.w, 4), per_wg = planes_in_lds((int)i0.h, (int)i0.w, nd.p.k);
             if (total >= kDwLdsMinOutputs && (nd.p.k == 3 || nd.p.k == 5) && (nd.p.stride == 1 || nd.p.stride == 2) && i0.w >= 4 &&
-                o.w >= 4 && per_wg > 0 && o.h * ceil_div(o.w, 4) <= quads && per_wg * (i0.h + 2 * bd) * (i0.w + 2 * bd) <= kSmemFloats) {
+                o.w >= 4 && per_wg > 0 && o.h * ceil_div(o.w, 4) <= quads) {
                 a.K = nd.p.k, a.S = nd.p.stride, a.planes_per_tile = (int)per_wg;
                 set_kernel<KID_DW_LDS>(t, a, ceil_div((long)o.n * o.c, per_wg));
                 break;
@@ -1054,12 +1055,12 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
             if (nd.op == NG_OP_DWCONV_DGRAD) {
                 a.w = wf(0);
                 const long plane = (long)a.H * a.W, planes = a.total / plane;
-                const int bd = a.K / 2;
-                const long quads = a.H * ceil_div(a.W, 4), per_wg = quads <= kBlock ? kBlock / quads : 0;
-                const bool whole = a.W % 4 == 0 && a.Wo % 4 == 0;  // ragged rows: LDS is read up to three floats beyond the last row
+                const long quads = a.H * ceil_div(a.W, 4);
+                // planes of dx of at most 256 quads; their dy planes, which are no larger, in LDS
+                const long per_wg = quads <= kBlock ? std::min<long>(kBlock / quads, (kSmemFloats - kPlaneSlack) / plane_floats(a.Ho, a.Wo, a.K)) : 0;
+                const bool whole = a.W % 4 == 0 && a.Wo % 4 == 0;
                 if ((a.K == 3 || a.K == 5) && (a.S == 1 || a.S == 2) && a.W >= 4 && a.Wo >= 4 && per_wg > 0 &&
-                    a.Ho * ceil_div(a.Wo, 4) <= quads && (whole || a.total >= kRaggedMinElements) &&
-                    per_wg * (a.Ho + 2 * bd) * (a.Wo + 2 * bd) + (whole ? 0 : 4) <= kSmemFloats) {
+                    a.Ho * ceil_div(a.Wo, 4) <= quads && (whole || a.total >= kRaggedMinElements)) {
                     a.chunks = (int)per_wg;                        // whole planes of dx per workgroup, their dy staged in LDS
                     set_kernel<KID_DW_DGRAD_LDS>(t, a, ceil_div(planes, per_wg));
                     break;

@@ -250,6 +250,21 @@ def test_training_depthwise_backward_kernels(shape, kernel):
     check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
 
 
+def test_training_depthwise_planes_limited_by_lds():
+    """Planes of one row of eight: 85 of them fit a workgroup's LDS with the border of a 5 x 5 filter, where 128 have 256 quads
+    of pixels; 200 planes end inside the third group. Forward, input gradient and weight gradient."""
+    from workloads.model import Builder
+    b = Builder("depthwise_flat")
+    pw = b.conv1x1(b.input(40, 5, 1, 8), 5)
+    f = b.fc(b.add_n([b.global_avgpool(b.dwconv(pw, k, s)) for k in (3, 5) for s in (1, 2)]), 4)
+    rng = np.random.default_rng(11)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    seeds = {f: rng.standard_normal(fwd.nodes[f].shape).astype(np.float32)}
+    assert _ragged_names(fwd, seeds, 0.01, "dwconv_dgrad") == {"dwconv_dgrad_lds"}
+    check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
+
+
 @pytest.mark.parametrize("shape,cout", [((3, 20, 6, 6), 24), ((2, 20, 8, 8), 24), ((5, 12, 4, 4), 40), ((1, 36, 16, 16), 7), ((2, 8, 5, 4), 150)])
 def test_training_conv1x1_pixel_kernels(shape, cout):
     """conv1x1 forward, input gradient and weight gradient through the kernels that read pixels 128 bits at a time:
