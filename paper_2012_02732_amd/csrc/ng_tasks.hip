@@ -445,8 +445,9 @@ int choose_patch_kernel(const Shape& in, const Shape& out, long stride, long pad
     if (!patch_reaches(in, out)) return KID_NONE;
     int best = KID_NONE;
     double best_cost = 0;
-    // the 32-row kernel is for 32 output channels and fewer; those take the others only where its runs of 128 pixels have no patch that fits
-    const bool rows32 = out.c <= 32 && choose_strips(KID_C3_Q32, 128, out.h, out.w, stride).width > 0;
+    // the 32-row kernel is for 32 output channels and fewer; those take the others only where it would apply but for the patches of its
+    // runs of 128 pixels (a stride of 2 on maps of about 16 columns)
+    const bool rows32 = out.c <= 32 && (patch_pixels(128, in.w, out.h, out.w, stride, pad) > 640 || choose_strips(KID_C3_Q32, 128, out.h, out.w, stride).width > 0);
     for (const PatchKernel& k : kPatchKernels) {
         if (k.kid == KID_C3_SK || patch_pixels(k.tn, in.w, out.h, out.w, stride, pad) > k.pm) continue;
         if ((k.tm == 32) != rows32 || choose_strips(k.kid, k.tn, out.h, out.w, stride).width == 0) continue;
