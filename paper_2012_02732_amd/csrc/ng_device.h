@@ -26,8 +26,9 @@ enum Kid : int {
     KID_C3_L32, KID_C3_L64,          // conv3x3 as an implicit GEMM staged through LDS, 32 x 128 / 64 x 64 output tiles (many columns)
     // conv3x3 for many output pixels, patch-stationary: 16 input channels of the tile's input patch sit in LDS and the nine taps
     // read it at shifted addresses; weights go from memory straight into matrix-instruction operands. Output tiles (rows x pixels)
-    // 64 x 64 and 96 x 64; for wide images and a stride of 2 32 x 128, 64 x 64 and 64 x 128
-    KID_C3_P64, KID_C3_P96, KID_C3_Q32, KID_C3_Q64, KID_C3_Q128,
+    // 64 x 64 and 96 x 64; for wide images 32 x 128, 64 x 64 and 64 x 128; for a stride of 2, whose patches are four times as
+    // large, 32 x 128 and 64 x 128 with room for 640 pixels
+    KID_C3_P64, KID_C3_P96, KID_C3_Q32, KID_C3_Q64, KID_C3_Q128, KID_C3_R32, KID_C3_R128,
     KID_C3_SK,                       // the same for few output pixels: 32 x 32, K split over the wavefronts, each with a patch of up to 160 pixels
     // conv1x1 for many output pixels on the same plan (activations pixel-major in LDS, 32 or 64 channels at a time, weights
     // straight from memory): 32 x 64 and 64 x 64 output tiles
@@ -72,8 +73,8 @@ constexpr bool has_add_epilogue(int kid) { return plain_variant(kid) != kid; }
 constexpr bool is_c3_patch(int kid) { return kid >= KID_C3_P64 && kid <= KID_C3_SK; }
 // their LDS: patches (the block that is multiplied and the next one, or only the one; conv3x3_mfma_split_k: one for each wavefront)
 // and pixels that each has room for
-constexpr int c3_patches(int kid) { return kid == KID_C3_SK ? 4 : kid == KID_C3_Q64 || kid == KID_C3_Q128 ? 1 : 2; }
-constexpr int c3_patch_pixels(int kid) { return kid == KID_C3_SK ? 160 : kid == KID_C3_Q64 ? 384 : kid == KID_C3_Q32 || kid == KID_C3_Q128 ? 256 : 192; }
+constexpr int c3_patches(int kid) { return kid == KID_C3_SK ? 4 : kid == KID_C3_P64 || kid == KID_C3_P96 || kid == KID_C3_Q32 ? 2 : 1; }
+constexpr int c3_patch_pixels(int kid) { return kid == KID_C3_SK ? 160 : kid == KID_C3_Q64 ? 384 : kid == KID_C3_R32 || kid == KID_C3_R128 ? 640 : 256; }
 // wavefronts per SIMD that the registers of a stand-alone kernel must leave room for: the compiler takes more than half of them for 96 rows
 constexpr int min_waves(int kid) { return is_c3_patch(kid) && kid != KID_C3_SK ? 2 : 1; }
 constexpr bool is_pw_columns(int kid) { return (kid >= KID_PW_V1 && kid <= KID_PW_S4) || kid == KID_PW_P32 || kid == KID_PW_P64; }   // tiles = row tiles x column blocks

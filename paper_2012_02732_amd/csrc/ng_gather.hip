@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kBlock, min_waves(KID)) void gathered_kernel(Gather
     X(KID_PW_D4) X(KID_PW_D8) X(KID_PW_D16) X(KID_PW_64) X(KID_PW_V1) X(KID_PW_V2) X(KID_PW_V3) X(KID_PW_V4)            \
     X(KID_PW_S1) X(KID_PW_S2) X(KID_PW_S3) X(KID_PW_S4) X(KID_PW_P32) X(KID_PW_P64)                                     \
     X(KID_C3_M1) X(KID_C3_M2) X(KID_C3_M3) X(KID_C3_M4) X(KID_C3_L32) X(KID_C3_L64)                                     \
-    X(KID_C3_P64) X(KID_C3_P96) X(KID_C3_Q32) X(KID_C3_Q64) X(KID_C3_Q128) X(KID_C3_SK)                                 \
+    X(KID_C3_P64) X(KID_C3_P96) X(KID_C3_Q32) X(KID_C3_Q64) X(KID_C3_Q128) X(KID_C3_R32) X(KID_C3_R128) X(KID_C3_SK)     \
     X(KID_PW_PX_FWD) X(KID_BN_RAW) X(KID_BN_BACKWARD) X(KID_PAIR_DW) X(KID_PAIR_DW_LDS) X(KID_PAIR_PW16)                \
     X(KID_PAIR_PW32) X(KID_POOL_DGRAD) X(KID_POOL_DGRAD_LDS) X(KID_SLICE_PAD) X(KID_SMALL_GEMM)
 

@@ -752,8 +752,8 @@ __device__ __forceinline__ f32x16 split_sum(const f32x16& high, const f32x16& lo
 //     per tile (out-of-image and padding positions get an offset beyond the buffer's size, for which a buffer load returns
 //     0), so a fill is eight 32-bit loads with a scalar channel offset and three 128-bit LDS writes per item. With two patches
 //     (BUFFERS) the next block's is split and stored between the matrix instructions of this one: one barrier per block.
-// A wavefront owns 32 rows x 64 pixels, so a weight fragment (3 KiB through the vector L1) serves twelve matrix instructions. 64
-// rows x 128 pixels: 2 x 2 wavefronts. 64 x 64 and 32 x 128: two wavefronts side by side and K over two pairs (WK), by taps: of the nine
+// A wavefront owns 32 rows x 64 pixels (PX = 2 blocks of 32), so a weight fragment (3 KiB through the vector L1) serves twelve matrix
+// instructions. 64 rows x 128 pixels: 2 x 2 wavefronts. 64 x 64 and 32 x 128: two wavefronts side by side and K over two pairs (WK), by taps: of the nine
 // of a block one pair takes five and the other four, in turns. 96 x 64: two wavefronts in each pair, of which one owns the upper 32 rows
 // and the other the lower ones, and each one half of the middle rows.
 // What bounds it: power. While these kernels run the clock goes down to 1.6 - 1.9 GHz (2.4 nominal), matrix cores busy 60 % of the
@@ -766,21 +766,21 @@ __device__ __forceinline__ f32x16 split_sum(const f32x16& high, const f32x16& lo
 // the strips that two patches have room for are too narrow).
 // Needs Cin % 16 == 0 and a patch of at most PM pixels.
 // ------------------------------------------------------------------------------------
-template <int ROWS, int WN, int WK, int PM, int BUFFERS, bool FIN, class Wait>
+template <int ROWS, int WN, int WK, int PX, int PM, int BUFFERS, bool FIN, class Wait>
 __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, float* smem, int tid, bool live, Wait& wait) {
     const bool fout = wait.far_out();
-    constexpr int FM = ROWS == 96 ? 2 : 1, UNITS = FM + 1, TM = ROWS, TN = 64 * WN;
+    constexpr int FM = ROWS == 96 ? 2 : 1, UNITS = FM + PX - 1, TM = ROWS, TN = 32 * PX * WN;
     constexpr int TAPS = WK == 1 ? 9 : 4, ST = WK == 1 ? 3 : 2;     // slices of every block that a wavefront has, and how far ahead it loads weights
     constexpr int ITEMS = (2 * PM + kBlock - 1) / kBlock, PLANE = 2 * PM;           // PLANE: one part of a patch, in units of 16 bytes
     constexpr int kIn = FIN ? kPolicyDeviceScope : 0;
-    static_assert((ROWS == 96 ? 2 : ROWS / 32) * WN * WK == 4 && (WK == 1 || 4 * (8 + 8 * FM) * 64 <= BUFFERS * PM * 24), "four wavefronts; the sums that are handed over fit");
+    static_assert((ROWS == 96 ? 2 : ROWS / 32) * WN * WK == 4 && (PX == 2 || (WK == 1 && FM == 1)) && (WK == 1 || 4 * (8 + 8 * FM) * 64 <= BUFFERS * PM * 24), "four wavefronts; the sums that are handed over fit");
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, g = lane >> 5;
     const int by = tile % a.co_groups, bt = tile / a.co_groups;
     // the wavefront's share of K, and its blocks of the tile: rows `top` (96 rows: and the middle ones) x pixels n[0] and n[1]
-    const int kg = WK == 2 ? wave >> 1 : 0, wm = ROWS == 64 ? (WK == 2 ? wave & 1 : wave >> 1) : ROWS == 96 ? wave & 1 : 0, wn = WN == 2 ? wave & 1 : 0;
+    const int kg = WK == 2 ? wave >> 1 : 0, wm = ROWS == 64 ? (WK == 2 ? wave & 1 : wave >> 1) : ROWS == 96 ? wave & 1 : 0, wn = wave % WN;
     const int top = ROWS == 96 ? 2 * wm : wm;
-    const int n[2] = {ROWS == 96 ? wm : 2 * wn, ROWS == 96 ? 1 - wm : 2 * wn + 1};
+    const int n[2] = {ROWS == 96 ? wm : PX * wn, ROWS == 96 ? 1 - wm : PX * wn + 1};
     const int img = bt / a.tiles_xy, seg = bt - img * a.tiles_xy;
     const int HWo = a.Ho * a.Wo, HW = a.H * a.W;
     // the strip of the image (all but the last are tiles_x wide) and the run of its pixels
@@ -811,9 +811,9 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
         loff[t] = item ? 2 * pixel + (j ^ ((pixel >> 2) & 1)) : -1;     // in units of 16 bytes
     }
     // the patch pixel under tap 0 of this lane's output pixels
-    int base[2];
+    int base[PX];
 #pragma unroll
-    for (int jn = 0; jn < 2; ++jn) {
+    for (int jn = 0; jn < PX; ++jn) {
         const int px = p0 + min(n[jn] * 32 + r, npx - 1);
         const int oy = px / ws, ox = px - oy * ws;
         base[jn] = (oy - oy_a) * a.stride * Wp + ox * a.stride - skip;
@@ -852,15 +852,24 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
 #pragma unroll
         for (int p = 0; p < 3; ++p) to[p] = __builtin_amdgcn_raw_buffer_load_b128(wr, at.lane + lane * 16, at.scalar + (unsigned)(p * 1024), 0);
     };
-    u32x4 bf[2][3];
+    u32x4 bf[2][3];                                     // of the two blocks of pixels; one block: of this slice and the next one
     auto b_load = [&](int jn, int block, int tap) {
-        const int pixel = base[jn] + tap / 3 * Wp + tap % 3;
+        const int pixel = base[PX == 1 ? 0 : jn] + tap / 3 * Wp + tap % 3;
         const u32x4* s = patches + block % BUFFERS * 3 * PLANE + 2 * pixel + (g ^ ((pixel >> 2) & 1));
         bf[jn][0] = s[0], bf[jn][1] = s[PLANE], bf[jn][2] = s[2 * PLANE];
     };
-    // One slice: every operand is loaded again, for the next slice that needs its registers, as soon as it has been used.
-    auto slice = [&](u32x4 (&w)[FM][3], int block, int b_tap, bool more, int a_block, int a_tap) {
-        mfma_split(w[0], bf[1], high[1], low[1]);
+    // One slice (the d-th of its block): every operand is loaded again, for the next slice that needs its registers, as soon as it has
+    // been used.
+    auto slice = [&](u32x4 (&w)[FM][3], int d, int block, int b_tap, bool more, int a_block, int a_tap) {
+        if constexpr (PX == 1) {
+            if (more) b_load((d + 1) & 1, block, b_tap);
+            mfma_split(w[0], bf[d & 1], high[0], low[0]);
+            __builtin_amdgcn_sched_barrier(0);
+            a_load(w[0], 0, a_block, a_tap);
+            __builtin_amdgcn_sched_barrier(0);
+            return;
+        }
+        mfma_split(w[0], bf[1], high[UNITS > 1], low[UNITS > 1]);
         __builtin_amdgcn_sched_barrier(0);
         if (more) b_load(1, block, b_tap);
         mfma_split(w[0], bf[0], high[0], low[0]);
@@ -895,18 +904,18 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
         if (live) {
             const int t0 = first_tap(block), t1 = first_tap(block + 1);
             const bool middle = WK == 2 && t0 == 0;
-            b_load(1, block, t0);
+            if constexpr (PX == 2) b_load(1, block, t0);
             b_load(0, block, t0);
 #pragma unroll
             for (int d = 0; d < TAPS; ++d) {
-                slice(af[d % ST], block, t0 + d + 1, d + 1 < TAPS || middle, d + ST < TAPS ? block : block + 1, d + ST < TAPS ? t0 + d + ST : t1 + d + ST - TAPS);
+                slice(af[d % ST], d, block, t0 + d + 1, d + 1 < TAPS || middle, d + ST < TAPS ? block : block + 1, d + ST < TAPS ? t0 + d + ST : t1 + d + ST - TAPS);
                 if (d == (BUFFERS == 2 ? 0 : TAPS / 2)) {
                     if (BUFFERS == 2 && block + 1 < blocks) fill_store(block + 1);   // between the matrix instructions
                     fill_load(min(block + BUFFERS, blocks - 1));
                     __builtin_amdgcn_sched_barrier(0);  // keep the loads here: the compiler would sink them to their use
                 }
             }
-            if (middle) slice(am, block, 0, false, block + 2, 4);
+            if (middle) slice(am, TAPS, block, 0, false, block + 2, 4);
         }
         __syncthreads();                                // this block's patch has been read (and the next one's is there)
         if (BUFFERS == 1) {
@@ -932,7 +941,7 @@ __device__ __forceinline__ void conv3x3_patch_tile(const C3Args& a, int tile, fl
     if constexpr (WK == 1) {
         if (!live) return;
         store(sum[0], 16, mw, n[0] * 32 + r);
-        store(sum[1], 16, mw, n[1] * 32 + r);
+        if constexpr (PX == 2) store(sum[1], 16, mw, n[1] * 32 + r);
     } else {
         // The two shares of K meet: the wavefronts of the first finish pixels n[0], those of the second n[1] (of the middle rows
         // one half each); what the other one finishes is handed over in LDS.
@@ -1895,11 +1904,13 @@ NG_KERNEL(KID_C3_L32, C3Args, "conv3x3_lds_32x128", conv3x3_lds_tile < 32, 128, 
 NG_KERNEL(KID_C3_L64, C3Args, "conv3x3_lds_64x64", conv3x3_lds_tile < 64, 64, 32)
 NG_KERNEL(KID_PW_P32, PwArgs, "conv1x1_patch_32x64", conv1x1_patch_tile < 32, 4)
 NG_KERNEL(KID_PW_P64, PwArgs, "conv1x1_patch_64x64", conv1x1_patch_tile < 64, 2)
-NG_KERNEL(KID_C3_P64, C3Args, "conv3x3_patch_64x64", conv3x3_patch_tile < 64, 1, 2, c3_patch_pixels(KID_C3_P64), c3_patches(KID_C3_P64))
-NG_KERNEL(KID_C3_P96, C3Args, "conv3x3_patch_96x64", conv3x3_patch_tile < 96, 1, 2, c3_patch_pixels(KID_C3_P96), c3_patches(KID_C3_P96))
-NG_KERNEL(KID_C3_Q32, C3Args, "conv3x3_patch_32x128_wide", conv3x3_patch_tile < 32, 2, 2, c3_patch_pixels(KID_C3_Q32), c3_patches(KID_C3_Q32))
-NG_KERNEL(KID_C3_Q64, C3Args, "conv3x3_patch_64x64_wide", conv3x3_patch_tile < 64, 1, 2, c3_patch_pixels(KID_C3_Q64), c3_patches(KID_C3_Q64))
-NG_KERNEL(KID_C3_Q128, C3Args, "conv3x3_patch_64x128_wide", conv3x3_patch_tile < 64, 2, 1, c3_patch_pixels(KID_C3_Q128), c3_patches(KID_C3_Q128))
+NG_KERNEL(KID_C3_P64, C3Args, "conv3x3_patch_64x64", conv3x3_patch_tile < 64, 1, 2, 2, c3_patch_pixels(KID_C3_P64), c3_patches(KID_C3_P64))
+NG_KERNEL(KID_C3_P96, C3Args, "conv3x3_patch_96x64", conv3x3_patch_tile < 96, 1, 2, 2, c3_patch_pixels(KID_C3_P96), c3_patches(KID_C3_P96))
+NG_KERNEL(KID_C3_Q32, C3Args, "conv3x3_patch_32x128_wide", conv3x3_patch_tile < 32, 2, 2, 2, c3_patch_pixels(KID_C3_Q32), c3_patches(KID_C3_Q32))
+NG_KERNEL(KID_C3_Q64, C3Args, "conv3x3_patch_64x64_wide", conv3x3_patch_tile < 64, 1, 2, 2, c3_patch_pixels(KID_C3_Q64), c3_patches(KID_C3_Q64))
+NG_KERNEL(KID_C3_Q128, C3Args, "conv3x3_patch_64x128_wide", conv3x3_patch_tile < 64, 2, 1, 2, c3_patch_pixels(KID_C3_Q128), c3_patches(KID_C3_Q128))
+NG_KERNEL(KID_C3_R32, C3Args, "conv3x3_patch_32x128_large", conv3x3_patch_tile < 32, 4, 1, 1, c3_patch_pixels(KID_C3_R32), c3_patches(KID_C3_R32))
+NG_KERNEL(KID_C3_R128, C3Args, "conv3x3_patch_64x128_large", conv3x3_patch_tile < 64, 2, 1, 2, c3_patch_pixels(KID_C3_R128), c3_patches(KID_C3_R128))
 NG_KERNEL(KID_C3_SK, C3Args, "conv3x3_mfma_split_k", conv3x3_split_k_tile < c3_patch_pixels(KID_C3_SK))
 NG_KERNEL(KID_GEMM_PW_FWD, GemmArgs, "gemm_conv1x1_fwd", gemm_tile < GEMM_PW_FWD)
 NG_KERNEL(KID_GEMM_PW_DGRAD, GemmArgs, "gemm_conv1x1_dgrad", gemm_tile < GEMM_PW_DGRAD)
@@ -2003,7 +2014,7 @@ NG_KERNEL0(KID_SGD_BATCH, SgdBatchArgs, "sgd_update_batch", sgd_batch_tile)
     X(KID_PW_V1A) X(KID_PW_V2A) X(KID_PW_V3A) X(KID_PW_V4A) X(KID_PW_S1A) X(KID_PW_S2A)                                 \
     X(KID_PW_S3A) X(KID_PW_S4A) X(KID_C3_M1A) X(KID_C3_M2A) X(KID_C3_M3A) X(KID_C3_M4A)                                 \
     X(KID_POOL_A) X(KID_POOL_P4A) X(KID_C3_L32) X(KID_C3_L64)                                                          \
-    X(KID_C3_P64) X(KID_C3_P96) X(KID_C3_Q32) X(KID_C3_Q64) X(KID_C3_Q128) X(KID_C3_SK) X(KID_PW_P32) X(KID_PW_P64)                    \
+    X(KID_C3_P64) X(KID_C3_P96) X(KID_C3_Q32) X(KID_C3_Q64) X(KID_C3_Q128) X(KID_C3_R32) X(KID_C3_R128) X(KID_C3_SK) X(KID_PW_P32) X(KID_PW_P64)                    \
     X(KID_POOL_ROW_S1) X(KID_POOL_ROW_S2) X(KID_DW_LDS)                                                                               \
     X(KID_GEMM_PW_FWD) X(KID_GEMM_PW_DGRAD) X(KID_GEMM_PW_WGRAD) X(KID_GEMM_C3_FWD) X(KID_GEMM_C3_DGRAD)                \
     X(KID_GEMM_C3_WGRAD) X(KID_SMALL_GEMM) X(KID_PW_PX_FWD) X(KID_PW_PX_DGRAD) X(KID_PW_WGRAD_PX) X(KID_PW_WGRAD_PX2) X(KID_C3_WGRAD_PX) X(KID_C3_WGRAD_PX2) X(KID_BN_RAW) X(KID_BN_DGRAD) X(KID_BN_WGRAD) X(KID_RELU_DGRAD) X(KID_DW_DGRAD) X(KID_DW_DGRAD_LDS)                \

@@ -94,9 +94,9 @@ double tile_round_us(const ng_graph* g, int v, int kid_any, int subs) {
         }
         case KID_C3_L32: base = 2.0, per_tile = 0.14 * cin; break;     // 9 Cin / 4 k-steps of 4 MFMAs per wavefront, plus the slice fills
         case KID_C3_L64: base = 2.0, per_tile = 0.16 * cin; break;
-        case KID_C3_P64: case KID_C3_Q64: case KID_C3_Q32: base = 2.5, per_tile = 0.18 * cin; break;   // 9 Cin / 16 slices of 6 (32 x 32) MFMAs per wavefront
+        case KID_C3_P64: case KID_C3_Q64: case KID_C3_Q32: case KID_C3_R32: base = 2.5, per_tile = 0.18 * cin; break;   // 9 Cin / 16 slices of 6 (32 x 32) MFMAs per wavefront
         case KID_C3_P96: base = 2.5, per_tile = 0.27 * cin; break;
-        case KID_C3_Q128: base = 2.5, per_tile = 0.36 * cin; break;
+        case KID_C3_Q128: case KID_C3_R128: base = 2.5, per_tile = 0.36 * cin; break;
         case KID_C3_SK: base = 3.0, per_tile = 0.012 * cin; break;      // a quarter of 9 Cin / 16 slices per wavefront
         case KID_PW_PX_FWD: case KID_PW_PX_DGRAD: base = 2.0, per_tile = 0.6; break;
         case KID_SMALL_GEMM: base = 2.5, per_tile = 0.3; break;

@@ -399,11 +399,12 @@ PwChoice choose_pw(const ng_graph* g, int v) {
 // conv3x3 with at least 8 input channels runs as an implicit GEMM with K = 9 Cin
 constexpr long kC3LdsMinCols = 2048;      // measured: below this the 16 x 16 tiles (more workgroups, shorter K loops each) win
 // The patch-stationary kernels: rows and pixels of a tile; pm: what a run's rows of whole width may need (it decides between the
-// kernels for narrow and for wide images).
-struct PatchKernel { int kid, tm, tn, pm; };
-constexpr PatchKernel kPatchKernels[] = {{KID_C3_P64, 64, 64, 256}, {KID_C3_P96, 96, 64, 256}, {KID_C3_Q32, 32, 128, 640},
-                                         {KID_C3_Q64, 64, 64, 640}, {KID_C3_Q128, 64, 128, 640},
-                                         {KID_C3_SK, 32, 32, c3_patch_pixels(KID_C3_SK)}};
+// kernels for narrow and for wide images); a tile's time while the chip is full of them (64: one of 64 x 64), from 430 layers of 9 x 9 to
+// 130 x 130, 16 - 384 output channels, strides of 1 and 2: choose_patch_kernel takes the fastest of the kernels, or one within 5 % of it.
+struct PatchKernel { int kid, tm, tn, pm; double cost; };
+constexpr PatchKernel kPatchKernels[] = {{KID_C3_P64, 64, 64, 256, 64}, {KID_C3_P96, 96, 64, 256, 94}, {KID_C3_Q32, 32, 128, 640, 68},
+                                         {KID_C3_Q64, 64, 64, 640, 73}, {KID_C3_Q128, 64, 128, 640, 117}, {KID_C3_R32, 32, 128, 640, 74},
+                                         {KID_C3_R128, 64, 128, 640, 140}, {KID_C3_SK, 32, 32, c3_patch_pixels(KID_C3_SK), 0}};
 // Largest patch a run of tn consecutive output pixels can need: the rows it touches (a run can start at the end of a
 // row), stride apart, plus two, each W + 2 pad wide.
 long patch_pixels(long tn, long W, long Ho, long Wo, long stride, long pad) {
@@ -411,23 +412,28 @@ long patch_pixels(long tn, long W, long Ho, long Wo, long stride, long pad) {
     return ((rows - 1) * stride + 3) * (W + 2 * pad);
 }
 // The strips that an image is cut into, so that the patch of every run of tn pixels of a strip fits into the kernel's LDS: the width
-// of all but the last (0: none fits) and the runs of an image. As few runs as possible, then as few strips.
+// of all but the last (0: none fits) and the runs of an image. As few strips as possible, unless more of them save more than one run in 33.
 struct Strips { long width, runs; };
 long largest_patch(long tn, long width, long Ho, long stride) {              // as the kernel counts it, over the runs of one strip
     long most = 0;
-    const long row = (width - 1) * stride + 3;
-    for (long p = 0; p < width * Ho; p += tn) {
-        const long last = std::min(p + tn, width * Ho) - 1;
+    const long row = (width - 1) * stride + 3, pixels = width * Ho;
+    auto run = [&](long p) {
+        const long last = std::min(p + tn, pixels) - 1;
         most = std::max(most, ((last / width - p / width) * stride + 2) * row + last % width * stride + 3 - p % width * stride);
-    }
+    };
+    // a whole run's patch depends on the column it starts in, and those repeat after at most `width` runs; the last run may be short
+    for (long i = 0, start = 0; i < width && start < pixels; ++i, start += tn) run(start);
+    run((pixels - 1) / tn * tn);
     return most;
 }
 Strips choose_strips(int kid, long tn, long Ho, long Wo, long stride) {
-    auto fits = [&](long width) { return largest_patch(tn, width, Ho, stride) <= c3_patch_pixels(kid); };
+    const long room = c3_patch_pixels(kid);
+    auto fits = [&](long width) { return largest_patch(tn, width, Ho, stride) <= room; };
+    const long widest = (room - 2 * 3 - 3) / 2 / stride + 1;                 // the smallest patch: two rows of the strip and three pixels
     Strips best{0, 0};
-    for (long n = 1; n <= Wo; ++n) {
+    for (long n = ceil_div(Wo, widest); n <= Wo; ++n) {
         const long width = ceil_div(Wo, n), rest = Wo - (ceil_div(Wo, width) - 1) * width;
-        if (n > 1 && ceil_div(Wo, width) != n) continue;                      // the same width as with fewer strips
+        if (ceil_div(Wo, width) != n) continue;                               // the same width as with fewer strips
         if (!fits(width) || !fits(rest)) continue;
         const long runs = (n - 1) * ceil_div(width * Ho, tn) + ceil_div(rest * Ho, tn);
         if (best.width == 0 || runs * 33 < best.runs * 32) best = Strips{width, runs};
@@ -438,23 +444,24 @@ Strips choose_strips(int kid, long tn, long Ho, long Wo, long stride) {
 bool patch_reaches(const Shape& in, const Shape& out) {
     return in.c % 16 == 0 && in.n * in.c * in.h * in.w * 4 < (1L << 31) && 9 * in.c * (out.c + 95) * 6 < (1L << 31);
 }
-// Which patch kernel a conv3x3 gets (KID_NONE: none fits). Decided from shapes: a workgroup's time goes with the rows of
-// its tile, a compute unit works its workgroups off side by side, so the estimate is (tiles per compute unit, rounded up)
-// x rows; one lone workgroup per compute unit cannot keep the matrix cores busy on its own (x 1.15).
+// Which patch kernel a conv3x3 gets (KID_NONE: none fits). Decided from shapes: a compute unit works its workgroups off side by
+// side, so the estimate is (tiles per compute unit, rounded up) x a tile's time; one lone workgroup per compute unit cannot keep the
+// matrix cores busy on its own (x 1.15; tiles of 64 x 128 over one or two blocks of channels, mostly filling patches, x 1.25: two rounds
+// of 64 x 64 take 10.6 - 10.9 us there, 13 layers of 32 channels, and one of 64 x 128 10.9 - 11.2; with 48 channels 13.2 and 12.6). Tiles are the runs of the strips: narrow strips have short runs, which count in full (128
+// images of 64 x 33 x 33 to 384 channels, stride 2: six runs of 64 x 128 with 256 pixels of patch instead of two, 222 us; counted as
+// two it was taken before 64 x 64 with 119 and, with 640 pixels, 64 x 128 with 93).
 int choose_patch_kernel(const Shape& in, const Shape& out, long stride, long pad) {
     if (!patch_reaches(in, out)) return KID_NONE;
     int best = KID_NONE;
     double best_cost = 0;
-    // the 32-row kernel is for 32 output channels and fewer; those take the others only where it would apply but for the patches of its
-    // runs of 128 pixels (a stride of 2 on maps of about 16 columns)
-    const bool rows32 = out.c <= 32 && (patch_pixels(128, in.w, out.h, out.w, stride, pad) > 640 || choose_strips(KID_C3_Q32, 128, out.h, out.w, stride).width > 0);
     for (const PatchKernel& k : kPatchKernels) {
         if (k.kid == KID_C3_SK || patch_pixels(k.tn, in.w, out.h, out.w, stride, pad) > k.pm) continue;
-        if ((k.tm == 32) != rows32 || choose_strips(k.kid, k.tn, out.h, out.w, stride).width == 0) continue;
-        const long tiles = out.n * ceil_div(out.h * out.w, k.tn) * ceil_div(out.c, k.tm);
-        const long rounds = ceil_div(tiles, 256);
-        double cost = (double)rounds * k.tm * (k.tn / 64) * (rounds == 1 ? 1.15 : 1.0) * (k.pm > 256 ? 1.08 : 1.0);
-        if (k.tn == 128) cost *= 0.92;                                    // the weights are fetched once for twice the pixels
+        if (k.tm == 32 && out.c > 32) continue;
+        const Strips strips = choose_strips(k.kid, k.tn, out.h, out.w, stride);
+        if (strips.width == 0) continue;
+        const long rounds = ceil_div(out.n * strips.runs * ceil_div(out.c, k.tm), 256);
+        const double lone = k.tm == 64 && k.tn == 128 && in.c <= 32 ? 1.25 : 1.15;
+        const double cost = (double)rounds * k.cost * (rounds == 1 ? lone : 1.0);
         if (best == KID_NONE || cost < best_cost) best = k.kid, best_cost = cost;
     }
     return best;
@@ -902,6 +909,8 @@ int build_task(ng_graph* g, int v, char* arena, float* packed, Task& t) {
                     case KID_C3_P96: set_kernel<KID_C3_P96>(t, a, n); break;
                     case KID_C3_Q32: set_kernel<KID_C3_Q32>(t, a, n); break;
                     case KID_C3_Q64: set_kernel<KID_C3_Q64>(t, a, n); break;
+                    case KID_C3_R32: set_kernel<KID_C3_R32>(t, a, n); break;
+                    case KID_C3_R128: set_kernel<KID_C3_R128>(t, a, n); break;
                     case KID_C3_SK: set_kernel<KID_C3_SK>(t, a, n); break;
                     default: set_kernel<KID_C3_Q128>(t, a, n); break;
                 }

@@ -219,6 +219,34 @@ def test_conv3x3_patch_kernels_on_strips(shape, cout, stride, pad, kernel):
     check_all_nodes(w, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT))
 
 
+# A stride of 2: patches of up to 640 pixels in one go (32 x 128: four wavefronts side by side, all nine taps each), and of 225 - 255 of
+# the 256 that the kernels for narrow images have room for. Against 64 bits, bound as below.
+@pytest.mark.parametrize("shape,cout,pad,kernel", [
+    ((200, 16, 17, 17), 16, 1, "conv3x3_patch_32x128_large"), ((100, 48, 29, 33), 7, 0, "conv3x3_patch_32x128_large"),
+    ((100, 32, 31, 31), 32, 1, "conv3x3_patch_32x128_large"), ((100, 32, 31, 31), 70, 1, "conv3x3_patch_64x128_large"),
+    ((200, 80, 19, 21), 70, 0, "conv3x3_patch_64x128_large"), ((128, 64, 13, 13), 384, 1, "conv3x3_patch_96x64"),
+    ((222, 48, 15, 15), 64, 0, "conv3x3_patch_64x64")])
+def test_conv3x3_patch_kernels_with_a_stride(shape, cout, pad, kernel):
+    w = single_op(lambda b: b.bn_act(b.conv3x3(b.input(*shape), cout, 2, pad), relu=True))
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        assert B.ng_task_kernel(r.g, 1) == kernel
+        x, wt = torch.from_numpy(w.input).double(), torch.from_numpy(w.nodes[1].weights[0]).double()
+        ref = torch.nn.functional.conv2d(x, wt.view(cout, shape[1], 3, 3), stride=2, padding=pad).numpy()
+        normed = forward(w, keep=[2])[2]
+        for mode in (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT):
+            r.arena.zero_()
+            r.set_input(w.input)
+            r.replay(mode)
+            r.sync()
+            got = r.output(1).astype(np.float64)
+            assert np.linalg.norm(got - ref) <= 2.0 ** -24 * (1 + np.sqrt(9 * shape[1] / 16)) * np.linalg.norm(ref), mode
+            assert rel_err(r.output(2), normed) <= TOL
+    finally:
+        r.close()
+
+
 # The patch-stationary convolutions multiply in three bf16 parts per value. Against 64 bits, ragged in every direction: their
 # large accumulator is rounded once per 16 products, and partial sums grow to the result, so the 2-norm of the error is at most
 # about 2^-24 sqrt(K / 16) of the result's; one more 2^-24 for the stored value.

@@ -769,6 +769,18 @@ def test_kernel_choice_of_the_patch_stationary_convolutions():
     assert _kernels_on((1, 96, 35, 35), [c3(96)])[0].startswith("conv3x3_mfma_")
 
 
+def test_kernel_choice_counts_the_runs_of_the_strips():
+    """Stride 2 on maps of 13 - 33 columns: a kernel whose patches only take a few columns at a time has two to three times the runs
+    that the image has pixels for, most of them short. Those with room for whole rows are taken instead."""
+    def c3(cout, pad):
+        return lambda b, x: b.conv3x3(x, cout, 2, pad)
+    assert _kernels_on((128, 64, 33, 33), [c3(384, 0)]) == _kernels_on((128, 64, 31, 31), [c3(384, 1)]) == ["conv3x3_patch_64x128_large"]
+    assert _kernels_on((128, 64, 23, 23), [c3(384, 0)]) == _kernels_on((256, 96, 17, 17), [c3(96, 1)]) == ["conv3x3_patch_64x128_large"]
+    assert _kernels_on((256, 32, 31, 31), [c3(32, 1)]) == _kernels_on((256, 48, 19, 19), [c3(16, 1)]) == ["conv3x3_patch_32x128_large"]
+    assert _kernels_on((128, 64, 13, 13), [c3(384, 1)]) == _kernels_on((256, 96, 15, 15), [c3(96, 0)]) == ["conv3x3_patch_96x64"]
+    assert _kernels_on((128, 64, 15, 15), [c3(192, 1)]) == ["conv3x3_patch_64x64_wide"]
+
+
 def test_kernel_choice_of_conv1x1_pool_and_the_networks():
     def pw(cout):
         return lambda b, x: b.conv1x1(x, cout)
