@@ -265,6 +265,42 @@ def test_training_depthwise_planes_limited_by_lds():
     check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
 
 
+@pytest.mark.parametrize("shape", [(3, 7, 16, 16), (40, 20, 10, 15), (9, 24, 27, 27)])
+@pytest.mark.parametrize("k,stride", [(3, 1), (3, 2), (5, 1), (5, 2)])
+def test_training_depthwise_input_gradient_of_infinities(shape, k, stride):
+    """An infinite gradient reaches the pixels under its window and no others: with a stride of 2 a row of the input between two
+    rows of outputs reads only one of them. Reference: tap by tap in 64 bits, the taps that there are."""
+    from workloads.model import Builder
+    b = Builder("depthwise_infinite_gradients")
+    pw = b.conv1x1(b.input(shape[0], 5, *shape[2:]), shape[1])
+    d = b.dwconv(pw, k, stride)
+    rng = np.random.default_rng(18)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[d])
+    dy = rng.standard_normal(fwd.nodes[d].shape).astype(np.float32)
+    ho, wo = dy.shape[2:]
+    for c, (oy, ox) in enumerate(((0, 0), (1, wo - 1), (ho // 2, wo // 2), (ho - 1, wo - 2), (ho - 2, 1), (ho // 2, wo - 1))):
+        dy[c % shape[0], c, oy, ox] = np.inf if c % 2 else -np.inf
+    assert _ragged_names(fwd, {d: dy}, 0.01, "dwconv_dgrad") == {"dwconv_dgrad_lds"}
+    tw = workloads.training_graph(fwd, 0.01, {d: dy})
+    w = fwd.nodes[d].weights[0].astype(np.float64).reshape(shape[1], k, k)
+    p = k // 2
+    ref = np.zeros((shape[0], shape[1], shape[2] + 2 * p + stride, shape[3] + 2 * p + stride))
+    with np.errstate(invalid="ignore"):
+        for da in range(k):
+            for db in range(k):
+                ref[:, :, da:da + stride * (ho - 1) + 1:stride, db:db + stride * (wo - 1) + 1:stride] += w[:, da, db][None, :, None, None] * dy
+    ref = ref[:, :, p:p + shape[2], p:p + shape[3]]
+    finite = np.isfinite(ref)
+    assert 0 < (~finite).sum() <= 6 * k * k
+    for mode in (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT):
+        tensors, _ = run_training_step(tw, mode)
+        got = tensors[tw.grad_of[pw]].reshape(ref.shape)
+        assert np.array_equal(got[~finite], ref[~finite], equal_nan=True), mode
+        assert np.isfinite(got[finite]).all(), (mode, "reached", int((~np.isfinite(got[finite])).sum()))
+        assert rel_err(got[finite], ref[finite]) <= TOL, mode
+
+
 @pytest.mark.parametrize("shape,cout", [((3, 20, 6, 6), 24), ((2, 20, 8, 8), 24), ((5, 12, 4, 4), 40), ((1, 36, 16, 16), 7), ((2, 8, 5, 4), 150)])
 def test_training_conv1x1_pixel_kernels(shape, cout):
     """conv1x1 forward, input gradient and weight gradient through the kernels that read pixels 128 bits at a time:
