@@ -196,7 +196,7 @@ void gradients_left_in_parts(const ng_graph* g, const std::vector<Task>& tasks, 
 void make_sgd_batch_task(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& members, const std::vector<char>& in_parts,
                          std::vector<SgdTile>& table, const SgdTile* table_dev, Task& t);
 int launch_kid(const std::vector<Task>& tasks, const std::vector<int>& fused_into, int v);
-void plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, bool gather,
+bool plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, bool gather,
                           std::vector<std::vector<int>>& launches);
 void build_launch_graph(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, LaunchGraph& out);
 // ng_resident_plan.cpp: xcds = 0 lets the cost model choose among 1, 2, 4, 8.

@@ -8,6 +8,8 @@
 // inside a stream or by a synchronised edge. The graph written here must carry exactly
 // that order between the kernels that are actually launched.
 #include <algorithm>
+#include <map>
+#include <set>
 
 #include "ng_device.h"
 #include "ng_internal.h"
@@ -141,14 +143,15 @@ void gradients_left_in_parts(const ng_graph* g, const std::vector<Task>& tasks, 
     }
 }
 
-// The launches of the single-stream modes, in order, each a list of launched tasks. `gather`: launches of one kernel that do not
-// depend on each other (a cell's depthwise convolutions, the 1 x 1 convolutions at the head of an Inception module, the
-// gradients of both) become one launch, for which the launches are taken in another order than the submission order, one that
-// every dependency allows: among the kernels with a task whose inputs are complete, one that no further task could join by
-// waiting (all its other tasks come after one of these) goes first, with all of its tasks that are ready; if there is none,
-// the kernel with the most ready tasks. On one stream a task waits for everything before it anyway, and a batch-1 task or a
-// CIFAR-sized gradient fills a fraction of the chip for a few microseconds, of which 1.6 us are the launch gap.
-void plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, bool gather,
+// The launches of the single-stream modes, in order, each a list of launched tasks; false if some task has found no place. `gather`:
+// launches of one kernel that do not depend on each other (a cell's depthwise convolutions, the 1 x 1 convolutions at the head of
+// an Inception module, the gradients of both) become one launch, for which the launches are taken in another order than the
+// submission order, one that every dependency allows: of the kernels with a task whose inputs are complete, one that no further
+// task could join by waiting (all its other tasks come after one of these) goes first, with all of its tasks that are ready; if
+// there is none, the kernel with the most ready tasks; among equals the one with the earliest task. On one stream a task waits for
+// everything before it anyway, and a batch-1 task or a CIFAR-sized gradient fills a fraction of the chip for a few microseconds,
+// of which 1.6 us are the launch gap.
+bool plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, const std::vector<int>& fused_into, bool gather,
                           std::vector<std::vector<int>>& launches) {
     const int n = (int)g->nodes.size();
     launches.clear();
@@ -158,7 +161,7 @@ void plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, con
     const int m = (int)node_of.size();
     if (!gather) {
         for (int v : node_of) launches.emplace_back(1, v);
-        return;
+        return true;
     }
     // dependencies between launches: whoever writes (part of) a tensor before whoever reads it
     std::vector<std::vector<int>> writers(n), next(m);
@@ -177,7 +180,12 @@ void plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, con
         const int to = writers[v][0];
         for (int p : g->nodes[v].preds)
             for (int from : writers[p])
-                if (from != to && std::find(next[from].begin(), next[from].end(), to) == next[from].end()) next[from].push_back(to), ++waiting[to];
+                if (from != to) next[from].push_back(to);
+    }
+    for (std::vector<int>& to : next) {
+        std::sort(to.begin(), to.end());
+        to.erase(std::unique(to.begin(), to.end()), to.end());
+        for (int t : to) ++waiting[t];
     }
     // a topological order (a launch that carries two tasks sits at the place of the earlier one, so ascending indices need not be one)
     std::vector<int> topo, left = waiting;
@@ -195,52 +203,69 @@ void plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, con
             for (size_t w = 0; w < words; ++w) row[w] |= after[(size_t)to * words + w];
         }
     }
-    // kernels (their ids), or tasks that always launch alone
-    std::vector<int> kind(m);
+    // the tasks of one kernel. While none of them is launched, ever more of them are ready or come after one that is: the members
+    // before `open` are or do, and need no second look.
+    struct Kernel {
+        std::vector<int> members, ready;
+        std::vector<uint64_t> behind;                           // launches after a ready one
+        size_t open = 0;
+        int looked_at = -1;                                     // when there were so many launches
+    };
+    std::map<int, Kernel> kernels;
+    std::vector<Kernel*> kernel_of(m, nullptr);                 // nullptr: always launches alone
     for (int i = 0; i < m; ++i) {
         const int kid = launch_kid(tasks, fused_into, node_of[i]);
-        kind[i] = can_gather(kid) ? kid : -1 - i;
+        if (!can_gather(kid)) continue;
+        Kernel& k = kernels[kid];
+        k.members.push_back(i), k.behind.resize(words, 0);
+        kernel_of[i] = &k;
     }
-    std::vector<int> ready;
-    std::vector<char> launched(m, 0);
-    for (int i = 0; i < m; ++i)
-        if (waiting[i] == 0) ready.push_back(i);
-    std::vector<uint64_t> behind(words);
-    while (!ready.empty()) {
-        int best = -1;
-        size_t best_count = 0;
-        bool best_closed = false;
-        for (size_t r = 0; r < ready.size(); ++r) {
-            const int c = kind[ready[r]];
-            bool first = true;                                  // once per kernel, at its earliest ready task
-            for (size_t q = 0; q < r; ++q) first = first && kind[ready[q]] != c;
-            if (!first) continue;
-            size_t count = 0;
-            std::fill(behind.begin(), behind.end(), 0);
-            std::vector<char> here(m, 0);
-            for (int i : ready)
-                if (kind[i] == c) {
-                    ++count, here[i] = 1;
-                    for (size_t w = 0; w < words; ++w) behind[w] |= after[(size_t)i * words + w];
-                }
-            bool closed = true;
-            for (int i = 0; i < m && closed; ++i)
-                closed = kind[i] != c || launched[i] || here[i] || ((behind[i / 64] >> (i % 64)) & 1);
-            if (best < 0 || closed > best_closed || (closed == best_closed && !closed && count > best_count)) best = c, best_count = count, best_closed = closed;
+    enum : char { WAITING, READY, LAUNCHED };
+    std::vector<char> state(m, WAITING);
+    std::set<int> ready;
+    auto make_ready = [&](int i) {
+        ready.insert(i);
+        state[i] = READY;
+        if (Kernel* k = kernel_of[i]) {
+            k->ready.push_back(i);
+            for (size_t w = 0; w < words; ++w) k->behind[w] |= after[(size_t)i * words + w];
         }
-        std::vector<int> now, rest;
-        for (int i : ready) (kind[i] == best ? now : rest).push_back(i);
-        ready.swap(rest);
+    };
+    for (int i = 0; i < m; ++i)
+        if (waiting[i] == 0) make_ready(i);
+    int placed = 0;
+    while (!ready.empty()) {
+        const Kernel* best = nullptr;                           // the one with the most ready tasks, unless one is closed
+        std::vector<int> now;
+        for (int i : ready) {
+            Kernel* k = kernel_of[i];
+            if (!k) { now.assign(1, i); break; }
+            if (k->looked_at == (int)launches.size()) continue;
+            k->looked_at = (int)launches.size();
+            while (k->open < k->members.size()) {
+                const int j = k->members[k->open];
+                if (state[j] == WAITING && !((k->behind[j / 64] >> (j % 64)) & 1)) break;
+                ++k->open;
+            }
+            if (k->open == k->members.size()) { now = k->ready; break; }
+            if (!best || k->ready.size() > best->ready.size()) best = k;
+        }
+        if (now.empty()) now = best->ready;
+        std::sort(now.begin(), now.end());
+        if (Kernel* k = kernel_of[now[0]]) {
+            k->ready.clear(), k->open = 0;
+            std::fill(k->behind.begin(), k->behind.end(), 0);
+        }
         for (size_t at = 0; at < now.size(); at += kGatherMax) {
             launches.emplace_back();
             for (size_t q = at; q < std::min(now.size(), at + kGatherMax); ++q) launches.back().push_back(node_of[now[q]]);
         }
-        for (int i : now) launched[i] = 1;
+        for (int i : now) ready.erase(i), state[i] = LAUNCHED, ++placed;
         for (int i : now)
             for (int to : next[i])
-                if (--waiting[to] == 0) ready.push_back(to);
-        std::sort(ready.begin(), ready.end());
+                if (--waiting[to] == 0) make_ready(to);
     }
+    return placed == m;
 }
 
 // The multi-stream graph: one kernel node per launched task, in submission order; a node
@@ -349,7 +374,8 @@ extern "C" int ng_get_single_launches(ng_graph* g, int* position, int* n_launche
     std::vector<int> fused_into;
     decide_launch_fusion(g, g->tasks, g->launch_fusion, true, fused_into);
     std::vector<std::vector<int>> launches;
-    plan_single_launches(g, g->tasks, fused_into, g->launch_fusion && !g->memory_reuse, launches);
+    if (!plan_single_launches(g, g->tasks, fused_into, g->launch_fusion && !g->memory_reuse, launches))
+        return g->fail(NG_EINVAL, "ng_get_single_launches: the launches wait for each other in a circle");
     if (position) {
         const int n = (int)g->nodes.size();
         std::vector<int> of(n, -1);

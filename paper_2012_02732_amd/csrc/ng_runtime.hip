@@ -688,7 +688,8 @@ int ng_bind(ng_graph* g, void* arena, size_t arena_bytes, void* const* hip_strea
     gradients_left_in_parts(g, g->tasks, single_fused_into, in_parts);
     fuse_launches(single_fused_into, in_parts, g->single_tasks);
     std::vector<std::vector<int>> launches;
-    plan_single_launches(g, g->tasks, single_fused_into, g->launch_fusion && !g->memory_reuse, launches);
+    if (!plan_single_launches(g, g->tasks, single_fused_into, g->launch_fusion && !g->memory_reuse, launches))
+        return g->fail(NG_EINVAL, "ng_bind: the launches of the single-stream modes wait for each other in a circle");
     g->single_launches.clear();
     for (const std::vector<int>& members : launches) {
         std::vector<const Task*> of;

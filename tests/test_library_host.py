@@ -1024,7 +1024,8 @@ def test_single_stream_launches_follow_every_dependency_and_share_only_one_kerne
         kernel = [None if nd.op == "input" else B.ng_planned_task_kernel(r.g, v) for v, nd in enumerate(w.nodes)]
         r.close()
         assert set(p for p in pos if p >= 0) == set(range(launches))
-        # tasks that ride on another's launch are where it is; nothing else changes who writes what
+        # every launched task has a place; tasks that ride on another's launch are where it is; nothing else changes who writes what
+        assert all(pos[v] >= 0 for v in range(n) if by[v] == v)
         assert all(pos[v] == (pos[by[v]] if by[v] >= 0 else by[v]) for v in range(n))
 
         def writers(t):
@@ -1048,6 +1049,45 @@ def test_single_stream_launches_follow_every_dependency_and_share_only_one_kerne
             shared += len(members) - 1
         assert fusion or all(len(m) == 1 for m in groups.values())
     assert (shared > 100) if fusion else shared == 0
+
+
+@pytest.mark.parametrize("op", ["global_avgpool", "bn_act"])
+def test_single_stream_launches_of_a_wide_graph_are_planned_in_no_time(op):
+    """2000 tasks side by side, kernels that launch alone and kernels that share launches: a fraction of a second (with a step for
+    every launch that looks at all pairs of ready tasks the former take 9.5 s)."""
+    import time
+    from workloads.model import Builder
+    b = Builder("wide")
+    x = b.input(1, 8, 8, 8)
+    outs = [getattr(b, op)(x) for _ in range(2000)]
+    rng = np.random.default_rng(0)
+    b.draw_weights(rng, 0.3, "random")
+    r = GraphRunner(b.finish(rng, outputs=outs[-1:]))
+    r.schedule()
+    r.plan()
+    t = time.perf_counter()
+    pos, launches = B.ng_get_single_launches(r.g)
+    t = time.perf_counter() - t
+    r.close()
+    assert sorted(set(pos) - {-1}) == list(range(launches)) and launches == (2000 if op == "global_avgpool" else 334)
+    assert t < 2.0, t
+
+
+def test_single_stream_kernels_that_launch_alone_do_not_go_last():
+    """A task of a kernel that always launches alone is ready at the start; behind it comes one more of a kernel that shares
+    launches: both of that kernel in one launch, after it."""
+    from workloads.model import Builder
+    b = Builder("alone_first")
+    x = b.input(1, 16, 8, 8)
+    a = b.pool(x, "max", 1, 1)                              # could go at once
+    c = b.pool(b.concat([b.global_avgpool(x), b.global_avgpool(x)]), "max", 1, 1)
+    rng = np.random.default_rng(0)
+    r = GraphRunner(b.finish(rng, outputs=[a, c]))
+    r.schedule()
+    r.plan()
+    pos, launches = B.ng_get_single_launches(r.g)
+    r.close()
+    assert pos[a] == pos[c] == launches - 1, pos
 
 
 def test_columns_dealt_out_to_the_xcds_cover_every_tile_once(tmp_path):
