@@ -213,6 +213,7 @@ __global__ __launch_bounds__(kGroup) void resident_kernel(DevPlan plan, unsigned
 #define NG_CASE(KID)                                                                                                         \
     case KID:                                                                                                                \
         if constexpr (in_build(BUILD, KID)) {                                                                                \
+            static_assert(smem_floats(KID) <= kSmemPerSub, "a sub-block has less LDS than the kernel takes");                \
             CounterWait<has_add_epilogue(KID)> wait{plan, rec, &s_abort, &s_late, epoch, task, np, n_late, lane, stamp, true, true, far_out}; \
             run_tiles<KID>(rec + 24, tile0, step, ntiles, subs, smem, sub, tid, far_in, wait);                               \
         }                                                                                                                    \
