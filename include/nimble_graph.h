@@ -413,16 +413,18 @@ int ng_time_task(ng_graph* g, int id, int reps, float* isolated_us);
  * *min_us (may be NULL) receive median and minimum. What the command processor spends around a
  * dispatch is not part of it (a kernel trace's begin-to-end time of the same kernel is 1-2 us longer).
  * as_executed = 0: the task's stand-alone kernel, one kernel per task whatever the replay mode does.
- * as_executed != 0 (needs ng_capture): the kernel the current replay mode really runs for the task -
- * in modes 0-3 a convolution together with the batch-norm / ReLU fused into its kernel, in the
- * device-resident mode the plan's kernel variant with its fused batch-norm and add_n - and 0 for a
- * task that has no kernel of its own in that mode (it runs inside another task's kernel or has
- * nothing to do) and for inputs. */
+ * as_executed != 0 (needs ng_capture): the launch the current replay mode really carries the task out with -
+ * in modes 0 and 3 a convolution together with the batch-norm / ReLU fused into its kernel, in modes 1 and 2
+ * that of every task at the same place of ng_get_single_launches (all tasks of the launch have its time: on a
+ * path of the DAG there is only one of them), in the device-resident mode the plan's kernel variant with its
+ * fused batch-norm and add_n - and 0 for a task that has no workgroups of its own in that mode (it runs inside
+ * another task's kernel or has nothing to do) and for inputs. */
 int ng_time_task_device(ng_graph* g, int id, int as_executed, int reps, float* median_us, float* min_us);
 /* One launch of the same kernel (as_executed as above; id = -1: an empty kernel) on the origin
  * stream, awaited before the call returns: a solo dispatch for a kernel trace taken from outside
  * (rocprofv3 --kernel-trace), whose begin-to-end timestamps are the other definition of an isolated
- * kernel time. Nothing is launched for a task without a kernel of its own. */
+ * kernel time. as_executed != 0 in modes 1 and 2: with it go the other tasks of the replay's launch. Nothing is
+ * launched for a task without a kernel of its own. */
 int ng_launch_task_solo(ng_graph* g, int id, int as_executed);
 /* Name of the kernel the current replay mode runs for the node, as timed by ng_time_task_device with
  * as_executed != 0; "" if it has none of its own. Needs ng_capture. Valid until ng_destroy. */

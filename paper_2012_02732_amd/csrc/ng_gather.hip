@@ -14,8 +14,7 @@ namespace ng {
 namespace {
 
 template <int KID>
-__global__ __launch_bounds__(kBlock, min_waves(KID)) void gathered_kernel(GatherArgs<typename KernelOf<KID>::Args> p) {
-    __shared__ __align__(16) float smem[smem_floats(KID)];
+__device__ __forceinline__ void gathered_tile(const GatherArgs<typename KernelOf<KID>::Args>& p, float* smem) {
     int place = (int)blockIdx.x, column = -1;
     if constexpr (is_pw_columns(KID)) {
         if (p.eights > 0) {
@@ -35,6 +34,25 @@ __global__ __launch_bounds__(kBlock, min_waves(KID)) void gathered_kernel(Gather
     }
     NoWait wait;
     KernelOf<KID>::template tile<false>(a, tile, smem, threadIdx.x, true, wait);
+}
+template <int KID>
+__global__ __launch_bounds__(kBlock, min_waves(KID)) void gathered_kernel(GatherArgs<typename KernelOf<KID>::Args> p) {
+    __shared__ __align__(16) float smem[smem_floats(KID)];
+    gathered_tile<KID>(p, smem);
+}
+// With the device's clock read around it, as timed_kernel does.
+template <int KID>
+__global__ __launch_bounds__(kBlock, min_waves(KID)) void timed_gathered_kernel(GatherArgs<typename KernelOf<KID>::Args> p, unsigned long long* stamps) {
+    __shared__ __align__(16) float smem[smem_floats(KID)];
+    unsigned long long t0 = 0;
+    if (threadIdx.x == 0) t0 = wall_clock64();
+    gathered_tile<KID>(p, smem);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                          // vmcnt(0): this wave's stores are acknowledged
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        stamps[2 * (size_t)blockIdx.x] = t0;
+        stamps[2 * (size_t)blockIdx.x + 1] = wall_clock64();
+    }
 }
 
 // the kernels that a network runs several of side by side
@@ -77,6 +95,7 @@ void fill(const std::vector<const Task*>& tasks, SingleLaunch& out) {
     else if (n == 1) return;                                    // launched as it is
     if (total <= 0 || total >= (1L << 31)) return;
     out.fn = reinterpret_cast<const void*>(&gathered_kernel<KID>);
+    out.timed_fn = reinterpret_cast<const void*>(&timed_gathered_kernel<KID>);
     out.grid = (unsigned)total;
     out.args.resize(sizeof p);
     std::memcpy(out.args.data(), &p, sizeof p);
@@ -102,7 +121,7 @@ void make_gathered_launch(const std::vector<const Task*>& tasks, SingleLaunch& o
         if (t->kid != tasks[0]->kid || !t->fn) return;
     if (tasks.size() == 1) {
         const Task& t = *tasks[0];
-        out.fn = t.fn, out.grid = t.grid[0], out.lds_bytes = t.lds_bytes;
+        out.fn = t.fn, out.timed_fn = timed_kernel_handle(t.kid), out.grid = t.grid[0], out.lds_bytes = t.lds_bytes;
         out.args.assign(t.args, t.args + sizeof t.args);
         if (!is_pw_columns(t.kid)) return;
     }

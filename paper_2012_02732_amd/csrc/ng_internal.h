@@ -95,6 +95,7 @@ struct ResidentPlan {
 // One launch of the single-stream modes: a task's own kernel, or several tasks of one kernel.
 struct SingleLaunch {
     const void* fn = nullptr;
+    const void* timed_fn = nullptr;            // the same with the device's clock read around every workgroup
     unsigned grid = 0, lds_bytes = 0;
     std::vector<unsigned char> args;
 };
@@ -137,6 +138,7 @@ struct ng_graph {
                                                          // a convolution is applied by that convolution's kernel and has no launch of its own
     std::vector<ng::Task> single_tasks;                  // what the single-stream modes launch: the same, with the weight updates of all streams in one launch
     std::vector<ng::SingleLaunch> single_launches;       // ... in the order in which they launch it
+    std::vector<int> single_launch_of;                   // [n_nodes] the launch with the workgroups of single_tasks[v], -1: none
     std::vector<int> launch_fused_into;                  // [n_nodes] that convolution (the node itself: a concat with nothing to copy), or -1
     ng::Runtime* rt = nullptr;
     int mode = NG_MODE_AUTO;

@@ -691,9 +691,10 @@ int ng_bind(ng_graph* g, void* arena, size_t arena_bytes, void* const* hip_strea
     if (!plan_single_launches(g, g->tasks, single_fused_into, g->launch_fusion && !g->memory_reuse, launches))
         return g->fail(NG_EINVAL, "ng_bind: the launches of the single-stream modes wait for each other in a circle");
     g->single_launches.clear();
+    g->single_launch_of.assign(g->nodes.size(), -1);
     for (const std::vector<int>& members : launches) {
         std::vector<const Task*> of;
-        for (int v : members) of.push_back(&g->single_tasks[v]);
+        for (int v : members) of.push_back(&g->single_tasks[v]), g->single_launch_of[v] = (int)g->single_launches.size();
         g->single_launches.emplace_back();
         make_gathered_launch(of, g->single_launches.back());
         if (!g->single_launches.back().fn) return g->fail(NG_EINVAL, "ng_bind: no kernel for the launch of task %d", members[0]);
@@ -1116,16 +1117,40 @@ int ng_time_task(ng_graph* g, int id, int reps, float* isolated_us) {
     return NG_OK;
 }
 
-// The task as replay mode `mode` really runs it, as a stand-alone launch: the per-task kernel, or the
-// convolution with its fused batch-norm (modes 0-3), or the kernel variant of the device-resident plan
-// (partition, outputs per thread, fused batch-norm and add_n). false: the task has no kernel of its own
-// in that mode (it runs inside another task's kernel, or has nothing to do).
-static bool executed_task(const ng_graph* g, int id, int mode, Task& out, const char** name) {
+// A kernel that is launched by itself, to be timed or traced.
+struct SoloLaunch {
+    const void *fn = nullptr, *timed_fn = nullptr;
+    const char* name = "";
+    dim3 grid, block{kBlock};
+    unsigned lds_bytes = 0;
+    std::vector<unsigned char> args;
+};
+static SoloLaunch solo_launch(const Task& t) {
+    SoloLaunch l;
+    l.fn = t.fn, l.timed_fn = timed_kernel_handle(t.kid), l.name = t.name;
+    l.grid = dim3(t.grid[0], t.grid[1], t.grid[2]), l.block = dim3(t.block[0], t.block[1], t.block[2]), l.lds_bytes = t.lds_bytes;
+    l.args.assign(t.args, t.args + sizeof t.args);
+    return l;
+}
+
+// The launch that replay mode `mode` really carries out task `id` with: the per-task kernel, or the convolution with its fused
+// batch-norm (modes 0 and 3), the launch that may carry other tasks of the same kernel as well (modes 1 and 2), or the kernel
+// variant of the device-resident plan (partition, outputs per thread, fused batch-norm and add_n). false: the task has no kernel
+// of its own in that mode (it runs inside another task's kernel, or has nothing to do).
+static bool executed_launch(const ng_graph* g, int id, int mode, SoloLaunch& out) {
     if (mode == NG_MODE_AUTO) mode = g->auto_mode;
+    if (mode == NG_MODE_GRAPH_SINGLE || mode == NG_MODE_EAGER_SINGLE) {
+        if ((size_t)id >= g->single_launch_of.size() || g->single_launch_of[id] < 0) return false;
+        const SingleLaunch& l = g->single_launches[g->single_launch_of[id]];
+        out = SoloLaunch();
+        out.fn = l.fn, out.timed_fn = l.timed_fn, out.name = g->single_tasks[id].name;
+        out.grid = dim3(l.grid), out.lds_bytes = l.lds_bytes, out.args = l.args;
+        return true;
+    }
     if (mode != NG_MODE_DEVICE_RESIDENT) {
-        out = (mode == NG_MODE_GRAPH_SINGLE || mode == NG_MODE_EAGER_SINGLE) ? g->single_tasks[id] : g->launch_tasks[id];
-        if (name) *name = out.name;
-        return out.fn != nullptr;
+        if (!g->launch_tasks[id].fn) return false;
+        out = solo_launch(g->launch_tasks[id]);
+        return true;
     }
     const Runtime& rt = *g->rt;
     if ((size_t)id >= rt.kept_tasks.size() || !g->tasks[id].fn || rt.fused_into[id] >= 0 || rt.elided[id]) return false;
@@ -1133,12 +1158,10 @@ static bool executed_task(const ng_graph* g, int id, int mode, Task& out, const 
     const char* nm = "";
     const void* fn = standalone_kernel_handle(d.kid, &nm);
     if (!fn || d.ntiles <= 0) return false;
-    out = Task();
-    out.fn = fn, out.name = nm, out.kid = d.kid, out.ntiles = d.ntiles;
-    out.grid[0] = (unsigned)d.ntiles, out.block[0] = kBlock;
-    static_assert(sizeof out.args >= sizeof d.args, "argument blocks");
-    std::memcpy(out.args, d.args, sizeof d.args);
-    if (name) *name = nm;
+    out = SoloLaunch();
+    out.fn = fn, out.timed_fn = timed_kernel_handle(d.kid), out.name = nm, out.grid = dim3((unsigned)d.ntiles);
+    static_assert(sizeof d.args <= kLaunchArgBytes, "argument blocks");
+    out.args.assign(reinterpret_cast<const unsigned char*>(&d.args), reinterpret_cast<const unsigned char*>(&d.args) + sizeof d.args);
     return true;
 }
 
@@ -1148,26 +1171,25 @@ int ng_time_task_device(ng_graph* g, int id, int as_executed, int reps, float* m
     if (id < 0 || id >= (int)g->nodes.size() || reps <= 0 || reps > 100000 || !median_us) return g->fail(NG_EINVAL, "ng_time_task_device: bad argument");
     *median_us = 0.f;
     if (min_us) *min_us = 0.f;
-    Task t = g->tasks[id];
-    if (as_executed && !executed_task(g, id, g->mode, t, nullptr)) return NG_OK;
-    if (!t.fn) return NG_OK;
+    SoloLaunch l = solo_launch(g->tasks[id]);
+    if (as_executed && !executed_launch(g, id, g->mode, l)) return NG_OK;
+    if (!l.fn) return NG_OK;
     Runtime& rt = *g->rt;
     hipStream_t s = rt.streams[0];
-    const void* fn = timed_kernel_handle(t.kid);
-    if (!fn) return g->fail(NG_EINVAL, "ng_time_task_device: kernel %d has no timed variant", t.kid);
-    const size_t wgs = (size_t)t.grid[0] * t.grid[1] * t.grid[2];
+    if (!l.timed_fn) return g->fail(NG_EINVAL, "ng_time_task_device: kernel %s has no timed variant", l.name);
+    const size_t wgs = (size_t)l.grid.x * l.grid.y * l.grid.z;
     if (rt.stamps_wgs < wgs) {                                     // one pair of readings per workgroup
         if (rt.stamps) (void)hipFree(rt.stamps), rt.stamps = nullptr, rt.stamps_wgs = 0;
         NG_HIP(hipMalloc(reinterpret_cast<void**>(&rt.stamps), wgs * 2 * sizeof(unsigned long long)));
         rt.stamps_wgs = wgs;
     }
     unsigned long long* stamps = rt.stamps;
-    void* args[2] = {t.args, &stamps};
+    void* args[2] = {l.args.data(), &stamps};
     std::vector<unsigned long long> h(2 * wgs);
     std::vector<float> us;
     NG_HIP(hipStreamSynchronize(s));
     for (int rep = -2; rep < reps; ++rep) {                        // two untimed launches first
-        NG_HIP(hipLaunchKernel(fn, dim3(t.grid[0], t.grid[1], t.grid[2]), dim3(t.block[0], t.block[1], t.block[2]), args, t.lds_bytes, s));
+        NG_HIP(hipLaunchKernel(l.timed_fn, l.grid, l.block, args, l.lds_bytes, s));
         NG_HIP(hipStreamSynchronize(s));                           // solo: nothing else is in flight when the next one starts
         if (rep < 0) continue;
         NG_HIP(hipMemcpy(h.data(), rt.stamps, h.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost));
@@ -1190,11 +1212,11 @@ int ng_launch_task_solo(ng_graph* g, int id, int as_executed) {
     if (id < 0) {
         NG_HIP(hipLaunchKernel(empty_kernel_handle(), dim3(1), dim3(64), nullptr, 0, s));
     } else {
-        Task t = g->tasks[id];
-        if (as_executed && !executed_task(g, id, g->mode, t, nullptr)) return NG_OK;
-        if (!t.fn) return NG_OK;
-        void* args[1] = {t.args};
-        NG_HIP(hipLaunchKernel(t.fn, dim3(t.grid[0], t.grid[1], t.grid[2]), dim3(t.block[0], t.block[1], t.block[2]), args, t.lds_bytes, s));
+        SoloLaunch l = solo_launch(g->tasks[id]);
+        if (as_executed && !executed_launch(g, id, g->mode, l)) return NG_OK;
+        if (!l.fn) return NG_OK;
+        void* args[1] = {l.args.data()};
+        NG_HIP(hipLaunchKernel(l.fn, l.grid, l.block, args, l.lds_bytes, s));
     }
     NG_HIP(hipStreamSynchronize(s));
     return NG_OK;
@@ -1202,9 +1224,8 @@ int ng_launch_task_solo(ng_graph* g, int id, int as_executed) {
 
 const char* ng_task_kernel_executed(const ng_graph* g, int id) {
     if (!g || g->phase < CAPTURED || id < 0 || id >= (int)g->tasks.size()) return "";
-    Task t;
-    const char* name = "";
-    return executed_task(g, id, g->mode, t, &name) ? name : "";
+    SoloLaunch l;
+    return executed_launch(g, id, g->mode, l) ? l.name : "";
 }
 
 int ng_time_launch_floor(ng_graph* g, int reps, float* median_us) {

@@ -113,7 +113,7 @@ def test_conv1x1_mfma(shape, couts):
         x = b.input(*shape)
         for c in couts:
             b.conv1x1(x, c)
-    check_all_nodes(single_op(build), (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_DEVICE_RESIDENT))
+    check_all_nodes(single_op(build), (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT))
 
 
 @pytest.mark.parametrize("shape,cout", [((1, 32, 32, 32), 32), ((1, 3, 37, 41), 44), ((2, 5, 9, 9), 7),
@@ -412,6 +412,83 @@ def test_pool_large_tensors(shape):
         r.close()
     assert "pool3x3_col4_s1" in names and (shape[0] < 16 or "pool3x3_col4_s2" in names), names
     check_all_nodes(w, (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_DEVICE_RESIDENT))
+
+
+# Launches that tasks share in the single-stream modes against a launch per task: the same kernels on the same values, so bit for
+# bit the same, and right. Eight layers are launches of six and of two with unequal numbers of row tiles; conv1x1 with 31 column
+# blocks (the tasks' own order), 32 (dealt out to the XCDs) and numbers that are no multiple of eight. A launch is timed and traced as
+# the replay issues it: with all of its tasks.
+@pytest.mark.parametrize("op,shape,couts,kernel", [
+    ("conv1x1", (1, 37, 31, 64), (16, 1, 33, 70, 130, 192, 48, 17), "conv1x1_v1"),
+    ("conv1x1", (1, 37, 32, 63), (16, 1, 33, 70, 130, 192, 48, 17), "conv1x1_v1"),
+    ("conv1x1", (2, 100, 46, 46), (16, 1, 33, 70, 20, 31, 48, 17), "conv1x1_v2"),
+    ("conv1x1", (3, 64, 27, 27), (16, 1, 33, 20, 31, 48, 17, 5), "conv1x1_s1"),
+    ("conv1x1", (1, 64, 46, 46), (70, 130, 192, 97, 100, 80, 129, 161), "conv1x1_patch_32x64"),
+    ("conv1x1", (4, 64, 45, 47), (100, 130, 192, 97, 128, 110, 129, 161), "conv1x1_patch_64x64"),
+    ("conv3x3", (4, 96, 28, 28), (32, 70, 96, 130, 33, 64, 65, 97), "conv3x3_mfma_split_k"),
+    ("conv3x3", (16, 64, 28, 28), (70, 96, 130, 160, 90, 85, 150, 71), "conv3x3_patch_96x64"),
+    ("conv3x3", (4, 48, 60, 61), (32, 7, 16, 30, 31, 1, 20, 17), "conv3x3_patch_32x128_wide"),
+    ("conv3x3", (4, 48, 60, 61), (70, 96, 97, 100, 120, 127, 110, 128), "conv3x3_patch_64x128_wide"),
+    ("dwconv", (96, 44, 32, 32), (3, 5, 3, 5, 3, 5, 3, 5), "dwconv_lds")])
+def test_shared_launches(op, shape, couts, kernel):
+    def build(b):
+        x = b.input(*shape)
+        for c in couts:
+            if op == "conv1x1":
+                b.conv1x1(x, c)
+            elif op == "conv3x3":
+                b.conv3x3(x, c, 1, 1)
+            else:
+                b.dwconv(x, c, 1)
+    w = single_op(build)
+    n = len(w.nodes)
+    ref = forward(w, keep=range(n))
+    got = {}
+    for fusion in (True, False):
+        r = GraphRunner(w, DEV)
+        r.prepare(plan_trials=1, launch_fusion=fusion)
+        try:
+            assert {B.ng_task_kernel(r.g, v) for v in range(1, n)} == {kernel}
+            pos, launches = B.ng_get_single_launches(r.g)
+            assert sorted(pos.count(i) for i in range(launches)) == ([2, 6] if fusion else [1] * 8), pos
+            r.arena.zero_()
+            r.set_input(w.input)
+            r.replay(B.NG_MODE_GRAPH_SINGLE)
+            r.sync()
+            got[fusion] = [r.output(v) for v in range(1, n)]
+            if fusion:
+                for first in (pos.index(0), pos.index(1)):
+                    r.arena.zero_()
+                    r.set_input(w.input)
+                    B.ng_launch_task_solo(r.g, first, True)
+                    for v in range(1, n):
+                        out = r.output(v)
+                        assert np.array_equal(out, got[True][v - 1]) if pos[v] == pos[first] else not out.any(), (first, v)
+                    for v in range(1, n):
+                        assert B.ng_time_task_device(r.g, v, True, 3)[0] > 0 and B.ng_task_kernel_executed(r.g, v) == kernel
+        finally:
+            r.close()
+    for v in range(1, n):
+        assert np.array_equal(got[True][v - 1], got[False][v - 1]), v
+        assert rel_err(got[True][v - 1], ref[v]) <= TOL, v
+
+
+def test_shared_launch_of_conv1x1_with_unequal_column_blocks():
+    """Layers of two inputs, 36 and 9 column blocks, in one launch: the tasks' own order. One layer alone with 36: dealt out."""
+    def build(b):
+        x = b.input(1, 37, 48, 48)
+        p = [b.pool(x, "max", 1, 1), b.pool(x, "avg", 2, 1)]
+        c = [b.conv1x1(p[i % 2], c) for i, c in enumerate((16, 40, 33, 70, 7, 50))]
+        b.conv1x1(c[0], 19)
+    w = single_op(build)
+    r = GraphRunner(w)
+    r.schedule()
+    r.plan()
+    pos, launches = B.ng_get_single_launches(r.g)
+    kernels = {B.ng_planned_task_kernel(r.g, v) for v in range(3, 9)}
+    r.close()
+    assert kernels == {"conv1x1_v1"} and pos == [-1, 0, 0, 1, 1, 1, 1, 1, 1, 2] and launches == 3, (kernels, pos)
+    check_all_nodes(w, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_EAGER_SINGLE))
 
 
 # dwconv on large tensors of small planes: whole planes through LDS, four outputs side by side per thread; both filter
