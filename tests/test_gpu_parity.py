@@ -512,6 +512,25 @@ def test_dwconv_planes_through_lds(shape):
     check_all_nodes(w, (B.NG_MODE_GRAPH_MULTI, B.NG_MODE_DEVICE_RESIDENT))
 
 
+# Planes of one row of eight: with the border of a 5 x 5 filter 85 of them fit a workgroup's LDS (of a 3 x 3 one 128: 256 quads of
+# pixels); 66560 planes end inside a group of 85
+def test_dwconv_planes_limited_by_lds():
+    def build(b):
+        x = b.input(130, 512, 1, 8)
+        for k in (3, 5):
+            for stride in (1, 2):
+                b.dwconv(x, k, stride)
+    w = single_op(build)
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        names = {B.ng_task_kernel(r.g, v) for v in range(1, len(w.nodes))}
+    finally:
+        r.close()
+    assert names == {"dwconv_lds"}, names
+    check_all_nodes(w, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT))
+
+
 @pytest.mark.parametrize("n,cin,cout", [(1, 2048, 1000), (3, 100, 10), (8, 33, 5), (32, 2048, 1000), (9, 64, 7),
                                         (1024, 70, 1000),      # a batch large enough for the LDS-tiled kernel, with a bias
                                         (2048, 64, 100)])      # ... and for the kernel with the activations pixel-major in LDS

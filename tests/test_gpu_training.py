@@ -252,7 +252,7 @@ def test_training_depthwise_backward_kernels(shape, kernel):
 
 def test_training_depthwise_planes_limited_by_lds():
     """Planes of one row of eight: 85 of them fit a workgroup's LDS with the border of a 5 x 5 filter, where 128 have 256 quads
-    of pixels; 200 planes end inside the third group. Forward, input gradient and weight gradient."""
+    of pixels; 200 planes end inside the third group. Input gradient."""
     from workloads.model import Builder
     b = Builder("depthwise_flat")
     pw = b.conv1x1(b.input(40, 5, 1, 8), 5)
@@ -262,6 +262,21 @@ def test_training_depthwise_planes_limited_by_lds():
     fwd = b.finish(rng, outputs=[f])
     seeds = {f: rng.standard_normal(fwd.nodes[f].shape).astype(np.float32)}
     assert _ragged_names(fwd, seeds, 0.01, "dwconv_dgrad") == {"dwconv_dgrad_lds"}
+    check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
+
+
+def test_training_depthwise_weight_gradient_in_passes_limited_by_lds():
+    """The same planes, 180 images of 512 channels: a weight gradient's chunk is all images, three passes of 85 planes and less
+    (128 with a 3 x 3 filter: two)."""
+    from workloads.model import Builder
+    b = Builder("depthwise_flat_passes")
+    pw = b.conv1x1(b.input(180, 5, 1, 8), 512)
+    f = b.fc(b.add_n([b.global_avgpool(b.dwconv(pw, k, s)) for k in (3, 5) for s in (1, 2)]), 4)
+    rng = np.random.default_rng(13)
+    b.draw_weights(rng, 0.3, "random")
+    fwd = b.finish(rng, outputs=[f])
+    seeds = {f: rng.standard_normal(fwd.nodes[f].shape).astype(np.float32)}
+    assert _ragged_names(fwd, seeds, 0.01, "dwconv_wgrad") == {"dwconv_wgrad"}
     check_training(fwd, seeds, 0.01, (B.NG_MODE_GRAPH_SINGLE, B.NG_MODE_DEVICE_RESIDENT), end_to_end=False)
 
 
