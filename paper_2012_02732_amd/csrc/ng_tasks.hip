@@ -398,13 +398,13 @@ PwChoice choose_pw(const ng_graph* g, int v) {
 }
 // conv3x3 with at least 8 input channels runs as an implicit GEMM with K = 9 Cin
 constexpr long kC3LdsMinCols = 2048;      // measured: below this the 16 x 16 tiles (more workgroups, shorter K loops each) win
-// The patch-stationary kernels: rows and pixels of a tile; pm: what a run's rows of whole width may need (it decides between the
-// kernels for narrow and for wide images); a tile's time while the chip is full of them (64: one of 64 x 64), from 430 layers of 9 x 9 to
-// 130 x 130, 16 - 384 output channels, strides of 1 and 2: choose_patch_kernel takes the fastest of the kernels, or one within 5 % of it.
-struct PatchKernel { int kid, tm, tn, pm; double cost; };
-constexpr PatchKernel kPatchKernels[] = {{KID_C3_P64, 64, 64, 256, 64}, {KID_C3_P96, 96, 64, 256, 94}, {KID_C3_Q32, 32, 128, 640, 68},
-                                         {KID_C3_Q64, 64, 64, 640, 73}, {KID_C3_Q128, 64, 128, 640, 117}, {KID_C3_R32, 32, 128, 640, 74},
-                                         {KID_C3_R128, 64, 128, 640, 140}, {KID_C3_SK, 32, 32, c3_patch_pixels(KID_C3_SK), 0}};
+// The patch-stationary kernels: rows and pixels of a tile; a tile's time while the chip is full of them (64: one of 64 x 64), from 430
+// layers of 9 x 9 to 130 x 130, 16 - 384 output channels, strides of 1 and 2: choose_patch_kernel takes the fastest of the kernels, or one
+// within 5 % of it.
+struct PatchKernel { int kid, tm, tn; double cost; };
+constexpr PatchKernel kPatchKernels[] = {{KID_C3_P64, 64, 64, 64}, {KID_C3_P96, 96, 64, 94}, {KID_C3_Q32, 32, 128, 68},
+                                         {KID_C3_Q64, 64, 64, 73}, {KID_C3_Q128, 64, 128, 117}, {KID_C3_R32, 32, 128, 74},
+                                         {KID_C3_R128, 64, 128, 140}, {KID_C3_SK, 32, 32, 0}};
 // Largest patch a run of tn consecutive output pixels can need: the rows it touches (a run can start at the end of a
 // row), stride apart, plus two, each W + 2 pad wide.
 long patch_pixels(long tn, long W, long Ho, long Wo, long stride, long pad) {
@@ -449,14 +449,19 @@ bool patch_reaches(const Shape& in, const Shape& out) {
 // matrix cores busy on its own (x 1.15; tiles of 64 x 128 over one or two blocks of channels, mostly filling patches, x 1.25: two rounds
 // of 64 x 64 take 10.6 - 10.9 us there, 13 layers of 32 channels, and one of 64 x 128 10.9 - 11.2; with 48 channels 13.2 and 12.6). Tiles are the runs of the strips: narrow strips have short runs, which count in full (128
 // images of 64 x 33 x 33 to 384 channels, stride 2: six runs of 64 x 128 with 256 pixels of patch instead of two, 222 us; counted as
-// two it was taken before 64 x 64 with 119 and, with 640 pixels, 64 x 128 with 93).
+// two it was taken before 64 x 64 with 119 and, with 640 pixels, 64 x 128 with 93). The kernels for narrow images take images whose
+// patches hold rows of whole width, those with 640 pixels only strides of 2 (at a stride of 1 32 x 128 takes 19.8 - 62 us there, 15.3 - 50
+// with 256), and 32 x 128 with 256 only strides of 1 (2: 16 images of 64 x 45 x 45 -> 32 17.3, 64 x 64 with 384 13.1). The others take any
+// width (4 images of 64 channels, stride 1, LDS-staged GEMM and now: 159 x 159 -> 32 66 / 30 us, 224 x 224 -> 64 161 / 72, 300 x 300 -> 96
+// 527 / 210; 16 images, stride 2: 90 x 90 -> 64 35 / 25, 127 x 127 -> 32 54 / 23, 200 x 200 -> 192 405 / 225).
 int choose_patch_kernel(const Shape& in, const Shape& out, long stride, long pad) {
     if (!patch_reaches(in, out)) return KID_NONE;
     int best = KID_NONE;
     double best_cost = 0;
     for (const PatchKernel& k : kPatchKernels) {
-        if (k.kid == KID_C3_SK || patch_pixels(k.tn, in.w, out.h, out.w, stride, pad) > k.pm) continue;
-        if (k.tm == 32 && out.c > 32) continue;
+        const bool narrow = k.kid == KID_C3_P64 || k.kid == KID_C3_P96;
+        if (k.kid == KID_C3_SK || (narrow && patch_pixels(k.tn, in.w, out.h, out.w, stride, pad) > c3_patch_pixels(k.kid))) continue;
+        if ((k.tm == 32 && out.c > 32) || (stride == 1 ? c3_patch_pixels(k.kid) == 640 : k.kid == KID_C3_Q32)) continue;
         const Strips strips = choose_strips(k.kid, k.tn, out.h, out.w, stride);
         if (strips.width == 0) continue;
         const long rounds = ceil_div(out.n * strips.runs * ceil_div(out.c, k.tm), 256);
@@ -481,7 +486,9 @@ PwChoice choose_c3(const ng_graph* g, int v) {
     // 196 / 41.5 / 43 (240). Where they don't apply (a stride of 2), from 96 tiles of 64 x 64 on the large tiles: 30 x 30 ->
     // 14 x 14 288 -> 384 six images 80 / 47 (144), one image of 35 x 35 -> 17 x 17 27 / 46 (30). 22 more layers of 64 - 512 channels
     // around the first line, 64 x 64 tiles / these: 120 - 144 tiles 10.3 - 53 / 7.4 - 30.4 (six, these 20 - 45 % faster), 156 - 160
-    // 10.6 - 23.9 / 10.6 - 21.5, 180 - 192 10.5 - 52.5 / 10.7 - 40.6, 200 - 250 10.9 - 22.6 / 12.9 - 25.0 (these 9 - 33 % slower). 14 more
+    // 10.6 - 23.9 / 10.6 - 21.5, 180 - 192 10.5 - 52.5 / 10.7 - 40.6, 200 - 250 10.9 - 22.6 / 12.9 - 25.0 (these 9 - 33 % slower). Alone
+    // these still win up to three 32 x 32 tiles on a compute unit (27 layers 0.73 - 0.99 of the time, one 1.06); but siblings share launches, which
+    // fill the chip with large tiles: with that line the Inception-style network on six images takes 1058 us instead of 1026. 14 more
     // with a stride of 2 around the second, gathering kernel / 64 x 64: 48 tiles 35 / 44.5, 60 - 96 within 7 % of each other, 108
     // 26 / 18 and 67 / 47.5.
     if (!knob("NG_NO_PATCH_KERNELS")) {

@@ -207,6 +207,12 @@ def test_concat_partly_in_place(nested):
     ((2, 32, 60, 101), 32, 1, 0, "conv3x3_patch_32x128_wide"),
     ((7, 48, 40, 131), 5, 1, 1, "conv3x3_patch_32x128_wide"),
     ((4, 48, 149, 147), 64, 1, 1, "conv3x3_patch_64x128_wide"),
+    # wider than whole rows of the patches ever were
+    ((1, 48, 37, 301), 32, 1, 1, "conv3x3_patch_32x128_wide"),
+    ((2, 16, 61, 225), 70, 1, 0, "conv3x3_patch_64x128_wide"),
+    ((7, 32, 99, 180), 31, 2, 1, "conv3x3_patch_32x128_large"),
+    ((8, 48, 131, 201), 64, 2, 0, "conv3x3_patch_64x128_large"),
+    ((2, 80, 41, 310), 64, 2, 1, "conv3x3_patch_64x64_wide"),
     ((32, 48, 35, 36), 96, 1, 1, "conv3x3_patch_96x64")])
 def test_conv3x3_patch_kernels_on_strips(shape, cout, stride, pad, kernel):
     w = single_op(lambda b: b.conv3x3(b.input(*shape), cout, stride, pad))

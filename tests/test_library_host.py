@@ -756,9 +756,10 @@ def test_kernel_choice_of_the_patch_stationary_convolutions():
     assert _kernels_on((32, 384, 8, 8), [c3(768)]) == ["conv3x3_patch_96x64"]
     # wide rows and thousands of tiles: 64 x 128
     assert _kernels_on((32, 32, 147, 147), [c3(64)]) == ["conv3x3_patch_64x128_wide"]
-    # 24 input channels are not whole blocks of 16; a run of 64 pixels of a 299-wide image can need 4 x 301 pixels of patch
+    # 24 input channels are not whole blocks of 16
     assert _kernels_on((2, 24, 97, 96), [c3(40)]) == ["conv3x3_lds_64x64"]
-    assert _kernels_on((1, 16, 299, 299), [c3(64)]) == ["conv3x3_lds_64x64"]
+    # any width in strips (one image of 299 x 299: 14 us against 42 of the LDS-staged GEMM)
+    assert _kernels_on((1, 16, 299, 299), [c3(64)]) == ["conv3x3_patch_64x128_wide"]
     # few tiles: K over the wavefronts; not with 32 channels, not where 32 pixels need a patch of more than 160 pixels (38 wide: 160,
     # 39 wide: 164; stride 2); six images of 14 x 14 at a stride of 2 are 144 tiles of 64 x 64, one is 24
     assert _kernels_on((1, 64, 38, 38), [c3(64)]) == _kernels_on((40, 64, 8, 8), [c3(64)]) == ["conv3x3_mfma_split_k"]
@@ -779,6 +780,16 @@ def test_kernel_choice_counts_the_runs_of_the_strips():
     assert _kernels_on((256, 32, 31, 31), [c3(32, 1)]) == _kernels_on((256, 48, 19, 19), [c3(16, 1)]) == ["conv3x3_patch_32x128_large"]
     assert _kernels_on((128, 64, 13, 13), [c3(384, 1)]) == _kernels_on((256, 96, 15, 15), [c3(96, 0)]) == ["conv3x3_patch_96x64"]
     assert _kernels_on((128, 64, 15, 15), [c3(192, 1)]) == ["conv3x3_patch_64x64_wide"]
+
+
+@pytest.mark.parametrize("stride,cout,kernels", [(1, 32, ["64x64", "32x128_wide"]), (1, 64, ["64x64", "64x64_wide", "64x128_wide"]),
+                                                 (2, 32, ["64x64_wide", "32x128_large"]), (2, 64, ["64x64_wide", "64x128_large"])])
+def test_kernel_choice_of_conv3x3_on_wide_images(stride, cout, kernels):
+    """Four images of 32 channels, 47 to 300 columns: a patch-stationary kernel everywhere, never back to the LDS-staged GEMM."""
+    seen = set()
+    for size in list(range(47, 129, 9)) + list(range(157, 164)) + [193, 224, 257, 300]:
+        seen.update(_kernels_on((4, 32, size, size), [lambda b, x: b.conv3x3(x, cout, stride, 1)]))
+    assert seen == {"conv3x3_patch_" + k for k in kernels}
 
 
 def test_kernel_choice_of_conv1x1_pool_and_the_networks():
