@@ -6,7 +6,7 @@
 // of one of each per task. The kernels are those of the tasks themselves (one instantiation per kernel id, so nothing is shared
 // with other kernels' registers); a workgroup finds its task by its index and takes that task's argument block from the kernel
 // arguments with uniform loads. Launches and time of a replay, one task at a time -> gathered: training step of a NAS cell, batch 32
-// 132 -> 63, 1049 -> 822 us, batch 96 2107 -> 1822 us, ten images of 27 x 27 635 -> 405 us; Inception-style network at batch 1
+// 132 -> 62, 1049 -> 817 us, batch 96 2107 -> 1812 us, ten images of 27 x 27 635 -> 400 us; Inception-style network at batch 1
 // 92 -> 56, 719 -> 585 us, six images 103 -> 65, 1148 -> 1039 us. The order this takes is that of plan_single_launches.
 #include "ng_kernels.hip"
 
@@ -67,8 +67,8 @@ __global__ __launch_bounds__(kBlock, min_waves(KID)) void timed_gathered_kernel(
     X(KID_PAIR_PW32) X(KID_POOL_DGRAD) X(KID_POOL_DGRAD_LDS) X(KID_SLICE_PAD) X(KID_SMALL_GEMM)
 
 // conv1x1 from this many column blocks on: they are dealt out to the XCDs (xcd_share). In the tiles' own order the row tiles of a
-// column block run on up to 8 XCDs and each fetches the block: 387 MB a launch on average for the 1 x 1 convolutions at the heads
-// of the Inception-style modules at batch 32, 70 MB being what they have to read and write. Four layers from 768 channels of
+// column block run on up to 8 XCDs and each of those reads the block into its own L2. Dealt out, the launches of 64 x 64 tiles of the
+// Inception-style network at batch 32 read 1.58 GB from memory (12 launches; 1.88 in 34 of one task each in their own order). Four layers from 768 channels of
 // 17 x 17 in one launch 94 -> 85 us, three of 288 channels and 35 x 35 60 -> 55; the whole network 3585 -> 3545 us. With fewer
 // column blocks eight of them are too coarse a unit: 19 blocks are three for some XCDs and two for others.
 constexpr int kXcdColumns = 32;

@@ -756,8 +756,9 @@ __device__ __forceinline__ f32x16 split_sum(const f32x16& high, const f32x16& lo
 // instructions. 64 rows x 128 pixels: 2 x 2 wavefronts. 64 x 64 and 32 x 128: two wavefronts side by side and K over two pairs (WK), by taps: of the nine
 // of a block one pair takes five and the other four, in turns. 96 x 64: two wavefronts in each pair, of which one owns the upper 32 rows
 // and the other the lower ones, and each one half of the middle rows.
-// What bounds it: power. While these kernels run the clock goes down to 1.6 - 1.9 GHz (2.4 nominal), matrix cores busy 60 % of the
-// cycles; the register-only loop of the same products reaches 302 - 354 TFLOP/s at 1.8 - 2.1 GHz. Without the bank conflicts at the ends of
+// What bounds it is no one unit: by the counters of single launches of the layers of an Inception-style network at batch 32 matrix cores
+// are busy in 32 - 37 % of the cycles (32 x 128: 24), LDS in 19 - 25 % (wide 64 x 64: 45), in more than half of those with conflicts, and
+// memory moves up to 3.6 TB/s. Without the bank conflicts at the ends of
 // rows, with half the barriers or three instead of two wavefronts per SIMD it takes the same time. Before, a wavefront owned 32 x 32
 // (96 rows: 64 x 32), and wide images had patches of up to 640 pixels, whole rows. Layers at batch 32, us before and after: 147 x 147 32 -> 64
 // 274 -> 256, 149 x 149 32 -> 32 165 -> 141, 73 x 73 80 -> 192 296 -> 282, 35 x 35 96 -> 96 59.8 -> 53.8, 35 x 35 288 -> 384 stride 2
@@ -1775,8 +1776,8 @@ __device__ __forceinline__ void load_filter(const float* w, int p0, int g, int C
 // thread; the taps then need no bounds) and every thread computes four outputs side by side, stored with one 128-bit store.
 // In a row that is no multiple of four the last quad of the input starts four pixels before the end, and the last quad of the
 // output is stored value by value. Vector instructions bound it: with single LDS values (bank conflicts in 2 of 3 LDS cycles), the border
-// cleared value by value and divisions by the plane's sizes 5 x 5 on 96 images of 44 channels of 32 x 32 took 14.9 us, with quads 10.8
-// (3.2 TB/s); 3 x 3 9.1 and 9.7, on 88 channels of 16 x 16 6.7 and 6.2.
+// cleared value by value and divisions by the plane's sizes 5 x 5 on 96 images of 44 channels of 32 x 32 took 12.8 us, with quads 9.1
+// (3.8 TB/s); 3 x 3 7.1 - 7.6 and 7.3 - 7.5, on 88 channels of 16 x 16 5.2 and 4.7 (by the device's clock, both in turn).
 // ------------------------------------------------------------------------------------
 template <int K, int S, bool FIN, class Wait>
 __device__ __forceinline__ void dwconv_lds_impl(const DwArgs& a, int tile, float* smem, int tid, bool live, Wait& wait) {
