@@ -445,15 +445,16 @@ bool patch_reaches(const Shape& in, const Shape& out) {
     return in.c % 16 == 0 && in.n * in.c * in.h * in.w * 4 < (1L << 31) && 9 * in.c * (out.c + 95) * 6 < (1L << 31);
 }
 // Which patch kernel a conv3x3 gets (KID_NONE: none fits). Decided from shapes: a compute unit works its workgroups off side by
-// side, so the estimate is (tiles per compute unit, rounded up) x a tile's time; one lone workgroup per compute unit cannot keep the
-// matrix cores busy on its own (x 1.15; tiles of 64 x 128 over one or two blocks of channels, mostly filling patches, x 1.25: two rounds
-// of 64 x 64 take 10.6 - 10.9 us there, 13 layers of 32 channels, and one of 64 x 128 10.9 - 11.2; with 48 channels 13.2 and 12.6). Tiles are the runs of the strips: narrow strips have short runs, which count in full (128
-// images of 64 x 33 x 33 to 384 channels, stride 2: six runs of 64 x 128 with 256 pixels of patch instead of two, 222 us; counted as
-// two it was taken before 64 x 64 with 119 and, with 640 pixels, 64 x 128 with 93). The kernels for narrow images take images whose
-// patches hold rows of whole width, those with 640 pixels only strides of 2 (at a stride of 1 32 x 128 takes 19.8 - 62 us there, 15.3 - 50
-// with 256), and 32 x 128 with 256 only strides of 1 (2: 16 images of 64 x 45 x 45 -> 32 17.3, 64 x 64 with 384 13.1). The others take any
-// width (4 images of 64 channels, stride 1, LDS-staged GEMM and now: 159 x 159 -> 32 66 / 30 us, 224 x 224 -> 64 161 / 72, 300 x 300 -> 96
-// 527 / 210; 16 images, stride 2: 90 x 90 -> 64 35 / 25, 127 x 127 -> 32 54 / 23, 200 x 200 -> 192 405 / 225).
+// side, so the estimate is (tiles per compute unit, rounded up) x a tile's time. One lone workgroup per compute unit cannot keep the
+// matrix cores busy on its own: x 1.15, and x 1.25 for 64 x 128 over one or two blocks of channels, mostly filling patches (13 layers of 32
+// channels: two rounds of 64 x 64 take 10.6 - 10.9 us there and one of 64 x 128 10.9 - 11.2; with 48 channels 13.2 and 12.6).
+// Tiles are the runs of the strips: narrow strips have short runs, which count in full. 128 images of 64 x 33 x 33 to 384 channels,
+// stride 2: 64 x 128 with 256 pixels of patch has six runs instead of two and takes 222 us; 64 x 64 takes 119, 64 x 128 with 640 pixels 93.
+// The kernels for narrow images take images whose patches hold rows of whole width. Those with 640 pixels take only strides of 2 (at a
+// stride of 1 32 x 128 takes 19.8 - 62 us, with 256 pixels 15.3 - 50), 32 x 128 with 256 only strides of 1 (2: 16 images of
+// 64 x 45 x 45 -> 32 17.3 us, 64 x 64 with 384 13.1). The others take any width (4 images of 64 channels, stride 1, LDS-staged GEMM / now:
+// 159 x 159 -> 32 66 / 30 us, 224 x 224 -> 64 161 / 72, 300 x 300 -> 96 527 / 210; 16 images, stride 2: 90 x 90 -> 64 35 / 25,
+// 127 x 127 -> 32 54 / 23, 200 x 200 -> 192 405 / 225).
 int choose_patch_kernel(const Shape& in, const Shape& out, long stride, long pad) {
     if (!patch_reaches(in, out)) return KID_NONE;
     int best = KID_NONE;
