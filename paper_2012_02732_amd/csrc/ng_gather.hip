@@ -72,6 +72,7 @@ __global__ __launch_bounds__(kBlock, min_waves(KID)) void timed_gathered_kernel(
 // 17 x 17 in one launch 94 -> 85 us, three of 288 channels and 35 x 35 60 -> 55; the whole network 3585 -> 3545 us. With fewer
 // column blocks eight of them are too coarse a unit: 19 blocks are three for some XCDs and two for others.
 constexpr int kXcdColumns = 32;
+constexpr long kMaxWorkgroups = (1L << 32) / kBlock;            // a launch has fewer than 2^32 work items
 
 template <int KID>
 void fill(const std::vector<const Task*>& tasks, SingleLaunch& out) {
@@ -81,7 +82,9 @@ void fill(const std::vector<const Task*>& tasks, SingleLaunch& out) {
     if constexpr (is_pw_columns(KID)) {
         bool same = true;
         for (int i = 1; i < n; ++i) same = same && p.task[i].tiles_n == p.task[0].tiles_n;
-        if (same && p.task[0].tiles_n >= kXcdColumns) p.eights = (p.task[0].tiles_n + 7) / 8;
+        long rows = 0;
+        for (int i = 0; i < n; ++i) rows += p.task[i].mtiles;
+        if (same && p.task[0].tiles_n >= kXcdColumns && (p.task[0].tiles_n + 7L) / 8 * 8 * rows < kMaxWorkgroups) p.eights = (p.task[0].tiles_n + 7) / 8;
     }
     long total = 0;
     for (int i = 0; i < kGatherMax; ++i) {
@@ -93,7 +96,7 @@ void fill(const std::vector<const Task*>& tasks, SingleLaunch& out) {
     }
     if (p.eights > 0) total *= 8L * p.eights;
     else if (n == 1) return;                                    // launched as it is
-    if (total <= 0 || total >= (1L << 31)) return;
+    if (total <= 0 || total >= kMaxWorkgroups) return;
     out.fn = reinterpret_cast<const void*>(&gathered_kernel<KID>);
     out.timed_fn = reinterpret_cast<const void*>(&timed_gathered_kernel<KID>);
     out.grid = (unsigned)total;

@@ -143,6 +143,10 @@ void gradients_left_in_parts(const ng_graph* g, const std::vector<Task>& tasks, 
     }
 }
 
+// Workgroups that tasks share a launch up to: a launch can have fewer than 2^32 work items, 2^24 workgroups, and column blocks that are
+// dealt out and tasks in pairs are rounded up. From there on a launch gap is less than a thousandth of a launch.
+constexpr long kGatherTiles = 1L << 23;
+
 // The launches of the single-stream modes, in order, each a list of launched tasks; false if some task has found no place. `gather`:
 // launches of one kernel that do not depend on each other (a cell's depthwise convolutions, the 1 x 1 convolutions at the head of
 // an Inception module, the gradients of both) become one launch, for which the launches are taken in another order than the
@@ -163,6 +167,10 @@ bool plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, con
         for (int v : node_of) launches.emplace_back(1, v);
         return true;
     }
+    // workgroups of each launch, with those that a task in the same launch would have by itself
+    std::vector<long> tiles(m, 0);
+    for (int v = 0; v < n; ++v)
+        if (tasks[v].fn && fused_into[v] != v) tiles[index[fused_into[v] >= 0 ? fused_into[v] : v]] += tasks[v].ntiles;
     // dependencies between launches: whoever writes (part of) a tensor before whoever reads it
     std::vector<std::vector<int>> writers(n), next(m);
     std::vector<int> waiting(m, 0);
@@ -256,9 +264,11 @@ bool plan_single_launches(const ng_graph* g, const std::vector<Task>& tasks, con
             k->ready.clear(), k->open = 0;
             std::fill(k->behind.begin(), k->behind.end(), 0);
         }
-        for (size_t at = 0; at < now.size(); at += kGatherMax) {
+        for (size_t at = 0, q; at < now.size(); at = q) {
             launches.emplace_back();
-            for (size_t q = at; q < std::min(now.size(), at + kGatherMax); ++q) launches.back().push_back(node_of[now[q]]);
+            long total = 0;
+            for (q = at; q < now.size() && q < at + kGatherMax && (q == at || total + tiles[now[q]] <= kGatherTiles); ++q)
+                launches.back().push_back(node_of[now[q]]), total += tiles[now[q]];
         }
         for (int i : now) ready.erase(i), state[i] = LAUNCHED, ++placed;
         for (int i : now)

@@ -1084,6 +1084,25 @@ def test_single_stream_launches_of_a_wide_graph_are_planned_in_no_time(op):
     assert t < 2.0, t
 
 
+def test_single_stream_launches_stay_within_what_a_launch_can_have():
+    """Seven tasks of four million workgroups: six of them are more than the 2^24 (2^32 work items) that one launch can have."""
+    from workloads.model import Builder
+    b = Builder("large")
+    x = b.conv1x1(b.input(1, 1, 1023, 1023), 1000)
+    outs = [b.bn_act(x) for _ in range(7)]
+    rng = np.random.default_rng(0)
+    b.draw_weights(rng, 0.3, "random")
+    r = GraphRunner(b.finish(rng, outputs=outs))
+    r.schedule()
+    r.plan()
+    pos, launches = B.ng_get_single_launches(r.g)
+    kernels = {B.ng_planned_task_kernel(r.g, v) for v in outs}
+    r.close()
+    assert kernels == {"bn_act"} and sorted(set(pos) - {-1}) == list(range(launches))
+    workgroups = -(-1000 * 1023 * 1023 // 256)
+    assert max(pos.count(i) for i in range(1, launches)) * workgroups < 2 ** 24, pos
+
+
 def test_single_stream_kernels_that_launch_alone_do_not_go_last():
     """A task of a kernel that always launches alone and one of a kernel that shares launches are ready at the start, another one of
     the latter waits for the former: it goes first, then both of the other kernel in one launch."""
