@@ -990,7 +990,9 @@ int ng_resident_trace(ng_graph* g, int enable, unsigned long long* ticks) {
     }
     if (enable) {
         if (!rt.plan.trace) NG_HIP(hipMalloc(reinterpret_cast<void**>(&rt.plan.trace), bytes));
-        NG_HIP(hipMemset(rt.plan.trace, 0, bytes));
+        // on the stream of the replays: it may be one that does not wait for the null stream, and a clearing that comes
+        // late takes readings away
+        NG_HIP(hipMemsetAsync(rt.plan.trace, 0, bytes, rt.streams[0]));
     } else if (rt.plan.trace) {
         NG_HIP(hipFree(rt.plan.trace));
         rt.plan.trace = nullptr;

@@ -788,6 +788,28 @@ def test_device_resident_timeline_respects_the_dag():
         r.close()
 
 
+def test_device_resident_timeline_beside_work_on_the_null_stream():
+    """Work that waits on the null stream when tracing is switched on: the readings are cleared before the replay writes them, not
+    when that work is done."""
+    w = workloads.make("tiny_cell")
+    r = GraphRunner(w, DEV)
+    r.prepare()
+    try:
+        B.ng_replay_mode(r.g, B.NG_MODE_DEVICE_RESIDENT)
+        B.ng_replay(r.g); B.ng_sync(r.g)
+        busy = torch.empty(1 << 28, device=DEV)
+        torch.cuda.synchronize()
+        for _ in range(100):
+            busy.fill_(1.0)                                     # 1 GiB each: about 20 ms in all
+        B.ng_resident_trace(r.g, 1)
+        B.ng_replay(r.g); B.ng_sync(r.g)
+        torch.cuda.synchronize()
+        tr = B.ng_resident_trace(r.g, 0, fetch=True)
+        assert all(tr[v] is not None and 0 <= tr[v][0] <= tr[v][3] < 1e5 for v, nd in enumerate(w.nodes) if nd.op != "input"), tr
+    finally:
+        r.close()
+
+
 def test_device_resident_long_lists_reload_records():
     """300 tiny dependent tasks: with one XCD and one-tile tasks, single workgroups get lists of
     more records than they hold in LDS at a time, so the reload between chunks of a list is
